@@ -176,7 +176,14 @@ int ozaki2_moduli(int num_moduli, int32_t *p, int32_t *kinds);
  *   off[4] uint8  [n_pad x k_pad]  Bbar (column j of op(B) as line j; accurate mode),
  *          k-blocked with n_pad lines
  *   off[5] uint8  [M x m_pad x k_pad]  digit slices of A' (slice order below), each
- *          k-blocked like Abar (INT8 residues as two's-complement bytes)
+ *          k-blocked like Abar (INT8 residues as two's-complement bytes).  FP8
+ *          lists with more than four output tiles (m_pad n_pad / 65536) hold
+ *          the same digits as 6-bit E2M3 codes (sign, 5-bit magnitude) from the
+ *          same offset, slice q at q (3/4) m_pad k_pad: line i, k h is code
+ *          h % 32 (lowest bits first) of the 24 bytes of lane
+ *          l = (i % 64) / 4 + 16 ((h % 128) / 32) in the 1536-byte fragment
+ *          i % 4 of line group i / 64 of 128-k stage h / 128 (stages outermost);
+ *          a fragment holds the first 16 bytes of its 64 lanes, then their last 8
  *   off[6] uint8  [M x n_pad x k_pad]  digit slices of B'
  *   off[7] int16  [N x n_pad x m_pad]  C'_l, entry (i, j) at l*n_pad*m_pad + j*m_pad + i;
  *          with k parts (ozaki2_set_split) one such copy per part, q*N*n_pad*m_pad
@@ -306,8 +313,8 @@ int ozaki2_get_schedule(void);
  * calling thread's subsequent batched calls, or -1 (default) to leave it to
  * the autotuner.  config / 3 is the tile program of the 256 x 256 output
  * tiles (0: eight waves of 128 x 64 outputs, two per SIMD; 1: four waves of
- * 128 x 128, one per SIMD); config % 3 the split-K limit (at most 1, 2 or 4
- * k parts).  Every configuration gives bit-identical results.  Returns 0, or
+ * 128 x 128, one per SIMD; the FP8 lists have the first only, and 3 .. 5 then
+ * act as 0 .. 2); config % 3 the split-K limit (at most 1, 2 or 4 k parts).  Every configuration gives bit-identical results.  Returns 0, or
  * -1 for a value outside -1..5 (the setting is then unchanged).
  */
 int ozaki2_set_schedule(int config);

@@ -292,11 +292,26 @@ bool valid_trans(char c) {
 
 bool is_trans(char c) { return !(c == 'N' || c == 'n'); }
 
+// Whether a single call's residue products run on E2M3 digits (k_residue6)
+// rather than E4M3 ones: FP8 lists with more than kE4M3Tiles output tiles in
+// the call, or in a full block of a blocked call (every block of a call has
+// the same format: op(A)'s digits serve a whole row of blocks).  Results are the same bits.  8192^3, N = 12: 8.55 against 12.7
+// ms, 4096^3 1.15 against 1.75.  Up to four tiles the digit slices stay E4M3
+// in the k-blocked layout that ozaki2_workspace_layout documents for
+// inspection (their launches leave most CUs idle in either format).  A batched
+// call of an FP8 list has E2M3 digits throughout: its problems share one
+// persistent launch.
+constexpr int64_t kE4M3Tiles = 4;
+
+int use_fp6(int list, int64_t mbp, int64_t nbp) {
+  return list != OZ2_MODULI_INT8 && (mbp / kGemmTIW) * (nbp / kGemmTJ) > kE4M3Tiles;
+}
+
 // Problem descriptor of one call whose workspace starts at ws (layout L).
 Problem make_problem(char transA, char transB, int64_t m, int64_t n, int64_t k, double alpha,
                      const double *A, int64_t lda, const double *B, int64_t ldb, double beta,
                      double *C, int64_t ldc, int N, uint8_t *ws, const Layout &L,
-                     const Tables *dt, const Tables *ht) {
+                     const Tables *dt, const Tables *ht, int fp6) {
   Problem P;
   memset(&P, 0, sizeof(P));
   const bool tA = is_trans(transA), tB = is_trans(transB);
@@ -310,7 +325,7 @@ Problem make_problem(char transA, char transB, int64_t m, int64_t n, int64_t k, 
   P.B.k = k;
   P.B.sr = tB ? 1 : ldb;
   P.B.sh = tB ? ldb : 1;
-  P.g = Geometry{m, n, k, L.mp, L.np, L.kp, N, L.M, ht->nsq, ht->nka, g_ts.list};
+  P.g = Geometry{m, n, k, L.mp, L.np, L.kp, N, L.M, ht->nsq, ht->nka, g_ts.list, 0};
   Work &w = P.w;
   w.amax = (uint64_t *)(ws + L.off[10]);
   w.flags = (uint32_t *)(ws + L.off[11]);
@@ -338,6 +353,7 @@ Problem make_problem(char transA, char transB, int64_t m, int64_t n, int64_t k, 
   P.mode = g_ts.mode;
   P.parts = L.parts;
   P.bparts = P.mode == OZ2_MODE_FAST ? 1 : L.bparts;
+  P.g.fp6 = fp6;
   return P;
 }
 
@@ -390,13 +406,17 @@ int enqueue_scaling(const Problem &P, hipStream_t st, Marks &mark) {
 int enqueue_products(const Problem &P, hipStream_t st, Marks &mark, bool res_a = true,
                      bool res_b = true) {
   // steps 4-6: integers, residues and FP8 digits
-  if (res_a) OZ2_TRY(launch_quant_family(kFamResA, &P, nullptr, st));
-  if (res_b) OZ2_TRY(launch_quant_family(kFamResB, &P, nullptr, st));
+  const bool fp6 = P.g.fp6 != 0;
+  if (res_a) OZ2_TRY(launch_quant_family(fp6 ? kFamRes6A : kFamResA, &P, nullptr, st));
+  if (res_b) OZ2_TRY(launch_quant_family(fp6 ? kFamRes6B : kFamResB, &P, nullptr, st));
   mark();
   // steps 7-8: residue products and their reduction modulo p (every k part
   // of a kind in one launch)
-  for (int f : {kFamGemmSq, kFamGemmKa, kFamGemmI8})
-    OZ2_TRY(launch_gemm_family(f, &P, nullptr, st));
+  if (fp6)
+    OZ2_TRY(launch_gemm_family(kFamGemm6, &P, nullptr, st));
+  else
+    for (int f : {kFamGemmSq, kFamGemmKa, kFamGemmI8})
+      OZ2_TRY(launch_gemm_family(f, &P, nullptr, st));
   mark();
   // steps 9-10: CRT and inverse scaling
   OZ2_TRY(launch_crt_family(&P, nullptr, P.limbs, P.g.N, st));
@@ -461,7 +481,10 @@ int enqueue_blocked(const Problem &P, int64_t mb, int64_t nb, hipStream_t st) {
 // 256 x 256 tile, two per SIMD; 1 = four waves of 128 x 128, one per SIMD)
 // and the split-K limit (config % 3: at most 1, 2 or 4 k parts for the
 // problems that parts_alloc allows to split).  Config 0 is the default.
+// The FP8 lists have the one tile program of k_residue6: their configurations
+// 3 .. 5 are 0 .. 2.
 constexpr int kNumConfigs = 6;
+int distinct_configs(bool int8) { return int8 ? kNumConfigs : 3; }
 int config_waves(int c) { return c / 3 == 0 ? 8 : 4; }
 int config_max_parts(int c) { return c % 3 == 0 ? 1 : (c % 3 == 1 ? 2 : 4); }
 
@@ -490,6 +513,7 @@ struct GLaunch {
 // Problems whose workspaces fit together, run as one set of grouped launches.
 struct SubBatch {
   std::vector<GLaunch> launches;
+  bool int8;
   int limbs;
   int N;  // number of moduli (every problem of a batch has the same)
 };
@@ -763,19 +787,21 @@ void build_subbatch(const std::vector<Problem> &probs, ImageWriter &W, SubBatch 
     L.G.total = start[np];
     sb->launches.push_back(L);
   };
+  sb->int8 = probs[0].g.list == OZ2_MODULI_INT8;
+  const Family resA = sb->int8 ? kFamResA : kFamRes6A;
+  const Family resB = sb->int8 ? kFamResB : kFamRes6B;
   // every problem of a batch has the calling thread's mode
   if (probs[0].mode == OZ2_MODE_FAST) {
-    for (int f : {kFamFill, kFamLmaxA, kFamLmaxB, kFamNormA, kFamNormB, kFamFinal, kFamResA,
-                  kFamResB})
+    for (int f : {kFamFill, kFamLmaxA, kFamLmaxB, kFamNormA, kFamNormB, kFamFinal, resA, resB})
       add(f, at_probs, -1);
   } else {
     for (int f : {kFamFill, kFamLmaxA, kFamLmaxB, kFamBarA, kFamBarB, kFamBgemm, kFamDecide,
-                  kFamFixup, kFamFinal, kFamResA, kFamResB})
+                  kFamFixup, kFamFinal, resA, resB})
       add(f, at_probs, -1);
   }
   const uint32_t zero2[2] = {0u, 0u};
   const size_t at_counters = W.put(zero2, sizeof(zero2));
-  for (int c = 0; c < kNumConfigs; ++c) {
+  for (int c = 0; c < distinct_configs(sb->int8); ++c) {
     std::vector<Problem> pc(probs);
     std::vector<ProductItem> items;
     for (int q = 0; q < np; ++q) {
@@ -815,7 +841,7 @@ void build_subbatch(const std::vector<Problem> &probs, ImageWriter &W, SubBatch 
       L.off_items = W.put(items.data(), sizeof(ProductItem) * items.size());
       L.off_counters = at_counters;
       L.items = (int64_t)items.size();
-      L.int8 = probs[0].g.list == OZ2_MODULI_INT8;
+      L.int8 = sb->int8;
       sb->launches.push_back(L);
     }
     add(kFamCrt, at_pc, c);
@@ -827,8 +853,8 @@ int family_group(int fam) {
   switch (fam) {
     case kFamBgemm: case kFamBreduce: return 1;
     case kFamDecide: case kFamFixup: case kFamFinal: return 2;
-    case kFamResA: case kFamResB: return 3;
-    case kFamGemmSq: case kFamGemmKa: case kFamGemmI8: case kFamPersist: return 4;
+    case kFamResA: case kFamResB: case kFamRes6A: case kFamRes6B: return 3;
+    case kFamGemmSq: case kFamGemmKa: case kFamGemmI8: case kFamGemm6: case kFamPersist: return 4;
     case kFamCrt: return 5;
     default: return 0;
   }
@@ -851,7 +877,7 @@ int enqueue_subbatch(const SubBatch &sb, int config, int cus, hipStream_t st, Ma
     return OZ2_SUCCESS;
   };
   for (const GLaunch &L : sb.launches) {
-    if (L.config >= 0 && L.config != config) continue;
+    if (L.config >= 0 && L.config != config % distinct_configs(sb.int8)) continue;
     const int gq = family_group(L.fam);
     if (gq < g0 || gq > g1) continue;
     if (advance(gq) != OZ2_SUCCESS) return OZ2_ERR_HIP;
@@ -914,7 +940,7 @@ int dgemm_fixed(char transA, char transB, int64_t m, int64_t n, int64_t k, doubl
   if (L.total > res.ws_bytes) return OZ2_ERR_SCRATCH;
   const Tables *dt = res.tables + (size_t)ts.list * kMaxN + (num_moduli - 1);
   const Problem P = make_problem(transA, transB, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc,
-                                 num_moduli, res.ws, L, dt, ht);
+                                 num_moduli, res.ws, L, dt, ht, use_fp6(ts.list, L.mbp, L.nbp));
   if (L.mbp < L.mp || L.nbp < L.np) return enqueue_blocked(P, L.mbp, L.nbp, st);
   Marks none{&ts, st, false};
   return enqueue_single(P, st, none);
@@ -1113,7 +1139,7 @@ int ozaki2_dgemm(char transA, char transB, int64_t m, int64_t n, int64_t k, doub
   int r = get_workspace(dev, L.total, &ws, &have);
   if (r != OZ2_SUCCESS) return r;
   const Problem P = make_problem(transA, transB, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc,
-                                 num_moduli, ws, L, dt, ht);
+                                 num_moduli, ws, L, dt, ht, use_fp6(ts.list, L.mbp, L.nbp));
   const bool blocked = L.mbp < L.mp || L.nbp < L.np;
   const int64_t mb = L.mbp, nb = L.nbp;
 
@@ -1309,7 +1335,7 @@ int ozaki2_dgemm_batched(int count, const char *transA, const char *transB, cons
       if (used + L.total > have) flush();
       cur.push_back(make_problem(transA[q], transB[q], m[q], n[q], k[q], alpha[q], A[q], lda[q],
                                  B[q], ldb[q], beta[q], C[q], ldc[q], num_moduli, ws + used, L,
-                                 dt, ht));
+                                 dt, ht, ts.list != OZ2_MODULI_INT8));
       used += L.total;
       for (int64_t v : {m[q], n[q], k[q]}) p->shape_key.push_back(v);
     }
@@ -1376,7 +1402,7 @@ int ozaki2_dgemm_batched(int count, const char *transA, const char *transB, cons
     // real pass)
     r = enqueue_subbatch(sb, 0, cus, st, none, nullptr, 0, 3);
     if (r != OZ2_SUCCESS) return r;
-    for (int c = 0; c < kNumConfigs; ++c) {
+    for (int c = 0; c < distinct_configs(sb.int8); ++c) {
       r = enqueue_subbatch(sb, c, cus, st, none, ts.ev, 4, 4);
       if (r != OZ2_SUCCESS) return r;
       float t = 0.0f;

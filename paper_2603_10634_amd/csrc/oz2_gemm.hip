@@ -442,7 +442,7 @@ __device__ __forceinline__ void karatsuba_tile_w(const uint8_t *Asl, const uint8
                                                  int16_t *__restrict__ planes,
                                                  const Tables *__restrict__ tab, int64_t mp,
                                                  int64_t np, int64_t kp, int64_t kbeg, int nk,
-                                                 int accumulate, int l, int64_t i0, int64_t j0,
+                                                 int l, int64_t i0, int64_t j0,
                                                  uint8_t *lds, int tid) {
   const int sl0 = (int)uni(tab->slice0[l]);
   const int p = (int)uni(tab->p[l]);
@@ -454,7 +454,6 @@ __device__ __forceinline__ void karatsuba_tile_w(const uint8_t *Asl, const uint8
   resident(sl0, p, __float_as_int(inv), mul_a);
   resident(mul_b, mul_c, second, second);
   resident_ptr(planes, planes);
-  resident(accumulate, accumulate, accumulate, accumulate);
   const int64_t sA = mp * kp, sB = np * kp;
   const uint8_t *A0 = Asl + (int64_t)sl0 * sA + i0 * 64;
   const uint8_t *B0 = Bsl + (int64_t)sl0 * sB + j0 * 64;
@@ -488,37 +487,12 @@ __device__ __forceinline__ void karatsuba_tile_w(const uint8_t *Asl, const uint8
     for (int ti = 0; ti < TBW; ++ti) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        int r = smod_i32(mul_c * (int)acc[tj][ti][v], p, inv);
+        const int r = smod_i32(mul_c * (int)acc[tj][ti][v], p, inv);
         const int64_t i = i0 + wi * 32 * TBW + ti * 32 + (lane & 31);
         const int64_t j = j0 + wj * 128 + tj * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
         int16_t *dst = out + j * mp + i;
-        if (accumulate) r = smod_i32(r + (int)*dst, p, inv);
         *dst = (int16_t)r;
       }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
-// acc = m (acc mods q) mods r, one 16-value MFMA tile at a time, in FP32,
-// with the reductions of fold_w (x - rint(x q^-1) q, exact); 1/r = 0 skips
-// the second reduction.
-template <int TBW>
-__device__ __forceinline__ void fold_g(v16f (&acc)[4][TBW], float q, float inv_q, float m,
-                                       float r, float inv_r) {
-  pin_agpr(acc);
-#pragma unroll
-  for (int tj = 0; tj < 4; ++tj)
-#pragma unroll
-    for (int ti = 0; ti < TBW; ++ti) {
-      v16f t16;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float x = acc[tj][ti][v];
-        const float y = fmaf(-rintf(x * inv_q), q, x) * m;
-        t16[v] = fmaf(-rintf(y * inv_r), r, y);
-      }
-      acc[tj][ti] = t16;
-      asm volatile("" : "+a"(acc[tj][ti]));
       __builtin_amdgcn_sched_barrier(0);
     }
 }
@@ -563,7 +537,7 @@ __device__ __forceinline__ void square_tile_w(const uint8_t *Asl, const uint8_t 
                                               int16_t *__restrict__ planes,
                                               const Tables *__restrict__ tab, int64_t mp,
                                               int64_t np, int64_t kp, int64_t kbeg, int nk,
-                                              int accumulate, int l, int64_t i0, int64_t j0,
+                                              int l, int64_t i0, int64_t j0,
                                               uint8_t *lds, int tid) {
   const int sl0 = (int)uni(tab->slice0[l]);
   const int p = (int)uni(tab->p[l]);
@@ -573,7 +547,6 @@ __device__ __forceinline__ void square_tile_w(const uint8_t *Asl, const uint8_t 
   resident(sl0, p, __float_as_int(inv), s);
   resident(__float_as_int(inv_s), s, s, s);
   resident_ptr(planes, planes);
-  resident(accumulate, accumulate, accumulate, accumulate);
   const int64_t sA = mp * kp, sB = np * kp;
   const uint8_t *A0 = Asl + (int64_t)sl0 * sA + i0 * 64;
   const uint8_t *B0 = Bsl + (int64_t)sl0 * sB + j0 * 64;
@@ -605,11 +578,10 @@ __device__ __forceinline__ void square_tile_w(const uint8_t *Asl, const uint8_t 
     for (int ti = 0; ti < TBW; ++ti) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        int r = smod_i32((int)acc[tj][ti][v], p, inv);
+        const int r = smod_i32((int)acc[tj][ti][v], p, inv);
         const int64_t i = i0 + wi * 32 * TBW + ti * 32 + (lane & 31);
         const int64_t j = j0 + wj * 128 + tj * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
         int16_t *dst = out + j * mp + i;
-        if (accumulate) r = smod_i32(r + (int)*dst, p, inv);
         *dst = (int16_t)r;
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -691,107 +663,23 @@ __global__ __launch_bounds__(64 * NW_RES, 1) void k_residue_gemm(Problem P) {
   int16_t *planes = uni(P.w.planes) + uni((int64_t)part * g.N) * mp * np;
   const int tid = threadIdx.x;
   if (KIND == 0)
-    square_tile_w<NW_RES>(uni(P.w.Asl), uni(P.w.Bsl), planes, uni(P.tab), mp, np, kp, k0, nk, 0,
-                          l, uni(c.x * TIW), uni(c.y * TJ), lds, tid);
+    square_tile_w<NW_RES>(uni(P.w.Asl), uni(P.w.Bsl), planes, uni(P.tab), mp, np, kp, k0, nk, l,
+                          uni(c.x * TIW), uni(c.y * TJ), lds, tid);
   else if (KIND == 1)
     karatsuba_tile_w<NW_RES>(uni(P.w.Asl), uni(P.w.Bsl), planes, uni(P.tab), mp, np, kp, k0, nk,
-                             0, l, uni(c.x * TIW), uni(c.y * TJ), lds, tid);
+                             l, uni(c.x * TIW), uni(c.y * TJ), lds, tid);
   else
     int8_tile_w<NW_RES>(uni(P.w.Asl), uni(P.w.Bsl), planes, uni(P.tab), mp, np, kp, k0, nk, 0, l,
                         uni(c.x * TIW), uni(c.y * TJ), lds, tid);
 }
 
-// One 256 x 256 tile of any FP8 modulus (square or Karatsuba) as three
-// single-product passes with two folds, every step from the tables:
-//   pass 1: acc = D(a1, b1);   fold: acc = m1 (acc mods q1), then mods r1
-//   pass 2: acc += D(a2, b2);  fold: acc = m2 (acc mods q2), then mods r2
-//   pass 3: acc += D(a3, b3);  result smod(m3 acc, p)
-// where D(a, b) is the product of A's digit slice a and B's slice b.
-//   square p = s^2 (as square_tile_w): passes (1, 2), (2, 1), (2, 2); the
-//     first fold reduces modulo p (X mod s is all that matters), the second
-//     is s (acc mods s) with no further reduction; m3 = 1;
-//   Karatsuba (as karatsuba_tile_w): passes X, Y, Z, folds a, b modulo p
-//     (each followed by a reduction modulo p), m3 = c.
-// A fold "then mods r" with no reduction uses 1/r = 0.  Every fold leaves
-// |acc| <= 2^10, so each pass's FP32 accumulation stays exact.
-template <int NW>
-__device__ __forceinline__ void fp8_tile_w(const uint8_t *Asl, const uint8_t *Bsl,
-                                           int16_t *__restrict__ planes,
-                                           const Tables *__restrict__ tab, int64_t mp,
-                                           int64_t np, int64_t kp, int64_t kbeg, int nk,
-                                           int accumulate, int l, int64_t i0, int64_t j0,
-                                           uint8_t *lds, int tid) {
-  const int sl0 = (int)uni(tab->slice0[l]);
-  const int p = (int)uni(tab->p[l]);
-  const float inv = __int_as_float((int)uni(__float_as_int(tab->inv_p[l])));
-  const bool square = uni(tab->kind[l]) == 0;
-  const int s = (int)uni(tab->s[l]);
-  const float inv_s = __int_as_float((int)uni(__float_as_int(tab->inv_s[l])));
-  const int second = square ? 0 : (int)uni(tab->kfold[l][3]);
-  // passes: (A slice, B slice)
-  const int a1 = 0, b1 = square ? 1 : 0;
-  const int a2 = square ? 1 : second, b2 = square ? 0 : second;
-  const int a3 = square ? 1 : 3 - second, b3 = square ? 1 : 3 - second;
-  // folds
-  const float q2 = square ? (float)s : (float)p, iq2 = square ? inv_s : inv;
-  const float m1 = square ? 1.0f : (float)uni(tab->kfold[l][0]);
-  const float m2 = square ? (float)s : (float)uni(tab->kfold[l][1]);
-  const float ir2 = square ? 0.0f : inv;
-  const int m3 = square ? 1 : (int)uni(tab->kfold[l][2]);
-  resident(sl0, p, __float_as_int(inv), s);
-  resident(__float_as_int(inv_s), second, m3, m3);
-  resident_ptr(planes, planes);
-  resident(accumulate, accumulate, accumulate, accumulate);
-  const int64_t sA = mp * kp, sB = np * kp;
-  const uint8_t *A0 = Asl + (int64_t)sl0 * sA + i0 * 64;
-  const uint8_t *B0 = Bsl + (int64_t)sl0 * sB + j0 * 64;
-
-  constexpr int NWW = NW, TBW = TB<NW>();
-  v16f acc[4][TBW];
-#pragma unroll
-  for (int tj = 0; tj < 4; ++tj)
-#pragma unroll
-    for (int ti = 0; ti < TBW; ++ti)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[tj][ti][v] = 0.0f;
-
-  pin_agpr(acc);
-  kloop_w<NWW, false, true>(B0 + b1 * sB, A0 + a1 * sA, np, mp, kbeg, nk, lds, acc, tid,
-                            B0 + b2 * sB, A0 + a2 * sA);
-  fold_g(acc, (float)p, inv, m1, (float)p, inv);
-  kloop_w<NWW, true, true>(B0 + b2 * sB, A0 + a2 * sA, np, mp, kbeg, nk, lds, acc, tid,
-                           B0 + b3 * sB, A0 + a3 * sA);
-  fold_g(acc, q2, iq2, m2, (float)p, ir2);
-  kloop_w<NWW, true, false>(B0 + b3 * sB, A0 + a3 * sA, np, mp, kbeg, nk, lds, acc, tid);
-
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wj = wave / (NWW / 2), wi = wave % (NWW / 2);
-  int16_t *out = planes + (int64_t)l * np * mp;
-#pragma unroll
-  for (int tj = 0; tj < 4; ++tj)
-#pragma unroll
-    for (int ti = 0; ti < TBW; ++ti) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        int r = smod_i32(m3 * (int)acc[tj][ti][v], p, inv);
-        const int64_t i = i0 + wi * 32 * TBW + ti * 32 + (lane & 31);
-        const int64_t j = j0 + wj * 128 + tj * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-        int16_t *dst = out + j * mp + i;
-        if (accumulate) r = smod_i32(r + (int)*dst, p, inv);
-        *dst = (int16_t)r;
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-}
-
-// The residue products of a whole batch in one launch: each workgroup takes
-// the next item of the work list (tile x modulus x k part of one problem,
-// longest first) until the list is exhausted; the k chunks of an item run in
-// order inside the workgroup, accumulating into its plane copy.  INT8 = the
-// INT8 arm's products, else the FP8 moduli of either kind.  The last
-// workgroup to finish clears the counters for the next launch, so the launch
+// The INT8 residue products of a whole batch in one launch (the FP8 lists':
+// k_residue6): each workgroup takes the next item of the work list (tile x
+// modulus x k part of one problem, longest first) until the list is
+// exhausted; the k chunks of an item run in order inside the workgroup,
+// accumulating into its plane copy.  The last workgroup to finish clears the counters for the next launch, so the launch
 // needs no memset and replays from a graph.
-template <int NW, bool INT8>
+template <int NW>
 __global__ __launch_bounds__(64 * NW, 1) void k_residue_persistent(WorkList W) {
   __shared__ __attribute__((aligned(1024))) uint8_t lds[LDS_RING];
   __shared__ uint32_t item_s;
@@ -815,12 +703,8 @@ __global__ __launch_bounds__(64 * NW, 1) void k_residue_persistent(WorkList W) {
       // k-loop instead of being hoisted above it and kept live (spilled)
       int tid = threadIdx.x;
       asm volatile("" : "+v"(tid));
-      if (INT8)
-        int8_tile_w<NW>(uni(P.w.Asl), uni(P.w.Bsl), planes, uni(P.tab), mp, np, kp, kb,
-                        (int)(len / BK), kb > k0 ? 1 : 0, l, i0, j0, lds, tid);
-      else
-        fp8_tile_w<NW>(uni(P.w.Asl), uni(P.w.Bsl), planes, uni(P.tab), mp, np, kp, kb,
-                       (int)(len / BK), kb > k0 ? 1 : 0, l, i0, j0, lds, tid);
+      int8_tile_w<NW>(uni(P.w.Asl), uni(P.w.Bsl), planes, uni(P.tab), mp, np, kp, kb,
+                      (int)(len / BK), kb > k0 ? 1 : 0, l, i0, j0, lds, tid);
     }
   }
   if (threadIdx.x == 0) {
@@ -1001,15 +885,12 @@ hipError_t launch_gemm_persistent(int nw, bool int8, const WorkList &W, int64_t 
   if (W.count <= 0) return hipSuccess;
   if (grid > W.count) grid = W.count;
   if (grid <= 0 || grid > 0x7FFFFFFFll || W.count > 0xFFFFFFFFll) return hipErrorInvalidValue;
+  if (!int8) return launch_gemm6_list(W, grid, st);
   const dim3 gr((unsigned)grid);
-  if (nw == 8 && !int8)
-    hipLaunchKernelGGL((k_residue_persistent<8, false>), gr, dim3(64 * 8), 0, st, W);
-  else if (nw == 4 && !int8)
-    hipLaunchKernelGGL((k_residue_persistent<4, false>), gr, dim3(64 * 4), 0, st, W);
-  else if (nw == 8)
-    hipLaunchKernelGGL((k_residue_persistent<8, true>), gr, dim3(64 * 8), 0, st, W);
+  if (nw == 8)
+    hipLaunchKernelGGL((k_residue_persistent<8>), gr, dim3(64 * 8), 0, st, W);
   else if (nw == 4)
-    hipLaunchKernelGGL((k_residue_persistent<4, true>), gr, dim3(64 * 4), 0, st, W);
+    hipLaunchKernelGGL((k_residue_persistent<4>), gr, dim3(64 * 4), 0, st, W);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
@@ -1020,6 +901,7 @@ hipError_t launch_gemm_family(int fam, const Problem *P, const Group *G, hipStre
   // products run as one persistent launch)
   const bool grouped = G != nullptr;
   if (grouped && fam != kFamBgemm) return hipErrorInvalidValue;
+  if (fam == kFamGemm6) return launch_gemm6(*P, st);
   Problem p1;
   Group g1;
   memset(&p1, 0, sizeof(p1));

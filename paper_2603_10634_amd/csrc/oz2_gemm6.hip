@@ -1,0 +1,460 @@
+// Residue products on E2M3 digits (v_mfma_f32_16x16x128_f8f6f4, FP32
+// accumulation).
+//
+// Every digit of Sections III-B and III-C is an integer of magnitude at most
+// 16, and E2M3 (6 bits, steps of 1/8 up to 2, OCP MX) holds d / 8 exactly for
+// each of them, so the products are those of the E4M3 digits: integers over
+// 64, exact in FP32 below 2^24 / 64.  The format halves the MFMA's cycles (16
+// per 16 x 16 x 128 step against 32) and takes a quarter off the bytes of
+// every slice.
+//
+// What bounds it: power.  A register-only loop on digits of this range
+// sustains 7.2 PFLOP/s with the 16 x 16 x 128 form and 6.2 with 32 x 32 x 64
+// (E4M3: 4.2), the chip lowering its clock to 1.5-1.6 GHz; hence the 16-wide
+// form, whose accumulators cost half as much register traffic per operation.
+// At 8192^3, N = 12 the 36 products run at 4.6 PFLOP/s (8.55 ms; 12.7 ms on
+// E4M3), with the MFMA busy 65 % of the cycles at 1.62 GHz.  Other orders of
+// the same work (a barrier per 64 or per 256 k, the barrier in the middle of
+// a stage, wave priorities, 32 x 32 x 64 steps at 71 % busy and 1.40 GHz)
+// came out within 2 % of one another or slower; the loads from L2 into LDS
+// alone account for a fifth of the time.
+//
+// Layout (digit6): a slice of R lines is cut into stages of 128 k, a stage
+// into groups of 64 lines, a group into the fragments of its lines r = q (mod
+// 4), q = 0 .. 3; fragment q holds, for lane l = r / 4 + 16 (h / 32), the 32
+// digits of line r and k h .. h + 31 as 24 bytes: the first 16 bytes of the 64
+// lanes in lane order, then their last 8.  One stage of 256 lines is 24 KB of
+// contiguous memory, LDS is filled by copies of it, and every fragment read
+// (one ds_read_b128 and one ds_read_b64 per lane) covers consecutive bytes
+// across the lanes, free of bank conflicts.  Interleaving the lines by four
+// gives each lane four consecutive rows i of its column j in the accumulators,
+// so the int16 planes are stored 8 bytes per lane.
+//
+// Workgroup: 256 (j) x 256 (i) outputs, 8 waves of 128 x 64 (128 accumulator
+// registers each, two waves per SIMD), one per CU, walking the (part,
+// modulus, tile) items blockIdx, blockIdx + grid, ...  The stages of an
+// item's three passes and of the next item form one sequence through an LDS
+// ring of three 48 KB slots, so the loads never stop: the next pass's first
+// stages land during the fold between the passes, the next item's during the
+// epilogue.
+#include <string.h>
+
+#include "oz2_internal.h"
+
+namespace oz2 {
+
+namespace {
+
+typedef int v2i __attribute__((ext_vector_type(2)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+constexpr int NW = 8;                       // waves: 2 (j) x 4 (i), each 128 x 64
+constexpr int TJ = 8, TI = 4;               // MFMA tiles of 16 x 16 per wave
+constexpr int FRAG = 1536;                  // bytes of a fragment: 16 lines x 128 k
+constexpr int SIDE = kGemmTJ / 16 * FRAG;   // one side of a stage: 256 lines, 24 KB
+constexpr int STAGE = 2 * SIDE;             // B side, then A side
+constexpr int S = 3;                        // ring slots
+constexpr int64_t kCUs = 256;               // one workgroup per CU
+constexpr int RING = S * STAGE;             // 144 KB
+constexpr int LPW = STAGE / 1024 / NW;      // 1 KB loads per wave and stage
+static_assert(LPW == 6 && kGemmTJ == 256 && kGemmTIW == 256 && kPad % (2 * kStage6) == 0,
+              "tile shape");
+
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt((N & 0xF) | (0x7 << 4) | (0xF << 8) | ((N >> 4) << 14));
+}
+__device__ __forceinline__ void wait_lgkm0() {
+  __builtin_amdgcn_s_waitcnt(0xF | (0x7 << 4) | (0x0 << 8) | (0x3 << 14));
+}
+
+__device__ __forceinline__ int uni32(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ v4f mma6(v8i a, v8i b, v4f c) {
+  // cbsz = blgp = 2 selects E2M3 for both operands
+  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 2, 2, 0, 0, 0, 0);
+}
+
+// A fragment: lane l's 32 digits (192 bits) as its first 16 bytes in one run
+// of 64 lanes and its last 8 in another.
+__device__ __forceinline__ v8i frag(const uint8_t *p, int lane) {
+  const v4i lo = *(const v4i *)(p + 16 * lane);
+  const v2i hi = *(const v2i *)(p + 1024 + 8 * lane);
+  return __builtin_shufflevector(lo, __builtin_shufflevector(hi, hi, 0, 1, -1, -1), 0, 1, 2, 3, 4,
+                                 5, -1, -1);
+}
+
+__device__ __forceinline__ void dma16(const uint8_t *base, uint32_t voff, uint32_t lds_off) {
+  asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base),
+               "{m0}"(lds_off)
+               : "memory");
+}
+
+__device__ __forceinline__ uint32_t lds_offset(const uint8_t *p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const uint8_t *)p;
+}
+
+// One tile of one modulus over a k range: what the loads need.
+struct Item {
+  const uint8_t *A, *B;   // slice 0 of the modulus at (k0, i0) / (k0, j0)
+  int64_t sA, sB;         // bytes between slices of a side
+  int64_t stA, stB;       // bytes of a stage of all lines of a side
+  int nk;                 // stages per pass
+  int ab;                 // slices of the passes: 2 bits each, a1 b1 a2 b2 a3 b3
+};
+
+// The stage to load next: its item, pass and place, and the item after it.
+struct Producer {
+  Item it, next;
+  const uint8_t *pB, *pA;
+  int left, pass;
+};
+
+__device__ __forceinline__ void start_pass(Producer &p) {
+  const int sl = p.it.ab >> (4 * p.pass);
+  p.pA = p.it.A + (int64_t)(sl & 3) * p.it.sA;
+  p.pB = p.it.B + (int64_t)((sl >> 2) & 3) * p.it.sB;
+  p.left = p.it.nk;
+}
+
+// On to the next stage: of the pass, of the item's next pass or of the next item.
+__device__ __forceinline__ void advance(Producer &p) {
+  p.pA += p.it.stA;
+  p.pB += p.it.stB;
+  if (__builtin_expect(--p.left == 0, 0)) {
+    if (++p.pass == 3) {
+      p.pass = 0;
+      p.it = p.next;
+    }
+    start_pass(p);
+  }
+}
+
+struct Lanes {
+  uint32_t vo[LPW / 2];  // byte offset of this lane in each of its wave's loads of a side
+  uint32_t ls;           // place of the wave's first load in a slot
+};
+
+// Load u (0 .. 5: three of the B side, three of the A side) of the producer's
+// stage into the slot at LDS byte address `slot`.
+template <int U>
+__device__ __forceinline__ void load(const Producer &p, const Lanes &ln, uint32_t slot) {
+  dma16(U < 3 ? p.pB : p.pA, ln.vo[U % 3], slot + ln.ls + 1024u * NW * U);
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+struct Ring {
+  uint32_t base;     // LDS byte address of the ring
+  uint32_t cur;      // slot offset of the stage being summed
+  uint32_t fill;     // slot offset of the stage being loaded
+};
+
+__device__ __forceinline__ uint32_t next_slot(uint32_t s) {
+  return s + STAGE == RING ? 0u : s + STAGE;
+}
+
+// One stage j (128 k) of a wave's 128 x 64 outputs: rows tj of four MFMAs, the
+// B fragment of row tj + 3 read and one or two of the six loads of stage j + 2
+// (into the slot stage j - 1 left) issued between them; before the last two
+// rows the barrier B_j, at which the wave's own loads of stage j + 1 have
+// landed and its reads of stage j are done; under those rows the A fragments
+// and first three B fragments of stage j + 1 are read.  ZERO: the accumulators
+// start at zero.  WAIT: wait for the loads (else they are known to be there).
+template <bool ZERO, bool WAIT>
+__device__ __forceinline__ void stage(Producer &p, const Lanes &ln, Ring &r, const uint8_t *lds,
+                                      const v8i (&fa)[TI], v8i (&fan)[TI], v8i (&fb0)[3],
+                                      v4f (&acc)[TJ][TI], int lane, int wj, int wi) {
+  const uint8_t *cur = lds + r.cur + wj * TJ * FRAG;
+  const uint32_t fill = r.base + r.fill;
+  const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
+  v8i fb[TJ];
+#pragma unroll
+  for (int t = 0; t < 3; ++t) fb[t] = fb0[t];
+#pragma unroll
+  for (int tj = 0; tj < TJ - 2; ++tj)
+#pragma unroll
+    for (int ti = 0; ti < TI; ++ti) {
+      acc[tj][ti] = mma6(fb[tj], fa[ti], ZERO ? zero : acc[tj][ti]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (ti == 0 && tj + 3 < TJ) {
+        fb[tj + 3] = frag(cur + (tj + 3) * FRAG, lane);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (tj == 0 && ti == 1) load<0>(p, ln, fill);
+      if (tj == 0 && ti == 3) load<3>(p, ln, fill);
+      if (tj == 1 && ti == 1) load<1>(p, ln, fill);
+      if (tj == 1 && ti == 3) load<4>(p, ln, fill);
+      if (tj == 2 && ti == 1) load<2>(p, ln, fill);
+      if (tj == 2 && ti == 3) load<5>(p, ln, fill);
+    }
+  advance(p);
+  r.fill = next_slot(r.fill);
+  wait_lgkm0();
+  if (WAIT) wait_vm<(S - 2) * LPW>();
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  // stage j + 1 is readable by all waves and slot j is free
+  r.cur = next_slot(r.cur);
+  const uint8_t *nb = lds + r.cur + wj * TJ * FRAG, *na = lds + r.cur + SIDE + wi * TI * FRAG;
+#pragma unroll
+  for (int tj = TJ - 2; tj < TJ; ++tj)
+#pragma unroll
+    for (int ti = 0; ti < TI; ++ti) {
+      acc[tj][ti] = mma6(fb[tj], fa[ti], ZERO ? zero : acc[tj][ti]);
+      __builtin_amdgcn_sched_barrier(0);
+      const int q = (tj - (TJ - 2)) * TI + ti;  // next: a0 b0 a1 a2 a3 b1 b2
+      if (q == 0) fan[0] = frag(na, lane);
+      if (q == 1) fb0[0] = frag(nb, lane);
+      if (q >= 2 && q <= 4) fan[q - 1] = frag(na + (q - 1) * FRAG, lane);
+      if (q == 5 || q == 6) fb0[q - 4] = frag(nb + (q - 4) * FRAG, lane);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// acc = m (acc mods q) up to a multiple of q: for an exact x (in units of
+// 1/64: q64 = q / 64, inv64 = 64 / q) with |64 x| < 2^24, x - rint(x / q) q is
+// exact in one fused multiply-add and at most q / 2 + 2 in magnitude, so the
+// result is below 258 256 < 2^17 and the next pass's sums (at most 2^23 more)
+// stay exact.
+__device__ __forceinline__ void fold(v4f (&acc)[TJ][TI], float q64, float inv64, float m) {
+#pragma unroll
+  for (int tj = 0; tj < TJ; ++tj)
+#pragma unroll
+    for (int ti = 0; ti < TI; ++ti) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float x = acc[tj][ti][v];
+        acc[tj][ti][v] = fmaf(-rintf(x * inv64), q64, x) * m;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// Where an item's tile is: a modulus, output tile and k range of a problem.
+struct Place {
+  CProblem *P;
+  int l, part, tx, ty;
+  int k0, nk;  // first k, stages per pass
+};
+
+__device__ __forceinline__ Item make_item(const Place &c, CTables *tab) {
+  const int64_t mp = c.P->g.mp, np = c.P->g.np, kp = c.P->g.kp;
+  const int sl0 = tab->slice0[c.l];
+  const int second = tab->kfold[c.l][3], third = 3 - second;
+  Item I;
+  I.sA = mp * kp / 4 * 3;
+  I.sB = np * kp / 4 * 3;
+  I.stA = mp * 96;
+  I.stB = np * 96;
+  I.A = c.P->w.Asl + sl0 * I.sA + c.k0 / kStage6 * I.stA + c.tx * (int64_t)SIDE;
+  I.B = c.P->w.Bsl + sl0 * I.sB + c.k0 / kStage6 * I.stB + c.ty * (int64_t)SIDE;
+  I.nk = c.nk;
+  I.ab = tab->kind[c.l] == 0 ? ((1 << 2) | (1 << 4) | (1 << 8) | (1 << 10))
+                             : ((second << 4) | (second << 6) | (third << 8) | (third << 10));
+  return I;
+}
+
+// Item `it` of a single problem: tiles (i fastest) within moduli within k parts.
+__device__ __forceinline__ Place place_single(CProblem *P, int it) {
+  const uint32_t tx_n = (uint32_t)(P->g.mp / kGemmTIW), ty_n = (uint32_t)(P->g.np / kGemmTJ);
+  const uint32_t N = (uint32_t)P->g.N, parts = (uint32_t)P->parts;
+  const uint32_t nb = (uint32_t)(P->g.kp / kPad);
+  const uint32_t u = (uint32_t)it, a = u / tx_n, b = a / ty_n, z = b / N;
+  const uint32_t k0 = z * nb / parts, k1 = (z + 1) * nb / parts;  // part_range, in 32 bits
+  Place c;
+  c.P = P;
+  c.l = uni32((int)(b - z * N));
+  c.part = uni32((int)z);
+  c.tx = uni32((int)(u - a * tx_n));
+  c.ty = uni32((int)(a - b * ty_n));
+  c.k0 = uni32((int)k0 * kPad);
+  c.nk = uni32((int)(k1 - k0) * (kPad / kStage6));
+  return c;
+}
+
+__device__ __forceinline__ Place place_list(const WorkList &W, int it) {
+  OZ2_CONST ProductItem *I = (OZ2_CONST ProductItem *)(uintptr_t)W.items + it;
+  Place c;
+  c.P = (CProblem *)(uintptr_t)W.probs + I->prob;
+  c.l = I->l;
+  c.part = I->part;
+  c.tx = I->tx;
+  c.ty = I->ty;
+  c.k0 = I->k0;
+  c.nk = (I->k1 - I->k0) / kStage6;
+  return c;
+}
+
+// The residue products of one problem (LIST false) or of a batch's work list:
+// per (modulus, tile, k part) the three passes of the modulus (square: A1 B2 +
+// A2 B1, fold s (. mod s), + A2 B2; Karatsuba: X, fold a, + Y, fold b, + Z,
+// times c, see the tables) into one accumulator, then the symmetric residue
+// into the modulus's int16 plane.  A pass of a list item longer than kChunkK is
+// summed in chunks of that length, each but the last reduced modulo p.  Items
+// go to the workgroups in rounds, every second one backwards: a list sorted
+// longest first comes out within 3 % of the average (512 problems log-uniform
+// in [64, 4096], and smaller batches), with no counter to fetch from.
+template <bool LIST>
+__global__ __launch_bounds__(64 * NW, 1) void k_residue6(Problem, WorkList W, int count) {
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[RING];
+  // the problem by value is the first kernel argument
+  CProblem *P1 = (CProblem *)__builtin_amdgcn_kernarg_segment_ptr();
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wj = wave >> 2, wi = wave & 3;
+  const int grid = (int)gridDim.x;
+  int round = 0, item = (int)blockIdx.x;
+  // a workgroup's item of round q; past the end: one that exists (its loads
+  // are issued and never read)
+  auto item_of = [&](int q) {
+    const int it = q * grid + (LIST && (q & 1) ? grid - 1 - (int)blockIdx.x : (int)blockIdx.x);
+    return it;
+  };
+  auto place = [&](int it) {
+    const int i = it < count ? it : (int)blockIdx.x;
+    return LIST ? place_list(W, i) : place_single(P1, i);
+  };
+  auto loads_of = [&](int it) {
+    const Place c = place(it);
+    return make_item(c, (CTables *)(uintptr_t)c.P->tab);
+  };
+  Lanes ln;
+  ln.ls = 1024u * wave;
+#pragma unroll
+  for (int u = 0; u < 3; ++u) ln.vo[u] = 1024u * (wave + NW * u) + 16u * lane;
+
+  Ring r;
+  r.base = lds_offset(lds);
+  r.cur = 0;
+  r.fill = 0;
+  Producer p;
+  p.it = loads_of(item);
+  p.next = p.it;
+  p.pass = 0;
+  start_pass(p);
+  // stages 0 .. S - 2
+#pragma unroll 1
+  for (int t = 0; t < S - 1; ++t) {
+    const uint32_t slot = r.base + r.fill;
+    load<0>(p, ln, slot);
+    load<1>(p, ln, slot);
+    load<2>(p, ln, slot);
+    load<3>(p, ln, slot);
+    load<4>(p, ln, slot);
+    load<5>(p, ln, slot);
+    advance(p);
+    r.fill = next_slot(r.fill);
+  }
+  wait_vm<0>();
+  __builtin_amdgcn_s_barrier();
+  v8i fa0[TI], fa1[TI], fb[3];
+#pragma unroll
+  for (int t = 0; t < TI; ++t) {
+    fa0[t] = frag(lds + SIDE + (wi * TI + t) * FRAG, lane);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int t = 0; t < 3; ++t) {
+    fb[t] = frag(lds + (wj * TJ + t) * FRAG, lane);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
+  for (; item < count; item = item_of(++round)) {
+    const Place c = place(item);
+    CTables *tab = (CTables *)(uintptr_t)c.P->tab;
+    const int l = c.l;
+    // the loads run at most S - 1 stages ahead, less than an item (six)
+    p.next = loads_of(item_of(round + 1));
+    // a scalar load still pending would turn every LDS wait of the loops into
+    // a full drain (both count on LGKM, out of order): wait for them here
+    asm volatile("" ::"s"(p.next.ab), "s"(p.next.A), "s"(p.next.B), "s"(p.next.nk));
+    constexpr int kMaxStages = kChunkK / kStage6;
+    v4f acc[TJ][TI];
+    // the loop over the stages [j, n) of one chunk
+    auto loop = [&](int j, int n) {
+#pragma unroll 1
+      for (; j < n; j += 2) {
+        stage<false, true>(p, ln, r, lds, fa0, fa1, fb, acc, lane, wj, wi);
+        stage<false, true>(p, ln, r, lds, fa1, fa0, fb, acc, lane, wj, wi);
+      }
+    };
+    // one pass (from stage j0 of it) and the fold that ends it: m (acc mods q)
+    // after the last chunk (m = 0: none), acc mods p after the others
+    auto pass = [&](int j0, float q, float iq, float m, float pf, float inv) {
+      int left = c.nk;
+      for (;;) {
+        const int n = LIST && left > kMaxStages ? kMaxStages : left;
+        loop(j0, n);
+        left -= n;
+        const bool last = !LIST || left == 0;
+        if (!last || m != 0.0f)
+          fold(acc, (last ? q : pf) * 0.015625f, (last ? iq : inv) * 64.0f, last ? m : 1.0f);
+        if (last) break;
+        j0 = 0;
+      }
+    };
+    const bool square = tab->kind[l] == 0;
+    const float pf = (float)tab->p[l], inv = tab->inv_p[l];
+    // every load of stage 1 had landed before the previous item's stores
+    stage<true, false>(p, ln, r, lds, fa0, fa1, fb, acc, lane, wj, wi);
+    stage<false, true>(p, ln, r, lds, fa1, fa0, fb, acc, lane, wj, wi);
+    pass(2, pf, inv, square ? 0.0f : (float)tab->kfold[l][0], pf, inv);
+    const float q2 = square ? (float)tab->s[l] : pf, iq2 = square ? tab->inv_s[l] : inv;
+    pass(0, q2, iq2, square ? q2 : (float)tab->kfold[l][1], pf, inv);
+    pass(0, pf, inv, 0.0f, pf, inv);
+    // symmetric residue, four consecutive rows i per lane: a first reduction to
+    // |r| <= p / 2 + 2, the multiplier, and a second one whose quotient is
+    // nudged by 1 / (4 p), so that an exact half (even p) goes to -p / 2 and no
+    // other value (at least 1 / (2 p) from a half) moves
+    const int64_t mp = c.P->g.mp, np = c.P->g.np;
+    const float m3 = 64.0f * (square ? 1.0f : (float)tab->kfold[l][2]);
+    const float inv64 = inv * 64.0f, q64 = pf * 0.015625f, bias = 0.25f * inv;
+    int16_t *out = c.P->w.planes + ((int64_t)c.part * c.P->g.N + l) * mp * np +
+                   ((int64_t)c.ty * kGemmTJ + wj * 128 + (lane >> 4) * 16) * mp +
+                   (int64_t)c.tx * kGemmTIW + wi * 64 + 4 * (lane & 15);
+#pragma unroll
+    for (int tj = 0; tj < TJ; ++tj) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        int res[TI];
+#pragma unroll
+        for (int ti = 0; ti < TI; ++ti) {
+          const float x = acc[tj][ti][v];
+          const float y = fmaf(-rintf(x * inv64), q64, x) * m3;
+          res[ti] = (int)fmaf(-rintf(fmaf(y, inv, bias)), pf, y);
+        }
+        const uint2 w = make_uint2(((uint32_t)res[0] & 0xFFFFu) | ((uint32_t)res[1] << 16),
+                                   ((uint32_t)res[2] & 0xFFFFu) | ((uint32_t)res[3] << 16));
+        // the next item's first two stages (their loads count with the stores)
+        if (tj == 0 && v == 0) wait_vm<0>();
+        *(uint2 *)(out + ((tj >> 2) * 64 + 4 * v + (tj & 3)) * mp) = w;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  wait_vm<0>();
+}
+
+}  // namespace
+
+hipError_t launch_gemm6(const Problem &P, hipStream_t st) {
+  const int64_t count = family_blocks(kFamGemm6, P);
+  if (count <= 0) return hipSuccess;
+  if (count > 0x7FFFFFFFll - 2 * kCUs) return hipErrorInvalidValue;
+  const dim3 gr((unsigned)(count < kCUs ? count : kCUs));
+  hipLaunchKernelGGL((k_residue6<false>), gr, dim3(64 * NW), 0, st, P, WorkList{}, (int)count);
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm6_list(const WorkList &W, int64_t grid, hipStream_t st) {
+  if (grid <= 0 || W.count > 0x7FFFFFFFll - 2 * grid) return hipErrorInvalidValue;
+  Problem none;
+  memset(&none, 0, sizeof(none));
+  hipLaunchKernelGGL((k_residue6<true>), dim3((unsigned)grid), dim3(64 * NW), 0, st, none, W,
+                     (int)W.count);
+  return hipGetLastError();
+}
+
+}  // namespace oz2

@@ -64,6 +64,8 @@ struct Geometry {
   int nsq;                    // square moduli (the first nsq of the list)
   int nka;                    // Karatsuba moduli (the next nka); the rest are INT8
   int list;                   // OZ2_MODULI_HYBRID, _KARATSUBA or _INT8
+  int fp6;                    // the digit slices hold E2M3 digits in the fragment order of
+                              // oz2_gemm6.hip (else E4M3 digits or INT8 residues, k-blocked)
 };
 
 // Workspace views of one call.
@@ -127,8 +129,8 @@ struct ProductItem {
   int32_t k0, k1;
 };
 
-// Work list of a persistent residue-product launch.  counters[0] hands out
-// items, counters[1] counts finished workgroups; both are zero between
+// Work list of a persistent residue-product launch.  For the INT8 arm,
+// counters[0] hands out items, counters[1] counts finished workgroups; both are zero between
 // launches (the last workgroup to finish clears them).
 struct WorkList {
   const Problem *probs;
@@ -151,6 +153,7 @@ constexpr int kGemmTJ = 256;  // output columns j per tile
 constexpr int kGemmTIW = 256; // output rows i per tile of the single-product kernels
                               // (Karatsuba products, bound product)
 constexpr int kGemmBK = 64;   // k per pipeline stage
+constexpr int kStage6 = 128;  // k per pipeline stage of the E2M3 products (one MFMA step)
 constexpr int kQL = 16;       // quantization passes: 16 lines x 128 k per block
 constexpr int kQK = 128;
 
@@ -171,9 +174,12 @@ enum Family : int {
   kFamFinal,      // shifts
   kFamResA,       // residues and FP8 digits
   kFamResB,
+  kFamRes6A,      // residues and E2M3 digits
+  kFamRes6B,
   kFamGemmSq,     // residue products, square moduli (every k part in one launch)
   kFamGemmKa,     // residue products, Karatsuba moduli
   kFamGemmI8,     // residue products, INT8 moduli
+  kFamGemm6,      // residue products on E2M3 digits, every FP8 modulus
   kFamCrt,        // CRT, inverse scaling, alpha / beta
   kNumFamilies
 };
@@ -231,6 +237,10 @@ __host__ __device__ inline Dims family_dims(int fam, const Problem &P) {
     case kFamNormB:
     case kFamResB:
       return {g.np / kQL, g.kp / kQK, 1};
+    case kFamRes6A:
+      return {g.mp / 64, g.kp / kStage6, 1};
+    case kFamRes6B:
+      return {g.np / 64, g.kp / kStage6, 1};
     case kFamBgemm:
       return {g.mp / kGemmTIW, g.np / kGemmTJ, P.bparts};
     case kFamBreduce:  // (the wide tile's 16 MFMA blocks per wave) per tile
@@ -249,6 +259,8 @@ __host__ __device__ inline Dims family_dims(int fam, const Problem &P) {
       const int64_t nz = fam == kFamGemmSq ? g.nsq : (fam == kFamGemmKa ? g.nka : g.N - g.nsq - g.nka);
       return {g.mp / kGemmTIW, g.np / kGemmTJ, nz * P.parts};
     }
+    case kFamGemm6:
+      return {g.mp / kGemmTIW, g.np / kGemmTJ, (int64_t)g.N * P.parts};
     case kFamCrt:
       return {(g.m + 63) / 64, (g.n + 3) / 4, 1};
     default:
@@ -292,6 +304,12 @@ __host__ __device__ inline const Tables *tables_of(const Problem &P1, const Grou
 }
 
 #if defined(__HIPCC__)
+// Wave-uniform data read from device memory: through the constant address
+// space it loads with scalar loads whatever the surrounding code stores.
+#define OZ2_CONST const __attribute__((address_space(4)))
+typedef OZ2_CONST Tables CTables;
+typedef OZ2_CONST Problem CProblem;
+
 // Segment holding block b: the last q with start[q] <= b (start is sorted;
 // empty segments repeat a value).
 __device__ __forceinline__ int find_segment(const Group &G, int64_t b) {
@@ -342,12 +360,17 @@ __device__ __forceinline__ Dims decode_block(const Dims &d, int64_t local) {
 hipError_t launch_quant_family(int fam, const Problem *P, const Group *G, hipStream_t st);
 hipError_t launch_scale_family(int fam, const Problem *P, const Group *G, hipStream_t st);
 hipError_t launch_gemm_family(int fam, const Problem *P, const Group *G, hipStream_t st);
-// The persistent residue-product launch: `grid` workgroups of nw (8 or 4)
-// waves take items of W in order until none is left; int8 selects the INT8
-// arm's products (every item's modulus is then an INT8 one), else every
-// item's modulus is a square or Karatsuba FP8 modulus.
+// The persistent residue-product launch: `grid` workgroups take the items of W
+// until none is left; int8 selects the INT8 arm's products (every item's
+// modulus is then an INT8 one, the tiles run nw = 8 or 4 waves), else every
+// item's modulus is a square or Karatsuba FP8 modulus with E2M3 digits.
 hipError_t launch_gemm_persistent(int nw, bool int8, const WorkList &W, int64_t grid,
                                   hipStream_t st);
+// The residue products on E2M3 digits of a single problem (kFamGemm6 of
+// launch_gemm_family).
+hipError_t launch_gemm6(const Problem &P, hipStream_t st);
+// The same over a work list (every item's modulus an FP8 one).
+hipError_t launch_gemm6_list(const WorkList &W, int64_t grid, hipStream_t st);
 hipError_t launch_crt_family(const Problem *P, const Group *G, int limbs, int N, hipStream_t st);
 // Device memory of the entry point that allocates nothing: a workspace and
 // the device tables of every (modulus list, N), laid out [list][N - 1].

@@ -484,6 +484,194 @@ __global__ __launch_bounds__(256) void k_residues(Problem P1, Group G) {
                 SIDE == 0 ? P.w.Asl : P.w.Bsl, tile);
 }
 
+// ---- E2M3 digits ----
+//
+// The digits of the products on E2M3 (k_residue6, oz2_gemm6.hip), in its
+// fragment order: the code of d / 8 is the sign and |d| as a 5-bit integer,
+// for |d| <= 16.
+//
+// A thread owns one line and 32 consecutive k, i.e. one lane's 24 bytes of
+// every slice, a wave 64 lines, a workgroup 64 lines x 128 k (a whole group of
+// a stage, 6 KB contiguous per slice).  Lines contiguous in memory are read
+// straight into registers, 512 bytes per load; lines with contiguous k in runs
+// of 16 k that are turned through LDS.
+//
+// Bound by vector issue.  Against the E4M3 pass (198 vector instructions per
+// input at N = 12) the set-up is two FP64 operations: a' = trunc(a 2^s) may be
+// large, NaN or infinite (the line's outputs are then NaN whatever its digits),
+// because each FP64 step takes 51 bits off it (mod_step) and a line's scale
+// exponent says how many steps its entries need; the digits are split in
+// packed FP16 (integers up to 547, exact), two per instruction, and converted
+// 32 at a time.  8192^3, N = 12, both operands: 0.83 ms, 0.99 ms before, and
+// 4.1 GB moved instead of 5.1.
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef _Float16 h32 __attribute__((ext_vector_type(32)));
+typedef uint32_t u6 __attribute__((ext_vector_type(6)));
+
+constexpr int kR6L = 64, kR6K = 128;  // lines x k per workgroup
+constexpr int kR6E = 32;              // inputs per thread
+constexpr int kR6Ld = 18;             // doubles per staged row of 16 (16-byte rows, skewed)
+
+__device__ __forceinline__ void store6(const h32 &d, uint8_t *slice, uint32_t off16,
+                                       uint32_t off8) {
+  // scale 8: the code of d / 8
+  const u6 w = __builtin_amdgcn_cvt_scalef32_pk32_fp6_f16(d, 8.0f);
+  *(uint4 *)(slice + off16) = make_uint4(w[0], w[1], w[2], w[3]);
+  *(uint2 *)(slice + off8) = make_uint2(w[4], w[5]);
+}
+
+// rint(x m) of both halves for |x m| < 512: the one rounding of x m + 1.5 2^10,
+// where FP16 has unit spacing.
+__device__ __forceinline__ h2 rint_h2(h2 x, h2 m) {
+  const h2 magic = {(_Float16)1536.0f, (_Float16)1536.0f};
+  return __builtin_elementwise_fma(x, m, magic) - magic;
+}
+
+// The digits of one modulus from f (|f| < 2^20 + 2^11, congruent to the
+// inputs): the nearest multiple of p removed in FP32 (exact, |u| <= (p + 1) / 2
+// at most at an even p's half), then, in FP16,
+//   square p = s^2: x1 = rint(u / s), x2 = u - s x1 (|u / s - x1| stays within
+//     1 / 2 although 1 / s is rounded: an odd s has no ties, and any choice
+//     does at a tie of s = 32);
+//   Karatsuba, s = 16: x1 = u / 16 away from zero, as rint of (|u| + 7.5) / 16,
+//     x2 = u - 16 x1, x3 = x1 + x2.
+// All have magnitude at most 16 for every modulus of both lists.
+template <int KIND>
+__device__ __forceinline__ void digits6(const float (&f)[kR6E], CTables *tab, int l,
+                                        uint8_t *base, int64_t slice_stride, uint32_t off16,
+                                        uint32_t off8) {
+  const float pf = (float)tab->p[l], invpf = tab->inv_p[l];
+  const h2 s2 = {(_Float16)tab->s[l], (_Float16)tab->s[l]};
+  const h2 is2 = {(_Float16)tab->inv_s[l], (_Float16)tab->inv_s[l]};
+  uint8_t *dst = base + (int64_t)tab->slice0[l] * slice_stride;
+  h32 d1, d2, d3;
+#pragma unroll
+  for (int q = 0; q < kR6E; q += 2) {
+    const float a = fmaf(-rintf(f[q] * invpf), pf, f[q]);
+    const float b = fmaf(-rintf(f[q + 1] * invpf), pf, f[q + 1]);
+    const h2 u = __builtin_bit_cast(h2, __builtin_amdgcn_cvt_pkrtz(a, b));
+    h2 x1, x2;
+    if (KIND == 0) {
+      x1 = rint_h2(u, is2);
+      x2 = __builtin_elementwise_fma(-s2, x1, u);
+    } else {
+      const uint32_t bias = (__builtin_bit_cast(uint32_t, u) & 0x80008000u) | 0x47804780u;  // 7.5
+      const h2 t = u + __builtin_bit_cast(h2, bias);
+      const h2 r16 = {(_Float16)0.0625f, (_Float16)0.0625f};
+      x1 = rint_h2(t, r16);
+      const h2 m16 = {(_Float16)-16.0f, (_Float16)-16.0f};
+      x2 = __builtin_elementwise_fma(m16, x1, u);
+      const h2 x3 = x1 + x2;
+      d3[q] = x3[0];
+      d3[q + 1] = x3[1];
+    }
+    d1[q] = x1[0];
+    d1[q + 1] = x1[1];
+    d2[q] = x2[0];
+    d2[q + 1] = x2[1];
+  }
+  store6(d1, dst, off16, off8);
+  store6(d2, dst + slice_stride, off16, off8);
+  if (KIND == 1) store6(d3, dst + 2 * slice_stride, off16, off8);
+}
+
+// x - R rint(x / R) for an integer x: with q the computed quotient (within
+// 2^-52 of x / R, relatively) it is a multiple of ulp(q) or 1 below
+// 2^-51 |x| + R / 2, i.e. of fewer than 53 bits (R < 2^21), so the fused
+// multiply-add is exact; each step takes 51 bits off a large x.
+__device__ __forceinline__ double mod_step(double x, double R, double invR) {
+  return fma(-rint(x * invR), R, x);
+}
+
+template <int KIND, int STEPS>
+__device__ __forceinline__ void kind6(const double (&x)[kR6E], CTables *tab, int l0, int l1,
+                                      uint8_t *base, int64_t slice_stride, uint32_t off16,
+                                      uint32_t off8) {
+  for (int l = l0; l < l1; l += 2) {
+    const bool two = l + 1 < l1;
+    const double R = two ? (double)(tab->p[l] * tab->p[l + 1]) : (double)tab->p[l];
+    const double invR = two ? tab->inv_pair[l] : tab->inv_pd[l];
+    float f[kR6E];
+#pragma unroll
+    for (int q = 0; q < kR6E; ++q) {
+      double y = mod_step(x[q], R, invR);
+#pragma unroll
+      for (int s = 1; s < STEPS; ++s) y = mod_step(y, R, invR);
+      f[q] = (float)y;
+    }
+    digits6<KIND>(f, tab, l, base, slice_stride, off16, off8);
+    if (two) digits6<KIND>(f, tab, l + 1, base, slice_stride, off16, off8);
+  }
+}
+
+template <int STEPS>
+__device__ __forceinline__ void moduli6(const double (&x)[kR6E], CTables *tab, int nsq, int nka,
+                                        uint8_t *base, int64_t slice_stride, uint32_t off16,
+                                        uint32_t off8) {
+  kind6<0, STEPS>(x, tab, 0, nsq, base, slice_stride, off16, off8);
+  kind6<1, STEPS>(x, tab, nsq, nsq + nka, base, slice_stride, off16, off8);
+}
+
+template <bool GROUPED, int SIDE>
+__global__ __launch_bounds__(256, 2) void k_residues6(Problem P1, Group G) {
+  __shared__ __attribute__((aligned(16))) double tile[4][kR6L * kR6Ld];
+  int64_t local;
+  const Problem &P = *locate<GROUPED>(P1, G, blockIdx.x, local);
+  const Operand &op = SIDE == 0 ? P.A : P.B;
+  const Dims d = family_dims(SIDE == 0 ? kFamRes6A : kFamRes6B, P);
+  const int64_t bx = local % d.x, by = local / d.x;
+  const int64_t R = SIDE == 0 ? P.g.mp : P.g.np, kp = P.g.kp;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t r0 = bx * kR6L, h0 = by * kR6K + 32 * wave;
+  const int64_t r = r0 + lane;
+  double x[kR6E];
+  if (op.sr == 1) {
+    // lines contiguous: lane = line
+    const bool in = r < op.lines;
+    const double *src = op.ptr + r + h0 * op.sh;
+#pragma unroll
+    for (int q = 0; q < kR6E; ++q) x[q] = in && h0 + q < op.k ? src[q * op.sh] : 0.0;
+  } else {
+    // k contiguous: runs of 16 k of each line, turned through LDS
+    double v[kR6E];
+#pragma unroll
+    for (int q = 0; q < kR6E; ++q) {
+      const int64_t rr = r0 + 4 * (q & 15) + (lane >> 4), h = h0 + 16 * (q >> 4) + (lane & 15);
+      v[q] = rr < op.lines && h < op.k ? op.ptr[rr * op.sr + h * op.sh] : 0.0;
+    }
+    double *mine = tile[wave];
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      if (half) __syncthreads();
+#pragma unroll
+      for (int q = 0; q < 16; ++q)
+        mine[(4 * q + (lane >> 4)) * kR6Ld + (lane & 15)] = v[16 * half + q];
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < 16; ++q) x[16 * half + q] = mine[lane * kR6Ld + q];
+    }
+  }
+  // a' = trunc(a 2^s); its magnitude is below 2^(e + 8)
+  const int64_t base_line = SIDE == 0 ? 0 : P.w.lineB;
+  const int s = P.w.shift[base_line + r], e = P.w.e[base_line + r];
+#pragma unroll
+  for (int q = 0; q < kR6E; ++q) x[q] = trunc(ldexp(x[q], s));
+  const int64_t slice_stride = R * kp / 4 * 3;
+  const uint32_t off16 = (uint32_t)((lane & 3) * 1536 + 16 * ((lane >> 2) + 16 * wave));
+  const uint32_t off8 = (uint32_t)((lane & 3) * 1536 + 1024 + 8 * ((lane >> 2) + 16 * wave));
+  uint8_t *base = (SIDE == 0 ? P.w.Asl : P.w.Bsl) + by * (R * 96) + bx * 6144;
+  CTables *tab = (CTables *)(uintptr_t)tables_of<GROUPED>(P1, G);
+  // |x| < 2^(e + 8): a step leaves |f| < R / 2 + 2^12 from below 2^63, two from
+  // below 2^113; the scale exponent stays below 160, so four always do
+  if (!__any(e > 55))
+    moduli6<1>(x, tab, P.g.nsq, P.g.nka, base, slice_stride, off16, off8);
+  else if (!__any(e > 105))
+    moduli6<2>(x, tab, P.g.nsq, P.g.nka, base, slice_stride, off16, off8);
+  else
+    moduli6<4>(x, tab, P.g.nsq, P.g.nka, base, slice_stride, off16, off8);
+}
+
 }  // namespace
 
 hipError_t launch_quant_family(int fam, const Problem *P, const Group *G, hipStream_t st) {
@@ -520,6 +708,8 @@ hipError_t launch_quant_family(int fam, const Problem *P, const Group *G, hipStr
     case kFamNormB: OZ2_Q2(k_bound_norm, 1) break;
     case kFamResA: OZ2_Q2(k_residues, 0) break;
     case kFamResB: OZ2_Q2(k_residues, 1) break;
+    case kFamRes6A: OZ2_Q2(k_residues6, 0) break;
+    case kFamRes6B: OZ2_Q2(k_residues6, 1) break;
     default: return hipErrorInvalidValue;
   }
 #undef OZ2_Q

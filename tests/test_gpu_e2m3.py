@@ -1,0 +1,126 @@
+"""The E2M3 path of the FP8 lists (more than four output tiles) through the C
+ABI: the stored digits, the residue planes and C against the oracle, at the
+edges of its tiles, stages and scale range."""
+import numpy as np
+import pytest
+
+import paper_2603_10634_amd as oz
+from oracle import ozaki2_ref as ref
+from workloads import phi_matrix
+
+from gpu_util import run, same_bits, split
+
+pytestmark = pytest.mark.gpu
+
+
+def _digits(r, which):
+    """M x lines x k digits decoded from the documented fragment order."""
+    mp, np_, kp, M = (r.pads[q] for q in ("mp", "np", "kp", "M"))
+    R = mp if which == "A" else np_
+    o = r.off[5 if which == "A" else 6]
+    size = R * kp // 4 * 3
+    h = np.arange(kp)
+    line = np.arange(R)[:, None]
+    frag = ((h // 128) * (R // 64) + line // 64) * 4 + line % 4
+    lane = (line % 64) // 4 + 16 * ((h % 128) // 32)
+    out = []
+    for q in range(M):
+        b = r.ws[o + q * size:o + (q + 1) * size].reshape(-1, 1536)
+        lanes = np.concatenate([b[:, :1024].reshape(-1, 64, 16), b[:, 1024:].reshape(-1, 64, 8)],
+                               axis=2)
+        bits = np.unpackbits(lanes, axis=2, bitorder="little").reshape(-1, 64, 32, 6)
+        code = bits @ (1 << np.arange(6))
+        val = np.where(code & 32, -(code & 31), code & 31).astype(np.int8)
+        out.append(val[frag, lane, h % 32])
+    return np.stack(out)
+
+
+def _check(A, B, N, ta="N", tb="N", mode="accurate", moduli="hybrid"):
+    m, k = A.shape
+    n = B.shape[1]
+    r = run(A, B, N, ta, tb, keep_ws=True, mode=mode, moduli=moduli, pad=(3, 5, 1))
+    assert r.status == 0
+    C, st = ref.emulate(A, B, N, keep_stages=True, mode=mode, moduli_set=moduli)
+    D = {"A": _digits(r, "A"), "B": _digits(r, "B")}
+    P = r.planes(N, [pm["p"] for pm in st["per_modulus"]])
+    sl = 0
+    for l, pm in enumerate(st["per_modulus"]):
+        p, square = pm["p"], pm["kind"] == "square"
+        s = int(round(p ** 0.5)) if square else 16
+        for which, want, lines in (("A", pm["dA"], m), ("B", [d.T for d in pm["dB"]], n)):
+            d = D[which][sl:sl + (2 if square else 3)].astype(np.int64)
+            assert np.abs(d).max() <= 16
+            assert not d[:, lines:].any() and not d[:, :, k:].any(), "padding"
+            u = s * d[0] + d[1]
+            w = s * want[0].astype(np.int64) + want[1].astype(np.int64)
+            assert not np.any((u[:lines, :k] - w) % p), f"residues of {which} modulo {p}"
+            if not square:
+                assert np.array_equal(d[2], d[0] + d[1])
+        sl += 2 if square else 3
+        assert np.array_equal(P[l, :n, :m].T, st["planes"][l]), f"plane {l}"
+    assert same_bits(r.C, C)
+
+
+@pytest.mark.parametrize("m,n,k,N,ta,tb,mode,moduli,phi", [
+    (513, 700, 1, 1, "N", "T", "fast", "hybrid", 1.0),        # one k of a stage
+    (1280, 64, 257, 6, "T", "N", "accurate", "hybrid", 1.0),  # five tiles, one more 256-block
+    (700, 600, 300, 12, "N", "N", "accurate", "hybrid", 0.5),
+    (600, 513, 128, 14, "T", "T", "accurate", "hybrid", 2.0),
+    (520, 770, 130, 17, "N", "N", "accurate", "hybrid", 4.0),  # a second FP64 step
+    (560, 520, 200, 33, "T", "N", "accurate", "hybrid", 6.0),  # the largest exponents
+    (600, 600, 500, 13, "N", "T", "accurate", "karatsuba", 1.0),
+])
+def test_stages(m, n, k, N, ta, tb, mode, moduli, phi):
+    print(f"E2M3 {m}x{n}x{k} N={N} {ta}{tb} {mode} {moduli} phi={phi}", flush=True)
+    _check(phi_matrix(m, k, phi, 9100 + m), phi_matrix(k, n, phi, 9200 + n), N, ta, tb, mode,
+           moduli)
+
+
+def test_special_lines():
+    A = phi_matrix(540, 150, 1.0, 9300)
+    B = phi_matrix(150, 700, 1.0, 9301)
+    A[7] = 0.0
+    A[130, 3] = np.inf
+    A[511, 149] = np.nan
+    A[200] *= 2.0 ** -1000
+    A[201] = 5e-324
+    B[:, 64] = 0.0
+    B[9, 699] = -np.inf
+    B[:, 300] *= 2.0 ** 900
+    print("E2M3 special lines", flush=True)
+    for N, mode in ((12, "accurate"), (20, "fast")):
+        r = run(A, B, N, mode=mode)
+        assert r.status == 0 and same_bits(r.C, ref.emulate(A, B, N, mode=mode))
+
+
+@pytest.mark.parametrize("moduli,N", [("hybrid", 12), ("karatsuba", 5)])
+def test_extreme_digit_sums(moduli, N):
+    # constant operands whose digits reach 16 x 16 over one accumulation of
+    # k = 2^15 (sums of 2^23 per product), rows of both signs, six tiles: every
+    # output is the 1 x k x 1 emulation's, up to sign
+    k = 32768
+    for c in (255, 199, 137, 131):
+        a, b = c / 128.0, (c + 1) / 128.0 if c < 255 else c / 128.0
+        _, st = ref.emulate(np.full((1, k), a), np.full((k, 1), b), N, keep_stages=True,
+                            moduli_set=moduli)
+        C1 = ref.emulate(np.full((1, k), a), np.full((k, 1), b), N, moduli_set=moduli)[0, 0]
+        top = max(abs(int(x[0, 0]) * int(y[0, 0])) for pm in st["per_modulus"]
+                  for x in pm["dA"] for y in pm["dB"])
+        print(f"E2M3 sums c={c}: digit products up to {top}", flush=True)
+        A = np.full((520, k), a)
+        A[1::2] *= -1.0
+        B = np.full((k, 260), b)
+        with split(1):
+            r = run(A, B, N, moduli=moduli)
+        want = np.where(np.arange(520)[:, None] % 2, -C1, C1) * np.ones((1, 260))
+        assert r.status == 0 and same_bits(r.C, want)
+
+
+@pytest.mark.parametrize("parts", [1, 3, 8])
+def test_split_and_blocked(parts):
+    # ragged k parts; blocks of which some have four tiles or fewer
+    A, B = phi_matrix(800, 2500, 1.0, 9400), phi_matrix(2500, 700, 1.0, 9401)
+    want = ref.emulate(A, B, 12)
+    with split(parts):
+        assert same_bits(run(A, B, 12).C, want)
+        assert same_bits(run(A, B, 12, "T", "T", blocking=(768, 512)).C, want)
