@@ -349,7 +349,7 @@ Problem make_problem(char transA, char transB, int64_t m, int64_t n, int64_t k, 
   P.beta = beta;
   P.C = C;
   P.ldc = ldc;
-  P.limbs = ht->limbs;
+  P.limbs = crt_shape(*ht);
   P.mode = g_ts.mode;
   P.parts = L.parts;
   P.bparts = P.mode == OZ2_MODE_FAST ? 1 : L.bparts;
@@ -1315,7 +1315,7 @@ int ozaki2_dgemm_batched(int count, const char *transA, const char *transB, cons
     auto flush = [&]() {
       if (cur.empty()) return;
       SubBatch sb;
-      sb.limbs = ht->limbs;
+      sb.limbs = crt_shape(*ht);
       sb.N = num_moduli;
       build_subbatch(cur, W, &sb);
       p->subs.push_back(std::move(sb));

@@ -187,4 +187,51 @@ __host__ __device__ __forceinline__ bool crt_reduce(const double (&acc)[L], cons
   return neg;
 }
 
+// x + y = s + e exactly.
+__host__ __device__ __forceinline__ double two_sum(double x, double y, double &e) {
+  const double s = x + y;
+  const double b = s - x;
+  e = (x - (s - b)) + (y - b);
+  return s;
+}
+
+// RN(C' 2^-t) for S = sum_q acc[q] of multiples of 2^(wbits q) (the sums of
+// cw[l][q] u_l, exact), where C' = S mods P; false if this does not decide it
+// (the caller then takes the exact integers).
+//   Q = rint(S / P) from the two highest sums: within 2^-40 of S / P, so D =
+//     S - Q P, limb by limb exact (one fused multiply-add each), is C' or off
+//     by P, and in that case |D| > P (1/2 - 2^-40);
+//   D = th + (tl + the lower errors), by exact additions of the limbs from the
+//     lowest up; the errors' sum v is off by less than 2^-50 m, m the largest
+//     of them, so RN(D) lies between RN(th + v - 2^-45 m) and RN(th + v + 2^-45
+//     m) and is both when they agree (they differ at ties, near ties, and when
+//     D is tiny against its limbs);
+//   the scaling is exact for a normal result.
+template <int L>
+__host__ __device__ __forceinline__ bool crt_rn(const double (&acc)[L],
+                                                const double *__restrict__ cP, double inv_P,
+                                                double crt_fast, int t, double &out) {
+  const double Q = rint((acc[L - 1] + (L > 1 ? acc[L > 1 ? L - 2 : 0] : 0.0)) * inv_P);
+  double r[L];
+#pragma unroll
+  for (int q = 0; q < L; ++q) r[q] = fma(-Q, cP[q], acc[q]);
+  double th = r[0], v = 0.0, m = 0.0;
+#pragma unroll
+  for (int q = 1; q < L; ++q) {
+    double e;
+    th = two_sum(r[q], th, e);
+    v = q == 1 ? e : v + e;
+    m = q == 1 ? fabs(e) : fmax(m, fabs(e));
+  }
+  const double lo = th + fma(-0x1p-45, m, v), hi = th + fma(0x1p-45, m, v);
+  out = ldexp(lo, -t);
+#if defined(__HIP_DEVICE_COMPILE__)
+  const int ex = __builtin_amdgcn_frexp_exp(lo);
+#else
+  int ex;
+  (void)frexp(lo, &ex);
+#endif
+  return lo == hi && fabs(lo) <= crt_fast && ex - t >= -1021;
+}
+
 }  // namespace oz2

@@ -10,6 +10,7 @@ namespace oz2 {
 
 constexpr int kMaxN = OZ2_MAX_MODULI;
 constexpr int kLimbs = 11;       // 32-bit limbs for S = sum_l w_l u_l (P < 2^296 for N = 33)
+constexpr int kWide = 8;         // 40-bit limbs of the CRT's fast path (P < 2^319)
 constexpr int kPad = 256;        // every dimension is padded to this multiple
 constexpr int kChunkK = 1 << 15; // longest k one residue-product accumulation covers
 constexpr int kPowT = 192;       // 2^t mod p is tabulated for t < kPowT; the integer
@@ -49,7 +50,22 @@ struct Tables {
   double P_d;                 // P rounded to double
   double inv_P_d;             // 1 / P_d (estimate of quotients S / P)
   double D;                   // largest double <= P - 1 (scale rule)
+  // the CRT's fast path: balanced limbs of wbits bits, as doubles times
+  // 2^(wbits q), of P and of the weights' representatives in (-P/2, P/2]
+  int32_t wlimbs, wbits;
+  double cP[kWide];
+  double cw[kMaxN][kWide];
 };
+
+// Wide limbs of the CRT kernel for P of `limbs` 32-bit limbs: 40 bits each, or
+// three of 41 bits where P is small enough (Tables::wlimbs).
+constexpr int wide_limbs(int limbs) { return limbs <= 3 ? limbs : limbs * 4 / 5 + (limbs < 10 && limbs % 5 != 0 ? 1 : 0); }
+static_assert(wide_limbs(4) == 4 && wide_limbs(5) == 4 && wide_limbs(6) == 5 &&
+              wide_limbs(7) == 6 && wide_limbs(8) == 7 && wide_limbs(9) == 8 &&
+              wide_limbs(10) == kWide, "32 limbs <= 40 wide limbs");
+
+// The limb counts that select the CRT kernel (launch_crt_family's `limbs`).
+inline int crt_shape(const Tables &t) { return t.limbs | t.wlimbs << 8; }
 
 // Builds the tables for N moduli of list `list` (OZ2_MODULI_HYBRID,
 // OZ2_MODULI_KARATSUBA or OZ2_MODULI_INT8) on the host.  Returns false for an
@@ -111,7 +127,7 @@ struct Problem {
   double alpha, beta;
   double *C;
   int64_t ldc;
-  int32_t limbs;       // 32-bit limbs of P (host tables), selects the CRT kernel
+  int32_t limbs;       // crt_shape of the tables: selects the CRT kernel
   int32_t mode;        // OZ2_MODE_ACCURATE or OZ2_MODE_FAST (selects the launch sequence)
   int32_t parts;       // k parts of the residue products (split-K): the CRT sums this
                        // many copies of the residue planes, each N mp np entries apart
@@ -262,7 +278,7 @@ __host__ __device__ inline Dims family_dims(int fam, const Problem &P) {
     case kFamGemm6:
       return {g.mp / kGemmTIW, g.np / kGemmTJ, (int64_t)g.N * P.parts};
     case kFamCrt:
-      return {(g.m + 63) / 64, (g.n + 3) / 4, 1};
+      return {(g.m + 63) / 64, (g.n + 7) / 8, 1};
     default:
       return {0, 1, 1};
   }
@@ -371,6 +387,7 @@ hipError_t launch_gemm_persistent(int nw, bool int8, const WorkList &W, int64_t 
 hipError_t launch_gemm6(const Problem &P, hipStream_t st);
 // The same over a work list (every item's modulus an FP8 one).
 hipError_t launch_gemm6_list(const WorkList &W, int64_t grid, hipStream_t st);
+// limbs: crt_shape of the tables.
 hipError_t launch_crt_family(const Problem *P, const Group *G, int limbs, int N, hipStream_t st);
 // Device memory of the entry point that allocates nothing: a workspace and
 // the device tables of every (modulus list, N), laid out [list][N - 1].

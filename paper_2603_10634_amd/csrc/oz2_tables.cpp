@@ -141,6 +141,38 @@ int sym(int64_t x, int p) {
   return r > p - 1 - p / 2 ? r - p : r;
 }
 
+// Balanced base-2^bits digits (each in [-2^(bits-1), 2^(bits-1)), the top one
+// what is left) of sign x, as doubles times 2^(bits q); false if they do not
+// fit in count digits.
+bool balanced_limbs(Big x, bool negative, int bits, int count, double *out) {
+  for (int q = 0; q < count; ++q) {
+    x.resize(std::max<size_t>(x.size(), 3), 0u);
+    const uint64_t lo = (uint64_t)x[0] | ((uint64_t)x[1] << 32);
+    int64_t d = (int64_t)(lo & ((1ull << bits) - 1));
+    if (q + 1 == count) {
+      for (size_t i = 2; i < x.size(); ++i)
+        if (x[i]) return false;
+      if (lo >> bits) return false;
+    } else if (d >> (bits - 1)) {
+      d -= (int64_t)1 << bits;
+    }
+    // x = (x - d) / 2^bits
+    Big y(x.size() + 1, 0u);
+    for (size_t i = 0; i + 1 < x.size(); ++i) {
+      const int w = bits / 32 + (int)i, b = bits % 32;
+      const uint64_t v = (w < (int)x.size() ? (uint64_t)x[w] : 0) |
+                         (w + 1 < (int)x.size() ? (uint64_t)x[w + 1] << 32 : 0);
+      y[i] = (uint32_t)(v >> b);
+    }
+    if (d < 0)
+      for (size_t i = 0; i < y.size(); ++i)
+        if (++y[i]) break;
+    x = y;
+    out[q] = std::ldexp((double)(negative ? -d : d), bits * q);
+  }
+  return true;
+}
+
 }  // namespace
 
 bool build_tables(int N, int list, Tables *t) {
@@ -226,6 +258,37 @@ bool build_tables(int N, int list, Tables *t) {
       t->w[l][i] = others[i];
       t->wd[l][i] = (double)others[i];
     }
+  }
+  // wide limbs: three of 41 bits if they hold P, else 40-bit ones
+  const bool three = limbs == 4 && (P.back() >> 25) == 0;  // P < 2^121
+  t->wlimbs = three ? 3 : wide_limbs(limbs);
+  t->wbits = three ? 41 : 40;
+  if (!balanced_limbs(P, false, t->wbits, t->wlimbs, t->cP)) return false;
+  double qmax = 2.0;  // of |rint(S / P)|: the weights are below P / 2, |u_l| <= p_l / 2 + 1
+  for (int l = 0; l < N; ++l) qmax += 0.5 * (p[l] / 2 + 1);
+  for (int l = 0; l < N; ++l) {
+    Big w(t->w[l], t->w[l] + limbs);
+    bool neg = false;
+    for (int i = limbs - 1; i >= 0; --i)
+      if (t->w[l][i] != t->half[i]) {
+        neg = t->w[l][i] > t->half[i];
+        break;
+      }
+    if (neg) {  // P - w
+      int64_t borrow = 0;
+      for (int i = 0; i < limbs; ++i) {
+        const int64_t d = (int64_t)P[i] - (int64_t)t->w[l][i] - borrow;
+        borrow = d < 0 ? 1 : 0;
+        w[i] = (uint32_t)(d + (borrow << 32));
+      }
+    }
+    if (!balanced_limbs(w, neg, t->wbits, t->wlimbs, t->cw[l])) return false;
+  }
+  // every limb sum, and what is left of it after Q P, is an exact double
+  for (int q = 0; q < t->wlimbs; ++q) {
+    double sum = qmax * std::fabs(t->cP[q]);
+    for (int l = 0; l < N; ++l) sum += (p[l] / 2 + 1) * std::fabs(t->cw[l][q]);
+    if (std::ldexp(sum, -t->wbits * q) > 0x1p53) return false;
   }
   t->P_d = big_to_double(P, true);
   t->inv_P_d = 1.0 / t->P_d;
