@@ -883,9 +883,9 @@ __global__ __launch_bounds__(64 * NW_BOUND) void k_bound_reduce(Problem P) {
 hipError_t launch_gemm_persistent(int nw, bool int8, const WorkList &W, int64_t grid,
                                   hipStream_t st) {
   if (W.count <= 0) return hipSuccess;
+  if (!int8) return launch_gemm6_list(W, grid, st);
   if (grid > W.count) grid = W.count;
   if (grid <= 0 || grid > 0x7FFFFFFFll || W.count > 0xFFFFFFFFll) return hipErrorInvalidValue;
-  if (!int8) return launch_gemm6_list(W, grid, st);
   const dim3 gr((unsigned)grid);
   if (nw == 8)
     hipLaunchKernelGGL((k_residue_persistent<8>), gr, dim3(64 * 8), 0, st, W);

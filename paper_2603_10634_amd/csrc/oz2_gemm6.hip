@@ -32,12 +32,14 @@
 //
 // Workgroup: 256 (j) x 256 (i) outputs, 8 waves of 128 x 64 (128 accumulator
 // registers each, two waves per SIMD), one per CU, walking the (part,
-// modulus, tile) items blockIdx, blockIdx + grid, ...  The stages of an
+// modulus, tile) items in rounds of the grid.  The stages of an
 // item's three passes and of the next item form one sequence through an LDS
 // ring of three 48 KB slots, so the loads never stop: the next pass's first
 // stages land during the fold between the passes, the next item's during the
 // epilogue.
 #include <string.h>
+
+#include <algorithm>
 
 #include "oz2_internal.h"
 
@@ -256,19 +258,27 @@ __device__ __forceinline__ Item make_item(const Place &c, CTables *tab) {
   return I;
 }
 
-// Item `it` of a single problem: tiles (i fastest) within moduli within k parts.
+// Item `it` of a single problem: tiles within moduli within k parts, the tiles
+// in bands of kBand rows j, column by column, so that 32 consecutive items
+// (what the CUs of one XCD sum at a time, see item_of) share 8 strips of A and
+// 4 of B in that XCD's L2 wherever the tile grid allows: 12 strips instead of
+// the 48 of a 4 x 4 grid dealt out tile by tile (1024 x 1024 x 65536).
+constexpr uint32_t kBand = 4;
+
 __device__ __forceinline__ Place place_single(CProblem *P, int it) {
   const uint32_t tx_n = (uint32_t)(P->g.mp / kGemmTIW), ty_n = (uint32_t)(P->g.np / kGemmTJ);
   const uint32_t N = (uint32_t)P->g.N, parts = (uint32_t)P->parts;
   const uint32_t nb = (uint32_t)(P->g.kp / kPad);
-  const uint32_t u = (uint32_t)it, a = u / tx_n, b = a / ty_n, z = b / N;
+  const uint32_t u = (uint32_t)it, tiles = tx_n * ty_n, b = u / tiles, z = b / N;
+  const uint32_t t = u - b * tiles, band = t / (kBand * tx_n), r = t - band * (kBand * tx_n);
+  const uint32_t left = ty_n - kBand * band, h = left < kBand ? left : kBand, x = r / h;
   const uint32_t k0 = z * nb / parts, k1 = (z + 1) * nb / parts;  // part_range, in 32 bits
   Place c;
   c.P = P;
   c.l = uni32((int)(b - z * N));
   c.part = uni32((int)z);
-  c.tx = uni32((int)(u - a * tx_n));
-  c.ty = uni32((int)(a - b * ty_n));
+  c.tx = uni32((int)x);
+  c.ty = uni32((int)(kBand * band + (r - x * h)));
   c.k0 = uni32((int)k0 * kPad);
   c.nk = uni32((int)(k1 - k0) * (kPad / kStage6));
   return c;
@@ -293,9 +303,9 @@ __device__ __forceinline__ Place place_list(const WorkList &W, int it) {
 // times c, see the tables) into one accumulator, then the symmetric residue
 // into the modulus's int16 plane.  A pass of a list item longer than kChunkK is
 // summed in chunks of that length, each but the last reduced modulo p.  Items
-// go to the workgroups in rounds, every second one backwards: a list sorted
-// longest first comes out within 3 % of the average (512 problems log-uniform
-// in [64, 4096], and smaller batches), with no counter to fetch from.
+// go to the workgroups in rounds, a list's every second one backwards: sorted
+// longest first it comes out within 3 % of the average (48 problems log-uniform
+// in [64, 2048]), with no counter to fetch from.
 template <bool LIST>
 __global__ __launch_bounds__(64 * NW, 1) void k_residue6(Problem, WorkList W, int count) {
   __shared__ __attribute__((aligned(1024))) uint8_t lds[RING];
@@ -305,15 +315,21 @@ __global__ __launch_bounds__(64 * NW, 1) void k_residue6(Problem, WorkList W, in
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wj = wave >> 2, wi = wave & 3;
   const int grid = (int)gridDim.x;
-  int round = 0, item = (int)blockIdx.x;
-  // a workgroup's item of round q; past the end: one that exists (its loads
-  // are issued and never read)
+  // This workgroup's item of round q (count: none).  Workgroups are dealt out
+  // over the eight XCDs in turn, so XCD b mod 8 takes the (b mod 8)-th run of
+  // ceil(n / 8) consecutive items of the round's n; a list's odd rounds run
+  // backwards.
   auto item_of = [&](int q) {
-    const int it = q * grid + (LIST && (q & 1) ? grid - 1 - (int)blockIdx.x : (int)blockIdx.x);
-    return it;
+    const int left = count - q * grid, n = left < grid ? left : grid;
+    const int per = (n + 7) / 8, y = (int)blockIdx.x / 8, at = (int)(blockIdx.x % 8) * per + y;
+    if (n <= 0 || y >= per || at >= n) return count;
+    return q * grid + (LIST && (q & 1) ? n - 1 - at : at);
   };
+  int round = 0, item = item_of(0);
+  if (item >= count) return;
+  const int first = item;
   auto place = [&](int it) {
-    const int i = it < count ? it : (int)blockIdx.x;
+    const int i = it < count ? it : first;  // past the end: loads that nothing reads
     return LIST ? place_list(W, i) : place_single(P1, i);
   };
   auto loads_of = [&](int it) {
@@ -439,21 +455,27 @@ __global__ __launch_bounds__(64 * NW, 1) void k_residue6(Problem, WorkList W, in
 
 }  // namespace
 
+// Workgroups for `count` items: a multiple of eight (see item_of), at most
+// `cus` rounded down to one.
+static int64_t grid_for(int64_t count, int64_t cus) {
+  return std::min((count + 7) / 8 * 8, std::max<int64_t>(cus / 8, 1) * 8);
+}
+
 hipError_t launch_gemm6(const Problem &P, hipStream_t st) {
   const int64_t count = family_blocks(kFamGemm6, P);
   if (count <= 0) return hipSuccess;
   if (count > 0x7FFFFFFFll - 2 * kCUs) return hipErrorInvalidValue;
-  const dim3 gr((unsigned)(count < kCUs ? count : kCUs));
-  hipLaunchKernelGGL((k_residue6<false>), gr, dim3(64 * NW), 0, st, P, WorkList{}, (int)count);
+  hipLaunchKernelGGL((k_residue6<false>), dim3((unsigned)grid_for(count, kCUs)), dim3(64 * NW), 0,
+                     st, P, WorkList{}, (int)count);
   return hipGetLastError();
 }
 
-hipError_t launch_gemm6_list(const WorkList &W, int64_t grid, hipStream_t st) {
-  if (grid <= 0 || W.count > 0x7FFFFFFFll - 2 * grid) return hipErrorInvalidValue;
+hipError_t launch_gemm6_list(const WorkList &W, int64_t cus, hipStream_t st) {
+  if (cus <= 0 || W.count > 0x7FFFFFFFll - 2 * cus) return hipErrorInvalidValue;
   Problem none;
   memset(&none, 0, sizeof(none));
-  hipLaunchKernelGGL((k_residue6<true>), dim3((unsigned)grid), dim3(64 * NW), 0, st, none, W,
-                     (int)W.count);
+  hipLaunchKernelGGL((k_residue6<true>), dim3((unsigned)grid_for(W.count, cus)), dim3(64 * NW), 0,
+                     st, none, W, (int)W.count);
   return hipGetLastError();
 }
 

@@ -386,7 +386,7 @@ hipError_t launch_gemm_persistent(int nw, bool int8, const WorkList &W, int64_t 
 // launch_gemm_family).
 hipError_t launch_gemm6(const Problem &P, hipStream_t st);
 // The same over a work list (every item's modulus an FP8 one).
-hipError_t launch_gemm6_list(const WorkList &W, int64_t grid, hipStream_t st);
+hipError_t launch_gemm6_list(const WorkList &W, int64_t cus, hipStream_t st);
 // limbs: crt_shape of the tables.
 hipError_t launch_crt_family(const Problem *P, const Group *G, int limbs, int N, hipStream_t st);
 // Device memory of the entry point that allocates nothing: a workspace and
