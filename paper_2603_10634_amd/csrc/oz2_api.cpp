@@ -352,6 +352,7 @@ Problem make_problem(char transA, char transB, int64_t m, int64_t n, int64_t k, 
   P.limbs = crt_shape(*ht);
   P.mode = g_ts.mode;
   P.parts = L.parts;
+  P.res_sides = 3;
   P.bparts = P.mode == OZ2_MODE_FAST ? 1 : L.bparts;
   P.g.fp6 = fp6;
   return P;
@@ -383,8 +384,7 @@ int enqueue_scaling(const Problem &P, hipStream_t st, Marks &mark) {
   const bool fast = P.mode == OZ2_MODE_FAST;
   mark();
   // step 1: mu', nu' and the FP8 bound operands (fast mode: their line norms)
-  for (int f : {kFamFill, kFamLmaxA, kFamLmaxB}) OZ2_TRY(launch_quant_family(f, &P, nullptr, st));
-  for (int f : {fast ? kFamNormA : kFamBarA, fast ? kFamNormB : kFamBarB})
+  for (int f : {kFamFill, kFamLmax, fast ? kFamNorm : kFamBar})
     OZ2_TRY(launch_quant_family(f, &P, nullptr, st));
   mark();
   // step 2: the FP8 bound product (its line maxima only; none in fast mode)
@@ -393,30 +393,24 @@ int enqueue_scaling(const Problem &P, hipStream_t st, Marks &mark) {
     if (P.bparts > 1) OZ2_TRY(launch_gemm_family(kFamBreduce, &P, nullptr, st));
   }
   mark();
-  // step 3: scale exponents mu, nu
+  // step 3: scale exponents mu, nu (those from an exact bound: with the residues)
   if (!fast)
     for (int f : {kFamDecide, kFamFixup}) OZ2_TRY(launch_scale_family(f, &P, nullptr, st));
-  OZ2_TRY(launch_scale_family(kFamFinal, &P, nullptr, st));
   mark();
   return OZ2_SUCCESS;
 }
 
-// Workflow steps 4-10 for one problem or block; res_a / res_b select which
-// operand's residues are (re)computed.
-int enqueue_products(const Problem &P, hipStream_t st, Marks &mark, bool res_a = true,
-                     bool res_b = true) {
+// Workflow steps 4-10 for one problem or block, with the residues of
+// P.res_sides (re)computed.
+int enqueue_products(const Problem &P, hipStream_t st, Marks &mark) {
   // steps 4-6: integers, residues and FP8 digits
   const bool fp6 = P.g.fp6 != 0;
-  if (res_a) OZ2_TRY(launch_quant_family(fp6 ? kFamRes6A : kFamResA, &P, nullptr, st));
-  if (res_b) OZ2_TRY(launch_quant_family(fp6 ? kFamRes6B : kFamResB, &P, nullptr, st));
+  OZ2_TRY(launch_quant_family(fp6 ? kFamRes6 : kFamRes, &P, nullptr, st));
   mark();
-  // steps 7-8: residue products and their reduction modulo p (every k part
-  // of a kind in one launch)
-  if (fp6)
-    OZ2_TRY(launch_gemm_family(kFamGemm6, &P, nullptr, st));
-  else
-    for (int f : {kFamGemmSq, kFamGemmKa, kFamGemmI8})
-      OZ2_TRY(launch_gemm_family(f, &P, nullptr, st));
+  // steps 7-8: residue products and their reduction modulo p (every modulus
+  // and k part in one launch)
+  OZ2_TRY(launch_gemm_family(fp6 ? kFamGemm6 : P.g.nsq + P.g.nka > 0 ? kFamGemm8 : kFamGemmI8, &P,
+                             nullptr, st));
   mark();
   // steps 9-10: CRT and inverse scaling
   OZ2_TRY(launch_crt_family(&P, nullptr, P.limbs, P.g.N, st));
@@ -448,6 +442,7 @@ Problem block_problem(const Problem &P, int64_t i0, int64_t j0, int64_t mi, int6
   B.w.e += i0;
   B.w.flags += i0;
   B.w.amax += i0;
+  B.w.rfix += i0;
   B.w.lineB = P.g.mp + j0 - i0;
   B.C += i0 + j0 * P.ldc;
   return B;
@@ -467,8 +462,9 @@ int enqueue_blocked(const Problem &P, int64_t mb, int64_t nb, hipStream_t st) {
   const int64_t nJ = (n + nb - 1) / nb;
   for (int64_t i0 = 0; i0 < m; i0 += mb)
     for (int64_t j0 = 0; j0 < n; j0 += nb) {
-      const Problem B = block_problem(P, i0, j0, std::min(mb, m - i0), std::min(nb, n - j0));
-      r = enqueue_products(B, st, none, j0 == 0, i0 == 0 || nJ > 1);
+      Problem B = block_problem(P, i0, j0, std::min(mb, m - i0), std::min(nb, n - j0));
+      B.res_sides = (j0 == 0 ? 1 : 0) | (i0 == 0 || nJ > 1 ? 2 : 0);
+      r = enqueue_products(B, st, none);
       if (r != OZ2_SUCCESS) return r;
     }
   return OZ2_SUCCESS;
@@ -788,15 +784,12 @@ void build_subbatch(const std::vector<Problem> &probs, ImageWriter &W, SubBatch 
     sb->launches.push_back(L);
   };
   sb->int8 = probs[0].g.list == OZ2_MODULI_INT8;
-  const Family resA = sb->int8 ? kFamResA : kFamRes6A;
-  const Family resB = sb->int8 ? kFamResB : kFamRes6B;
+  const Family res = sb->int8 ? kFamRes : kFamRes6;
   // every problem of a batch has the calling thread's mode
   if (probs[0].mode == OZ2_MODE_FAST) {
-    for (int f : {kFamFill, kFamLmaxA, kFamLmaxB, kFamNormA, kFamNormB, kFamFinal, resA, resB})
-      add(f, at_probs, -1);
+    for (int f : {kFamFill, kFamLmax, kFamNorm, res}) add(f, at_probs, -1);
   } else {
-    for (int f : {kFamFill, kFamLmaxA, kFamLmaxB, kFamBarA, kFamBarB, kFamBgemm, kFamDecide,
-                  kFamFixup, kFamFinal, resA, resB})
+    for (int f : {kFamFill, kFamLmax, kFamBar, kFamBgemm, kFamDecide, kFamFixup, res})
       add(f, at_probs, -1);
   }
   const uint32_t zero2[2] = {0u, 0u};
@@ -852,9 +845,9 @@ void build_subbatch(const std::vector<Problem> &probs, ImageWriter &W, SubBatch 
 int family_group(int fam) {
   switch (fam) {
     case kFamBgemm: case kFamBreduce: return 1;
-    case kFamDecide: case kFamFixup: case kFamFinal: return 2;
-    case kFamResA: case kFamResB: case kFamRes6A: case kFamRes6B: return 3;
-    case kFamGemmSq: case kFamGemmKa: case kFamGemmI8: case kFamGemm6: case kFamPersist: return 4;
+    case kFamDecide: case kFamFixup: return 2;
+    case kFamRes: case kFamRes6: return 3;
+    case kFamGemm8: case kFamGemmI8: case kFamGemm6: case kFamPersist: return 4;
     case kFamCrt: return 5;
     default: return 0;
   }
@@ -885,7 +878,7 @@ int enqueue_subbatch(const SubBatch &sb, int config, int cus, hipStream_t st, Ma
       OZ2_TRY(launch_gemm_persistent(config_waves(config), L.int8, L.W, cus, st));
     else if (L.fam == kFamBgemm)
       OZ2_TRY(launch_gemm_family(L.fam, nullptr, &L.G, st));
-    else if (L.fam == kFamDecide || L.fam == kFamFixup || L.fam == kFamFinal)
+    else if (L.fam == kFamDecide || L.fam == kFamFixup)
       OZ2_TRY(launch_scale_family(L.fam, nullptr, &L.G, st));
     else if (L.fam == kFamCrt)
       OZ2_TRY(launch_crt_family(nullptr, &L.G, sb.limbs, sb.N, st));

@@ -161,9 +161,9 @@ template <int LL, int L, int NF, bool GROUPED>
 __global__ __launch_bounds__(256) void k_crt(Problem P1, Group G) {
   int64_t local;
   const Problem &P = *locate<GROUPED>(P1, G, blockIdx.x, local);
-  const int64_t nbx = (P.g.m + 63) / 64;
-  const int64_t i = (local % nbx) * 64 + 2 * (threadIdx.x & 31);
-  const int64_t j = (local / nbx) * 8 + (threadIdx.x >> 5);
+  const Dims c = decode_block(family_dims(kFamCrt, P), local);
+  const int64_t i = c.x * 64 + 2 * (threadIdx.x & 31);
+  const int64_t j = c.y * 8 + (threadIdx.x >> 5);
   if (j >= P.g.n || i >= P.g.m) return;
   crt_pair<LL, L, NF>(P, tables_of<GROUPED>(P1, G), i, j);
 }

@@ -640,37 +640,34 @@ __device__ __forceinline__ void int8_tile_w(const uint8_t *Asl, const uint8_t *B
     }
 }
 
-// Residue products of one problem, 256 x 256 tiles: KIND 0 over the square
-// moduli (l = z mod nsq), 1 over the Karatsuba moduli (l = nsq + z mod nka),
-// 2 over the INT8 moduli (l = nsq + nka + z mod n8).  The workgroup covers k
-// part z / (moduli of the kind) of P.parts and writes that part's copy of the
-// planes; the host makes every part at most kChunkK long.
-template <int KIND>
+// Residue products of one problem, 256 x 256 tiles, over the INT8 moduli
+// (INT8) or the FP8 moduli of either kind on E4M3 digits: modulus z mod N and
+// k part z / N of P.parts, whose copy of the planes the workgroup writes; the
+// host makes every part at most kChunkK long.
+template <bool INT8>
 __global__ __launch_bounds__(64 * NW_RES, 1) void k_residue_gemm(Problem P) {
   __shared__ __attribute__((aligned(1024))) uint8_t lds[LDS_RING];
   const Geometry &g = P.g;
-  const Dims d = family_dims(KIND == 0 ? kFamGemmSq : (KIND == 1 ? kFamGemmKa : kFamGemmI8), P);
+  const Dims d = family_dims(kFamGemm8, P);
   const Dims c = decode_block(d, blockIdx.x);
   const int64_t mp = uni(g.mp), np = uni(g.np), kp = uni(g.kp);
-  const int parts = (int)uni((int64_t)P.parts);
-  const int64_t nz = d.z / parts;
-  const int part = (int)uni(c.z / nz);
-  const int l = (int)uni((KIND == 0 ? 0 : (KIND == 1 ? g.nsq : g.nsq + g.nka)) + c.z % nz);
+  const int part = (int)uni(c.z / g.N);
+  const int l = (int)uni(c.z % g.N);
   int64_t k0, k1;
-  part_range(kp, parts, part, &k0, &k1);
+  part_range(kp, (int)uni((int64_t)P.parts), part, &k0, &k1);
   const int nk = (int)uni((k1 - k0) / BK);
   k0 = uni(k0);
   int16_t *planes = uni(P.w.planes) + uni((int64_t)part * g.N) * mp * np;
   const int tid = threadIdx.x;
-  if (KIND == 0)
-    square_tile_w<NW_RES>(uni(P.w.Asl), uni(P.w.Bsl), planes, uni(P.tab), mp, np, kp, k0, nk, l,
-                          uni(c.x * TIW), uni(c.y * TJ), lds, tid);
-  else if (KIND == 1)
-    karatsuba_tile_w<NW_RES>(uni(P.w.Asl), uni(P.w.Bsl), planes, uni(P.tab), mp, np, kp, k0, nk,
-                             l, uni(c.x * TIW), uni(c.y * TJ), lds, tid);
-  else
+  if (INT8)
     int8_tile_w<NW_RES>(uni(P.w.Asl), uni(P.w.Bsl), planes, uni(P.tab), mp, np, kp, k0, nk, 0, l,
                         uni(c.x * TIW), uni(c.y * TJ), lds, tid);
+  else if (l < g.nsq)
+    square_tile_w<NW_RES>(uni(P.w.Asl), uni(P.w.Bsl), planes, uni(P.tab), mp, np, kp, k0, nk, l,
+                          uni(c.x * TIW), uni(c.y * TJ), lds, tid);
+  else
+    karatsuba_tile_w<NW_RES>(uni(P.w.Asl), uni(P.w.Bsl), planes, uni(P.tab), mp, np, kp, k0, nk,
+                             l, uni(c.x * TIW), uni(c.y * TJ), lds, tid);
 }
 
 // The INT8 residue products of a whole batch in one launch (the FP8 lists':
@@ -945,14 +942,11 @@ hipError_t launch_gemm_family(int fam, const Problem *P, const Group *G, hipStre
     case kFamBreduce:
       hipLaunchKernelGGL(k_bound_reduce, gr, blk, 0, st, p1);
       break;
-    case kFamGemmSq:
-      hipLaunchKernelGGL((k_residue_gemm<0>), gr, blk, 0, st, p1);
-      break;
-    case kFamGemmKa:
-      hipLaunchKernelGGL((k_residue_gemm<1>), gr, blk, 0, st, p1);
+    case kFamGemm8:
+      hipLaunchKernelGGL((k_residue_gemm<false>), gr, blk, 0, st, p1);
       break;
     case kFamGemmI8:
-      hipLaunchKernelGGL((k_residue_gemm<2>), gr, blk, 0, st, p1);
+      hipLaunchKernelGGL((k_residue_gemm<true>), gr, blk, 0, st, p1);
       break;
     default:
       return hipErrorInvalidValue;

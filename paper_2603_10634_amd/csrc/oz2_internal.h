@@ -108,7 +108,8 @@ struct Work {
                       // from op(A)'s first line (mp, or a block's offset)
 };
 
-// kFixup: the line's exponent comes from the exact bound in rfix.
+// kFixup: the line's exponent comes from the exact bound in rfix; the residue
+// pass takes it from there and stores e and shift (final_shift).
 enum LineFlag : uint32_t { kNonFinite = 1u, kZeroLine = 2u, kFixup = 4u };
 
 // Operand view: line r (row of op(A) or column of op(B)), k-index h at
@@ -131,6 +132,7 @@ struct Problem {
   int32_t mode;        // OZ2_MODE_ACCURATE or OZ2_MODE_FAST (selects the launch sequence)
   int32_t parts;       // k parts of the residue products (split-K): the CRT sums this
                        // many copies of the residue planes, each N mp np entries apart
+  int32_t res_sides;   // operands whose residues are computed: 1 op(A), 2 op(B), 3 both
   int32_t bparts;      // k parts of the bound product (1: one pass with line maxima)
 };
 
@@ -177,49 +179,50 @@ constexpr int kQK = 128;
 // covers one problem or a whole group of problems (a batch).
 enum Family : int {
   kFamFill = 0,   // zero the per-line accumulators
-  kFamLmaxA,      // line maxima of op(A) / op(B)
-  kFamLmaxB,
-  kFamBarA,       // FP8 bound operands
-  kFamBarB,
-  kFamNormA,      // fast mode: squared norms of the bound operands' lines
-  kFamNormB,
+  kFamLmax,       // line maxima of op(A), then of op(B)
+  kFamBar,        // FP8 bound operands of both
+  kFamNorm,       // fast mode: squared norms of the bound operands' lines
   kFamBgemm,      // FP8 bound product (line maxima, or per-part sums when split)
   kFamBreduce,    // split bound product: sum of the parts, line maxima
   kFamDecide,     // scale exponents from the FP8 bound
   kFamFixup,      // exact bound product for undecided lines
-  kFamFinal,      // shifts
-  kFamResA,       // residues and FP8 digits
-  kFamResB,
-  kFamRes6A,      // residues and E2M3 digits
-  kFamRes6B,
-  kFamGemmSq,     // residue products, square moduli (every k part in one launch)
-  kFamGemmKa,     // residue products, Karatsuba moduli
+  kFamRes,        // residues and FP8 digits (or INT8 residues) of Problem::res_sides
+  kFamRes6,       // residues and E2M3 digits of Problem::res_sides
+  kFamGemm8,      // residue products on E4M3 digits, every FP8 modulus and k part
   kFamGemmI8,     // residue products, INT8 moduli
   kFamGemm6,      // residue products on E2M3 digits, every FP8 modulus
   kFamCrt,        // CRT, inverse scaling, alpha / beta
   kNumFamilies
 };
 
-// k-split of the line-maxima pass.
+// k-split of the line-maxima pass: enough blocks for the chip, but at least
+// kLmaxK elements of a line per thread (64 threads' worth of 8 where k is
+// contiguous): every chunk ends in an atomic per line, which at one or two
+// elements per chunk cost more than the reads (48 uneven problems: 267 us for
+// both operands' maxima).
+constexpr uint32_t kLmaxK = 32;
+
 struct LmaxShape {
   int64_t gx, splits, hchunk;
 };
 
 __host__ __device__ inline LmaxShape lmax_shape(const Operand &op) {
   LmaxShape s;
+  const uint32_t k = (uint32_t)op.k;  // at most OZ2_MAX_K
   if (op.sh == 1) {  // k contiguous: a wave per line and k chunk, ~2048 waves
     s.gx = (op.lines + 3) / 4;
-    const int64_t splits = (2048 + s.gx - 1) / s.gx;
-    int64_t h = (op.k + splits - 1) / splits;
-    h = (h + 63) / 64 * 64;
+    const uint32_t g = (uint32_t)(s.gx < 2048 ? s.gx : 2048), splits = (2048 + g - 1) / g;
+    uint32_t h = ((k + splits - 1) / splits + 63) / 64 * 64;
+    if (h < 512) h = 512;
     s.hchunk = h;
-    s.splits = (op.k + h - 1) / h;
+    s.splits = (k + h - 1) / h;
   } else {  // lines contiguous: a thread per line and k chunk
     s.gx = (op.lines + 255) / 256;
-    int64_t splits = (4096 + s.gx - 1) / s.gx;
-    if (splits > op.k) splits = op.k;
-    s.hchunk = (op.k + splits - 1) / splits;
-    s.splits = (op.k + s.hchunk - 1) / s.hchunk;
+    const uint32_t g = (uint32_t)(s.gx < 4096 ? s.gx : 4096), splits = (4096 + g - 1) / g;
+    uint32_t h = (k + splits - 1) / splits;
+    if (h < kLmaxK) h = kLmaxK;
+    s.hchunk = h;
+    s.splits = (k + h - 1) / h;
   }
   return s;
 }
@@ -227,6 +230,20 @@ __host__ __device__ inline LmaxShape lmax_shape(const Operand &op) {
 struct Dims {
   int64_t x, y, z;
 };
+
+// Groups of moduli the residue pass deals out over workgroups of their own:
+// with few tiles (an input's moduli are a serial chain of vector work) each
+// takes a half or a quarter of them.
+__host__ __device__ inline int64_t res_groups(int64_t tiles, int N) {
+  const int64_t want = tiles >= 512 ? 1 : (tiles >= 256 ? 2 : 4);
+  return want < N ? want : N;
+}
+
+// Padded lines the residue pass covers: of op(A) (side bit 1), then of op(B)
+// (side bit 2).
+__host__ __device__ inline int64_t res_lines(const Problem &P) {
+  return (P.res_sides & 1 ? P.g.mp : 0) + (P.res_sides & 2 ? P.g.np : 0);
+}
 
 // Block grid of family `fam` for one problem.  Blocks are numbered x fastest,
 // then y, then z.
@@ -237,45 +254,34 @@ __host__ __device__ inline Dims family_dims(int fam, const Problem &P) {
       int64_t b = (P.w.zero_words + 255) / 256;
       return {b < 64 ? b : 64, 1, 1};
     }
-    case kFamLmaxA: {
-      const LmaxShape s = lmax_shape(P.A);
-      return {s.gx, s.splits, 1};
+    case kFamLmax: {
+      const LmaxShape a = lmax_shape(P.A), b = lmax_shape(P.B);
+      return {a.gx * a.splits + b.gx * b.splits, 1, 1};
     }
-    case kFamLmaxB: {
-      const LmaxShape s = lmax_shape(P.B);
-      return {s.gx, s.splits, 1};
+    case kFamBar:
+    case kFamNorm:
+      return {(g.mp + g.np) / kQL, g.kp / kQK, 1};
+    case kFamRes: {
+      const int64_t x = res_lines(P) / kQL, y = g.kp / kQK;
+      return {x, y, res_groups(x * y, g.N)};
     }
-    case kFamBarA:
-    case kFamNormA:
-    case kFamResA:
-      return {g.mp / kQL, g.kp / kQK, 1};
-    case kFamBarB:
-    case kFamNormB:
-    case kFamResB:
-      return {g.np / kQL, g.kp / kQK, 1};
-    case kFamRes6A:
-      return {g.mp / 64, g.kp / kStage6, 1};
-    case kFamRes6B:
-      return {g.np / 64, g.kp / kStage6, 1};
+    case kFamRes6: {
+      const int64_t x = res_lines(P) / 64, y = g.kp / kStage6;
+      return {x, y, res_groups(x * y, g.N)};
+    }
     case kFamBgemm:
       return {g.mp / kGemmTIW, g.np / kGemmTJ, P.bparts};
     case kFamBreduce:  // (the wide tile's 16 MFMA blocks per wave) per tile
       return {16 * (g.mp / kGemmTIW) * (g.np / kGemmTJ), 1, P.bparts > 1 ? 1 : 0};
     case kFamDecide:
-    case kFamFinal:
       return {(g.mp + g.np + 255) / 256, 1, 1};
     case kFamFixup: {  // one-wave workgroups walking the flagged lines' items
       int64_t b = (g.mp + g.np) / 8;
       return {b < 8 ? 8 : (b > 4096 ? 4096 : b), 1, 1};
     }
-    case kFamGemmSq:
-    case kFamGemmKa:
-    case kFamGemmI8: {
-      // z = part * (moduli of the kind) + modulus
-      const int64_t nz = fam == kFamGemmSq ? g.nsq : (fam == kFamGemmKa ? g.nka : g.N - g.nsq - g.nka);
-      return {g.mp / kGemmTIW, g.np / kGemmTJ, nz * P.parts};
-    }
-    case kFamGemm6:
+    case kFamGemm8:
+    case kFamGemmI8:
+    case kFamGemm6:  // z = part * N + modulus
       return {g.mp / kGemmTIW, g.np / kGemmTJ, (int64_t)g.N * P.parts};
     case kFamCrt:
       return {(g.m + 63) / 64, (g.n + 7) / 8, 1};
@@ -357,13 +363,16 @@ __device__ __forceinline__ const Problem *locate(const Problem &P1, const Group 
   }
 }
 
-// Local block coordinates of block `local` of a family grid.
+// Local block coordinates of block `local` of a family grid (a launch has
+// fewer than 2^31 blocks, so 32-bit divisions do: the 64-bit ones are some
+// hundred instructions each, felt by blocks that run for microseconds).
 __device__ __forceinline__ Dims decode_block(const Dims &d, int64_t local) {
+  const uint32_t b = (uint32_t)local, x = (uint32_t)d.x, y = (uint32_t)d.y;
+  const uint32_t r = b / x, z = r / y;
   Dims c;
-  c.x = local % d.x;
-  const int64_t r = local / d.x;
-  c.y = r % d.y;
-  c.z = r / d.y;
+  c.x = b - r * x;
+  c.y = r - z * y;
+  c.z = z;
   return c;
 }
 #endif
@@ -386,7 +395,7 @@ hipError_t launch_gemm_persistent(int nw, bool int8, const WorkList &W, int64_t 
 // launch_gemm_family).
 hipError_t launch_gemm6(const Problem &P, hipStream_t st);
 // The same over a work list (every item's modulus an FP8 one).
-hipError_t launch_gemm6_list(const WorkList &W, int64_t cus, hipStream_t st);
+hipError_t launch_gemm6_list(const WorkList &W, int64_t grid, hipStream_t st);
 // limbs: crt_shape of the tables.
 hipError_t launch_crt_family(const Problem *P, const Group *G, int limbs, int N, hipStream_t st);
 // Device memory of the entry point that allocates nothing: a workspace and

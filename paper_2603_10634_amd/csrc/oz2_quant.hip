@@ -9,6 +9,7 @@
 
 #include "oz2_device.h"
 #include "oz2_internal.h"
+#include "oz2_window.h"
 
 namespace oz2 {
 
@@ -116,15 +117,30 @@ __global__ __launch_bounds__(256) void k_fill(Problem P1, Group G) {
   fill_zero(P.w.zero, P.w.zero_words, local, d.x);
 }
 
-// SIDE 0: rows of op(A) (lines 0..mp-1), 1: columns of op(B) (lines mp..)
-template <bool GROUPED, int SIDE>
+// Both operands of a problem in one launch: the blocks of op(A)'s lines (0 ..
+// mp - 1 of the per-line vectors), then those of op(B)'s (from mp).  A pass over
+// a small operand costs its launch (256^3: 4-5 us each), whichever the size.
+__device__ __forceinline__ Operand operand(const Problem &P, bool b) {
+  Operand o;
+  o.ptr = b ? P.B.ptr : P.A.ptr;
+  o.lines = b ? P.B.lines : P.A.lines;
+  o.k = b ? P.B.k : P.A.k;
+  o.sr = b ? P.B.sr : P.A.sr;
+  o.sh = b ? P.B.sh : P.A.sh;
+  return o;
+}
+
+template <bool GROUPED>
 __global__ __launch_bounds__(256) void k_line_max(Problem P1, Group G) {
   int64_t local;
   const Problem &P = *locate<GROUPED>(P1, G, blockIdx.x, local);
-  const Operand &op = SIDE == 0 ? P.A : P.B;
-  const int64_t base = SIDE == 0 ? 0 : P.g.mp;
+  const LmaxShape sa = lmax_shape(P.A);
+  const bool side = local >= sa.gx * sa.splits;
+  if (side) local -= sa.gx * sa.splits;
+  const Operand op = operand(P, side);
+  const int64_t base = side ? P.g.mp : 0;
   const LmaxShape sh = lmax_shape(op);
-  const int64_t bx = local % sh.gx, by = local / sh.gx;
+  const int64_t by = (uint32_t)local / (uint32_t)sh.gx, bx = local - by * sh.gx;
   if (op.sh == 1)
     line_max_kcontig(op, sh, bx, by, P.w.amax + base, P.w.flags + base);
   else
@@ -200,17 +216,18 @@ __device__ __forceinline__ void bound_operand_tile(const Operand &op, int64_t li
   *(uint2 *)(bar + kblocked(r, h0 + b * 8, lines_pad)) = make_uint2(packed[0], packed[1]);
 }
 
-template <bool GROUPED, int SIDE>
+template <bool GROUPED>
 __global__ __launch_bounds__(256) void k_bound_operand(Problem P1, Group G) {
   __shared__ double tile[kQL * kRowLd];
   int64_t local;
   const Problem &P = *locate<GROUPED>(P1, G, blockIdx.x, local);
-  const Operand &op = SIDE == 0 ? P.A : P.B;
-  const int64_t base = SIDE == 0 ? 0 : P.g.mp;
-  const Dims d = family_dims(SIDE == 0 ? kFamBarA : kFamBarB, P);
-  const int64_t bx = local % d.x, by = local / d.x;
-  bound_operand_tile(op, SIDE == 0 ? P.g.mp : P.g.np, bx * kQL, by * kQK, P.w.amax + base,
-                     P.w.E + base, P.w.flags + base, SIDE == 0 ? P.w.Abar : P.w.Bbar, tile);
+  const Dims c = decode_block(family_dims(kFamBar, P), local);
+  const int64_t r0 = c.x * kQL, by = c.y;
+  const bool side = r0 >= P.g.mp;
+  const int64_t base = side ? P.g.mp : 0;
+  bound_operand_tile(operand(P, side), side ? P.g.np : P.g.mp, r0 - base, by * kQK,
+                     P.w.amax + base, P.w.E + base, P.w.flags + base,
+                     side ? P.w.Bbar : P.w.Abar, tile);
 }
 
 // Fast mode: 2^18 x the squared Euclidean norm of every line of the round-up
@@ -251,17 +268,17 @@ __device__ __forceinline__ void bound_norm_tile(const Operand &op, int64_t r0, i
   if (b == 0 && sum) atomicAdd((unsigned long long *)&norm[r], (unsigned long long)sum);
 }
 
-template <bool GROUPED, int SIDE>
+template <bool GROUPED>
 __global__ __launch_bounds__(256) void k_bound_norm(Problem P1, Group G) {
   __shared__ double tile[kQL * kRowLd];
   int64_t local;
   const Problem &P = *locate<GROUPED>(P1, G, blockIdx.x, local);
-  const Operand &op = SIDE == 0 ? P.A : P.B;
-  const int64_t base = SIDE == 0 ? 0 : P.g.mp;
-  const Dims d = family_dims(SIDE == 0 ? kFamNormA : kFamNormB, P);
-  const int64_t bx = local % d.x, by = local / d.x;
-  bound_norm_tile(op, bx * kQL, by * kQK, P.w.amax + base, P.w.E + base, P.w.flags + base,
-                  P.w.rfix + base, tile);
+  const Dims c = decode_block(family_dims(kFamNorm, P), local);
+  const int64_t r0 = c.x * kQL, by = c.y;
+  const bool side = r0 >= P.g.mp;
+  const int64_t base = side ? P.g.mp : 0;
+  bound_norm_tile(operand(P, side), r0 - base, by * kQK, P.w.amax + base, P.w.E + base,
+                  P.w.flags + base, P.w.rfix + base, tile);
 }
 
 // Residues of a' (eq. def:A') for every modulus, split into digits, for one
@@ -423,28 +440,66 @@ __device__ __forceinline__ void kind_moduli(const ResidueIn &in, const Tables *_
   }
 }
 
-// Every modulus of one thread's inputs, kind by kind.
+// The moduli [l0, l1) of the workgroup's group, split by kind.
+struct ModuliRange {
+  int l0, a, b, l1;  // squares [l0, a), Karatsuba [a, b), INT8 [b, l1)
+};
+
+__device__ __forceinline__ ModuliRange moduli_range(const Geometry &g, int64_t z, int64_t groups) {
+  ModuliRange r;
+  r.l0 = (int)(z * g.N / groups);
+  r.l1 = (int)((z + 1) * g.N / groups);
+  r.a = max(r.l0, min(r.l1, g.nsq));
+  r.b = max(r.l0, min(r.l1, g.nsq + g.nka));
+  return r;
+}
+
+// Those moduli of one thread's inputs, kind by kind.
 template <bool HUGE>
 __device__ __forceinline__ void residue_moduli(const ResidueIn &in, const Tables *__restrict__ tab,
-                                               int N, int nsq, int nka, uint8_t *base,
+                                               const ModuliRange &r, uint8_t *base,
                                                int64_t slice_stride) {
-  kind_moduli<0, HUGE>(in, tab, 0, nsq, base, slice_stride);
-  kind_moduli<1, HUGE>(in, tab, nsq, nsq + nka, base, slice_stride);
-  kind_moduli<2, HUGE>(in, tab, nsq + nka, N, base, slice_stride);
+  kind_moduli<0, HUGE>(in, tab, r.l0, r.a, base, slice_stride);
+  kind_moduli<1, HUGE>(in, tab, r.a, r.b, base, slice_stride);
+  kind_moduli<2, HUGE>(in, tab, r.b, r.l1, base, slice_stride);
+}
+
+// log2 of the scale of line r (in the per-line vectors of its side, from
+// `base`): the stored shift, or for a line with an exact bound (2^18 x the
+// line's maximum or norm, < 2^53, in rfix) the one this bound gives, stored by
+// the thread with `store` for the CRT and for inspection.  Taking it here
+// spares a launch over the lines between the bound and the residues.
+__device__ __forceinline__ int final_shift(const Work &w, int64_t base, int64_t r, double D,
+                                           bool store, int *e) {
+  const int64_t L = base + r;
+  if (!(w.flags[L] & kFixup)) {
+    *e = w.e[L];
+    return w.shift[L];
+  }
+  const uint64_t r18 = w.rfix[L];
+  const int ev = r18 ? exponent_rule(ldexp((double)r18, -18), D) : 0;
+  const int s = 7 - w.E[L] + ev;
+  if (store) {
+    w.e[L] = ev;
+    w.shift[L] = s;
+  }
+  *e = ev;
+  return s;
 }
 
 __device__ __forceinline__ void residues_tile(const Operand &op, int64_t kp, int64_t lines_pad,
-                                              int64_t r0, int64_t h0,
-                                              const int32_t *__restrict__ shift,
-                                              const Tables *__restrict__ tab, int N, int nsq,
-                                              int nka, uint8_t *__restrict__ slices,
-                                              double *tile) {
+                                              int64_t r0, int64_t h0, const Work &w,
+                                              int64_t base_line,
+                                              const Tables *__restrict__ tab,
+                                              const ModuliRange &range,
+                                              uint8_t *__restrict__ slices, double *tile) {
   stage_tile(op, r0, h0, tile);
   __syncthreads();
   // thread t: line t / 16, the kRE = 8 consecutive k (t % 16) * 8 .. + 7
   const int rl = threadIdx.x >> 4, b = threadIdx.x & 15;
   const int64_t r = r0 + rl;
-  const int s = shift[r];  // log2(mu_r)
+  int e;
+  const int s = final_shift(w, base_line, r, tab->D, h0 == 0 && b == 0, &e);  // log2(mu_r)
 
   ResidueIn in;
   bool huge = false;
@@ -465,23 +520,23 @@ __device__ __forceinline__ void residues_tile(const Operand &op, int64_t kp, int
   const int64_t slice_stride = lines_pad * kp;
   uint8_t *base = slices + kblocked(r, h0 + b * kRE, lines_pad);
   if (__any(huge))
-    residue_moduli<true>(in, tab, N, nsq, nka, base, slice_stride);
+    residue_moduli<true>(in, tab, range, base, slice_stride);
   else
-    residue_moduli<false>(in, tab, N, nsq, nka, base, slice_stride);
+    residue_moduli<false>(in, tab, range, base, slice_stride);
 }
 
-template <bool GROUPED, int SIDE>
+template <bool GROUPED>
 __global__ __launch_bounds__(256) void k_residues(Problem P1, Group G) {
   __shared__ double tile[kQL * kRowLd];
   int64_t local;
   const Problem &P = *locate<GROUPED>(P1, G, blockIdx.x, local);
-  const Operand &op = SIDE == 0 ? P.A : P.B;
-  const int64_t base = SIDE == 0 ? 0 : P.w.lineB;
-  const Dims d = family_dims(SIDE == 0 ? kFamResA : kFamResB, P);
-  const int64_t bx = local % d.x, by = local / d.x;
-  residues_tile(op, P.g.kp, SIDE == 0 ? P.g.mp : P.g.np, bx * kQL, by * kQK, P.w.shift + base,
-                tables_of<GROUPED>(P1, G), P.g.N, P.g.nsq, P.g.nka,
-                SIDE == 0 ? P.w.Asl : P.w.Bsl, tile);
+  const Dims d = family_dims(kFamRes, P), c = decode_block(d, local);
+  const int64_t r0 = c.x * kQL, by = c.y;
+  const int64_t first = P.res_sides & 1 ? P.g.mp : 0;
+  const bool side = r0 >= first;
+  residues_tile(operand(P, side), P.g.kp, side ? P.g.np : P.g.mp, side ? r0 - first : r0,
+                by * kQK, P.w, side ? P.w.lineB : 0, tables_of<GROUPED>(P1, G),
+                moduli_range(P.g, c.z, d.z), side ? P.w.Bsl : P.w.Asl, tile);
 }
 
 // ---- E2M3 digits ----
@@ -605,22 +660,26 @@ __device__ __forceinline__ void kind6(const double (&x)[kR6E], CTables *tab, int
 }
 
 template <int STEPS>
-__device__ __forceinline__ void moduli6(const double (&x)[kR6E], CTables *tab, int nsq, int nka,
-                                        uint8_t *base, int64_t slice_stride, uint32_t off16,
+__device__ __forceinline__ void moduli6(const double (&x)[kR6E], CTables *tab,
+                                        const ModuliRange &m, uint8_t *base, int64_t slice_stride, uint32_t off16,
                                         uint32_t off8) {
-  kind6<0, STEPS>(x, tab, 0, nsq, base, slice_stride, off16, off8);
-  kind6<1, STEPS>(x, tab, nsq, nsq + nka, base, slice_stride, off16, off8);
+  kind6<0, STEPS>(x, tab, m.l0, m.a, base, slice_stride, off16, off8);
+  kind6<1, STEPS>(x, tab, m.a, m.b, base, slice_stride, off16, off8);
 }
 
-template <bool GROUPED, int SIDE>
+template <bool GROUPED>
 __global__ __launch_bounds__(256, 2) void k_residues6(Problem P1, Group G) {
   __shared__ __attribute__((aligned(16))) double tile[4][kR6L * kR6Ld];
   int64_t local;
   const Problem &P = *locate<GROUPED>(P1, G, blockIdx.x, local);
-  const Operand &op = SIDE == 0 ? P.A : P.B;
-  const Dims d = family_dims(SIDE == 0 ? kFamRes6A : kFamRes6B, P);
-  const int64_t bx = local % d.x, by = local / d.x;
-  const int64_t R = SIDE == 0 ? P.g.mp : P.g.np, kp = P.g.kp;
+  const Dims d = family_dims(kFamRes6, P), c = decode_block(d, local);
+  int64_t bx = c.x;
+  const int64_t by = c.y;
+  const int64_t first = P.res_sides & 1 ? P.g.mp / kR6L : 0;
+  const bool side = bx >= first;
+  if (side) bx -= first;
+  const Operand op = operand(P, side);
+  const int64_t R = side ? P.g.np : P.g.mp, kp = P.g.kp;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t r0 = bx * kR6L, h0 = by * kR6K + 32 * wave;
@@ -653,23 +712,25 @@ __global__ __launch_bounds__(256, 2) void k_residues6(Problem P1, Group G) {
     }
   }
   // a' = trunc(a 2^s); its magnitude is below 2^(e + 8)
-  const int64_t base_line = SIDE == 0 ? 0 : P.w.lineB;
-  const int s = P.w.shift[base_line + r], e = P.w.e[base_line + r];
+  const int64_t base_line = side ? P.w.lineB : 0;
+  CTables *tab = (CTables *)(uintptr_t)tables_of<GROUPED>(P1, G);
+  int e;
+  const int s = final_shift(P.w, base_line, r, tab->D, h0 == 0 && c.z == 0, &e);
 #pragma unroll
   for (int q = 0; q < kR6E; ++q) x[q] = trunc(ldexp(x[q], s));
   const int64_t slice_stride = R * kp / 4 * 3;
   const uint32_t off16 = (uint32_t)((lane & 3) * 1536 + 16 * ((lane >> 2) + 16 * wave));
   const uint32_t off8 = (uint32_t)((lane & 3) * 1536 + 1024 + 8 * ((lane >> 2) + 16 * wave));
-  uint8_t *base = (SIDE == 0 ? P.w.Asl : P.w.Bsl) + by * (R * 96) + bx * 6144;
-  CTables *tab = (CTables *)(uintptr_t)tables_of<GROUPED>(P1, G);
+  uint8_t *base = (side ? P.w.Bsl : P.w.Asl) + by * (R * 96) + bx * 6144;
+  const ModuliRange m = moduli_range(P.g, c.z, d.z);
   // |x| < 2^(e + 8): a step leaves |f| < R / 2 + 2^12 from below 2^63, two from
   // below 2^113; the scale exponent stays below 160, so four always do
   if (!__any(e > 55))
-    moduli6<1>(x, tab, P.g.nsq, P.g.nka, base, slice_stride, off16, off8);
+    moduli6<1>(x, tab, m, base, slice_stride, off16, off8);
   else if (!__any(e > 105))
-    moduli6<2>(x, tab, P.g.nsq, P.g.nka, base, slice_stride, off16, off8);
+    moduli6<2>(x, tab, m, base, slice_stride, off16, off8);
   else
-    moduli6<4>(x, tab, P.g.nsq, P.g.nka, base, slice_stride, off16, off8);
+    moduli6<4>(x, tab, m, base, slice_stride, off16, off8);
 }
 
 }  // namespace
@@ -693,27 +754,16 @@ hipError_t launch_quant_family(int fam, const Problem *P, const Group *G, hipStr
     hipLaunchKernelGGL((KER<true>), grid, blk, 0, st, p1, g1);              \
   else                                                                      \
     hipLaunchKernelGGL((KER<false>), grid, blk, 0, st, p1, g1);
-#define OZ2_Q2(KER, SIDE)                                                   \
-  if (grouped)                                                              \
-    hipLaunchKernelGGL((KER<true, SIDE>), grid, blk, 0, st, p1, g1);        \
-  else                                                                      \
-    hipLaunchKernelGGL((KER<false, SIDE>), grid, blk, 0, st, p1, g1);
   switch (fam) {
     case kFamFill: OZ2_Q(k_fill) break;
-    case kFamLmaxA: OZ2_Q2(k_line_max, 0) break;
-    case kFamLmaxB: OZ2_Q2(k_line_max, 1) break;
-    case kFamBarA: OZ2_Q2(k_bound_operand, 0) break;
-    case kFamBarB: OZ2_Q2(k_bound_operand, 1) break;
-    case kFamNormA: OZ2_Q2(k_bound_norm, 0) break;
-    case kFamNormB: OZ2_Q2(k_bound_norm, 1) break;
-    case kFamResA: OZ2_Q2(k_residues, 0) break;
-    case kFamResB: OZ2_Q2(k_residues, 1) break;
-    case kFamRes6A: OZ2_Q2(k_residues6, 0) break;
-    case kFamRes6B: OZ2_Q2(k_residues6, 1) break;
+    case kFamLmax: OZ2_Q(k_line_max) break;
+    case kFamBar: OZ2_Q(k_bound_operand) break;
+    case kFamNorm: OZ2_Q(k_bound_norm) break;
+    case kFamRes: OZ2_Q(k_residues) break;
+    case kFamRes6: OZ2_Q(k_residues6) break;
     default: return hipErrorInvalidValue;
   }
 #undef OZ2_Q
-#undef OZ2_Q2
   return hipGetLastError();
 }
 

@@ -58,6 +58,7 @@ __global__ __launch_bounds__(256) void k_scale_decide(Problem P1, Group G) {
     }
   }
   w.e[L] = ev;
+  w.shift[L] = 7 - w.E[L] + ev;  // (an undecided line's is replaced with its residues)
 }
 
 // Exact maxima of the bound product over the flagged lines.  With both
@@ -197,22 +198,6 @@ __global__ __launch_bounds__(kFixJ) void k_scale_fixup(Problem P1, Group G) {
   scale_fixup(P.w.Abar, P.w.Bbar, P.g.mp, P.g.np, P.g.kp, P.w.amb, P.w.rfix, local, d.x);
 }
 
-template <bool GROUPED>
-__global__ __launch_bounds__(256) void k_scale_finalize(Problem P1, Group G) {
-  int64_t local;
-  const Problem &P = *locate<GROUPED>(P1, G, blockIdx.x, local);
-  const int64_t L = local * 256 + threadIdx.x;
-  if (L >= P.g.mp + P.g.np) return;
-  const Work &w = P.w;
-  int ev = w.e[L];
-  if (w.flags[L] & kFixup) {
-    const uint64_t r18 = w.rfix[L];  // 2^18 x the exact line maximum, < 2^53
-    ev = r18 ? exponent_rule(ldexp((double)r18, -18), tables_of<GROUPED>(P1, G)->D) : 0;
-    w.e[L] = ev;
-  }
-  w.shift[L] = 7 - w.E[L] + ev;
-}
-
 }  // namespace
 
 hipError_t launch_scale_family(int fam, const Problem *P, const Group *G, hipStream_t st) {
@@ -237,7 +222,6 @@ hipError_t launch_scale_family(int fam, const Problem *P, const Group *G, hipStr
   switch (fam) {
     case kFamDecide: OZ2_S(k_scale_decide) break;
     case kFamFixup: OZ2_S(k_scale_fixup) break;
-    case kFamFinal: OZ2_S(k_scale_finalize) break;
     default: return hipErrorInvalidValue;
   }
 #undef OZ2_S
