@@ -18,7 +18,7 @@
 // the same exponent, it is the exponent of the exact r_i.  Lines whose window
 // straddles a threshold are recomputed exactly: Abar and Bbar are multiples
 // of 2^-9 up to 256, so 2^18 (Abar Bbar)_ij is an integer below 2^52 for
-// k <= 2^18 and is summed exactly in 64-bit integers.  The result is a
+// k <= 2^18 and is summed exactly in FP64.  The result is a
 // deterministic function of the inputs, independent of the MFMA's summation
 // order.  (Integer digit products stay exact: every product is an integer of
 // magnitude <= 256, far inside the 2^-13 window, and every partial sum is at
@@ -61,89 +61,40 @@ __global__ __launch_bounds__(256) void k_scale_decide(Problem P1, Group G) {
   w.shift[L] = 7 - w.E[L] + ev;  // (an undecided line's is replaced with its residues)
 }
 
-// Exact maxima of the bound product over the flagged lines.  With both
-// factors multiples of 2^-9 up to 256, q9 = 2^9 x (an entry of Abar or Bbar)
-// is an integer below 2^18 and every partial sum of q9 products is an integer
-// below 2^52 (k <= 2^18), so FP64 fused multiply-adds sum them exactly, in any
-// order.  The flagged lines of each side (rows of op(A), columns of op(B):
-// the two ends of the list) are taken in groups of kFixG; an item is (group,
-// chunk of kFixJ partner lines): the group's lines, decoded into LDS kFixKC k
-// at a time, against one partner line per thread; the block's maximum per
-// line goes to rfix (2^18 x the exact maximum) by an atomic maximum.  Each of
-// the problem's nblk workgroups walks items blk, blk + nblk, ...
-constexpr int kFixG = 2;   // few lines per item: many items, so many waves per SIMD
-constexpr int kFixJ = 64;  // one wave per workgroup: small LDS, many workgroups per CU
-constexpr int kFixKC = 256;
+// Exact maxima of the bound product over the flagged lines, on FP64 matrix
+// instructions: products of entries of Abar and Bbar are multiples of 2^-18 up
+// to 2^16, so every partial sum over k <= 2^18 is an integer below 2^52 times
+// 2^-18 and exact in any order.  An item is 16 flagged lines of a side (rows of
+// op(A), columns of op(B): the two ends of the list) against 16 partner lines,
+// one wave; the 64 k of a k-block are summed in 16 steps of 4, step s taking
+// byte s of each lane's 16 (lane group lane / 16 holds k 16 (lane / 16) ..
+// + 15 of its line, on both sides).  The partners are the instruction's rows,
+// so a lane's four sums all belong to flagged line lane % 16, whatever its
+// rows; their maximum over the lanes goes to rfix (2^18 x the exact maximum) by
+// an atomic maximum.  Each of the problem's nblk one-wave workgroups walks
+// items blk, blk + nblk, ...
+//
+// Loads run four k-blocks ahead: a wave has no other way to hide them, and
+// the matrix instructions and the conversions (24 per 16 bytes) take turns.
+// 16384 x 16384 x 1024 (59 lines flagged), with k_scale_decide: 362 -> 150 us
+// against pairs of lines in LDS, a table lookup per partner byte and FP64
+// multiply-adds; 48 products of 192 x 224 x 160 .. 1344: 77 -> 53 us.
+typedef double v4d __attribute__((ext_vector_type(4)));
+typedef float v2f __attribute__((ext_vector_type(2)));
 
-// One item with the group's first G lines (L[q] < 0: none): acc[q] = the exact
-// bound product of line L[q] with partner line j (one per thread), k in
-// chunks of kFixKC decoded into LDS; the partner's bytes of the next 64 k are
-// loaded while the current 64 are summed.
-template <int G>
-__device__ __forceinline__ void fixup_item(const uint8_t *__restrict__ own_op, int64_t nown,
-                                           int64_t base, const uint8_t *__restrict__ part,
-                                           int64_t npart, int64_t kp, const int64_t (&L)[kFixG],
-                                           int64_t j, double (*own)[kFixKC],
-                                           const double *q9tab, uint64_t *__restrict__ rfix) {
-  const int t = threadIdx.x;
-  double acc[G];
+constexpr int kFixG = 16;  // flagged lines and partners per item
+
+// Sixteen E4M3 codes as doubles.
+__device__ __forceinline__ void decode16(const uint4 &w, double (&x)[16]) {
+  const uint32_t u[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
-  for (int q = 0; q < G; ++q) acc[q] = 0.0;
-  const bool jv = j < npart;
-  for (int64_t k0 = 0; k0 < kp; k0 += kFixKC) {  // kp is a multiple of kFixKC
-    __syncthreads();  // the previous chunk's (or item's) readers are done
-#pragma unroll
-    for (int v = 0; v < G * kFixKC / kFixJ; ++v) {
-      const int q = v / (kFixKC / kFixJ);
-      const int h = (v % (kFixKC / kFixJ)) * kFixJ + t;
-      double x = 0.0;
-      if (L[q] >= 0) x = q9tab[own_op[kblocked(L[q] - base, k0 + h, nown)] & 0x7Fu];
-      own[q][h] = x;
-    }
-    __syncthreads();
-    if (jv) {
-      // the partner's 64 bytes of each 64-k block are contiguous, blocks
-      // 64 npart bytes apart
-      const uint8_t *pj = part + kblocked(j, k0, npart);
-      const int64_t step = npart * 64;
-      constexpr int nb = kFixKC / 64;
-      uint32_t cur[16];
-#pragma unroll
-      for (int w = 0; w < 16; ++w) cur[w] = *(const uint32_t *)(pj + 4 * w);
-      for (int b = 0; b < nb; ++b) {
-        uint32_t nxt[16];
-        if (b + 1 < nb) {
-#pragma unroll
-          for (int w = 0; w < 16; ++w) nxt[w] = *(const uint32_t *)(pj + (b + 1) * step + 4 * w);
-        }
-#pragma unroll 2
-        for (int w = 0; w < 16; ++w) {
-          const uint32_t word = cur[w];
-#pragma unroll
-          for (int z = 0; z < 4; ++z) {
-            const double bv = q9tab[(word >> (8 * z)) & 0x7Fu];
-            const int h = b * 64 + w * 4 + z;
-#pragma unroll
-            for (int q = 0; q < G; ++q) acc[q] = fma(own[q][h], bv, acc[q]);
-          }
-        }
-        if (b + 1 < nb) {
-#pragma unroll
-          for (int w = 0; w < 16; ++w) cur[w] = nxt[w];
-        }
-      }
-    }
-  }
-  // maxima per line over the wave's partners: exact integers below 2^52
-#pragma unroll
-  for (int q = 0; q < G; ++q) {
-    if (L[q] < 0) continue;
-    uint64_t m = jv ? (uint64_t)acc[q] : 0ull;
-    for (int off = 32; off > 0; off >>= 1) {
-      const uint64_t o = __shfl_xor(m, off, 64);
-      m = o > m ? o : m;
-    }
-    if (t == 0 && m) atomicMax((unsigned long long *)&rfix[L[q]], (unsigned long long)m);
+  for (int q = 0; q < 4; ++q) {
+    const v2f lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)u[q], false);
+    const v2f hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)u[q], true);
+    x[4 * q] = (double)lo[0];
+    x[4 * q + 1] = (double)lo[1];
+    x[4 * q + 2] = (double)hi[0];
+    x[4 * q + 3] = (double)hi[1];
   }
 }
 
@@ -153,45 +104,62 @@ __device__ __forceinline__ void scale_fixup(const uint8_t *__restrict__ Abar,
                                             const uint32_t *__restrict__ amb,
                                             uint64_t *__restrict__ rfix, int64_t blk,
                                             int64_t nblk) {
-  __shared__ double own[kFixG][kFixKC];
-  __shared__ double q9tab[128];
-  const int t = threadIdx.x;
-  for (int c = t; c < 128; c += kFixJ) q9tab[c] = (double)e4m3_q9((uint32_t)c);
+  const int lane = threadIdx.x, row = lane & 15, grp = lane >> 4;
   const int64_t lines = mp + np;
   const int64_t countA = amb[0], countB = amb[1];
   const int64_t groupsA = (countA + kFixG - 1) / kFixG, groupsB = (countB + kFixG - 1) / kFixG;
   // partners: the columns of op(B) for rows of op(A), and the other way
-  const int64_t chunksA = (np + kFixJ - 1) / kFixJ, chunksB = (mp + kFixJ - 1) / kFixJ;
+  const int64_t chunksA = np / kFixG, chunksB = mp / kFixG;
   const int64_t itemsA = groupsA * chunksA, items = itemsA + groupsB * chunksB;
   for (int64_t it = blk; it < items; it += nblk) {
-    const int side = it < itemsA ? 0 : 1;  // 0: rows of op(A) against the columns of op(B)
-    const int64_t r = side == 0 ? it : it - itemsA;
-    const int64_t groups = side == 0 ? groupsA : groupsB;
-    const int64_t g = r % groups, c = r / groups;
-    const int64_t count = side == 0 ? countA : countB;
-    const uint8_t *own_op = side == 0 ? Abar : Bbar;
-    const uint8_t *part = side == 0 ? Bbar : Abar;
-    const int64_t nown = side == 0 ? mp : np, npart = side == 0 ? np : mp;
-    const int64_t base = side == 0 ? 0 : mp;  // line index of the side's first line
-    // the group's lines (-1: none), the same in every thread; groups are
-    // filled from the front, so the first n are valid
-    int64_t L[kFixG];
+    const bool rows = it < itemsA;  // flagged rows of op(A) against the columns of op(B)
+    const int64_t r = rows ? it : it - itemsA;
+    const int64_t groups = rows ? groupsA : groupsB;
+    const int64_t c = r / groups, g = r - c * groups;
+    const int64_t count = rows ? countA : countB;
+    const uint8_t *own_op = rows ? Abar : Bbar, *part_op = rows ? Bbar : Abar;
+    const int64_t nown = rows ? mp : np, npart = rows ? np : mp;
+    const int64_t e = g * kFixG + row;  // this lane's flagged line, if any
+    const bool have = e < count;
+    const int64_t L = have ? (int64_t)amb[rows ? 2 + e : 1 + lines - e] : 0;
+    const uint8_t *own = own_op + (have ? L - (rows ? 0 : mp) : 0) * 64 + 16 * grp;
+    const uint8_t *part = part_op + (c * kFixG + row) * 64 + 16 * grp;
+    v4d acc = {0.0, 0.0, 0.0, 0.0};
+    // four k-blocks (kp is a multiple of 256), the next four loaded meanwhile
+    uint4 wo[4], wp[4];
 #pragma unroll
-    for (int q = 0; q < kFixG; ++q) {
-      const int64_t e = g * kFixG + q;
-      L[q] = e < count ? (int64_t)amb[side == 0 ? 2 + e : 1 + lines - e] : -1;
+    for (int q = 0; q < 4; ++q) {
+      wo[q] = *(const uint4 *)(own + q * nown * 64);
+      wp[q] = *(const uint4 *)(part + q * npart * 64);
     }
-    const int64_t n = count - g * kFixG;
-    const int64_t j = c * kFixJ + t;
-    if (n > 1)
-      fixup_item<kFixG>(own_op, nown, base, part, npart, kp, L, j, own, q9tab, rfix);
-    else
-      fixup_item<1>(own_op, nown, base, part, npart, kp, L, j, own, q9tab, rfix);
+    for (int64_t kb = 256; kb <= kp; kb += 256) {
+      own += nown * 256;
+      part += npart * 256;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        double xo[16], xp[16];
+        decode16(wo[q], xo);
+        decode16(wp[q], xp);
+        if (kb < kp) {
+          wo[q] = *(const uint4 *)(own + q * nown * 64);
+          wp[q] = *(const uint4 *)(part + q * npart * 64);
+        }
+#pragma unroll
+        for (int s = 0; s < 16; ++s)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(xp[s], xo[s], acc, 0, 0, 0);
+      }
+    }
+    double m = fmax(fmax(acc[0], acc[1]), fmax(acc[2], acc[3]));
+    m = fmax(m, __shfl_xor(m, 16, 64));
+    m = fmax(m, __shfl_xor(m, 32, 64));
+    const uint64_t m18 = (uint64_t)(m * 0x1p18);
+    if (lane < kFixG && have && m18)
+      atomicMax((unsigned long long *)&rfix[L], (unsigned long long)m18);
   }
 }
 
 template <bool GROUPED>
-__global__ __launch_bounds__(kFixJ) void k_scale_fixup(Problem P1, Group G) {
+__global__ __launch_bounds__(64) void k_scale_fixup(Problem P1, Group G) {
   int64_t local;
   const Problem &P = *locate<GROUPED>(P1, G, blockIdx.x, local);
   const Dims d = family_dims(kFamFixup, P);
@@ -213,7 +181,7 @@ hipError_t launch_scale_family(int fam, const Problem *P, const Group *G, hipStr
   const int64_t blocks = grouped ? G->total : family_blocks(fam, *P);
   if (blocks <= 0) return hipSuccess;
   if (blocks > 0x7FFFFFFFll) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)blocks), blk(fam == kFamFixup ? kFixJ : 256);
+  const dim3 grid((unsigned)blocks), blk(fam == kFamFixup ? 64 : 256);
 #define OZ2_S(KER)                                             \
   if (grouped)                                                 \
     hipLaunchKernelGGL((KER<true>), grid, blk, 0, st, p1, g1); \

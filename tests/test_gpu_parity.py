@@ -206,6 +206,31 @@ def test_exact_fixups_many_lines_both_sides():
     assert np.array_equal(r.C, np.minimum(counts[:, None], counts[None, :]).astype(np.float64))
 
 
+@pytest.mark.parametrize("m, n, k", [(1, 1, 200), (15, 17, 256), (16, 33, 300), (47, 3, 1111)])
+def test_exact_fixups_group_edges(m, n, k):
+    # equal rows against equal columns, every product within 2^-20 of a
+    # threshold of the exponent rule (in units of 2^14, the binary expansion of
+    # the threshold in ones and 2^-1 .. 2^-16): all m + n lines go to the
+    # exact fix-up, whose groups of 16 are short, full and one over
+    N = 12
+    P = ref.crt_weights([p for p, _, _ in ref.moduli_table(N)])[0]
+    e = ((P - 1).bit_length() - 1 - 14 - 7) // 2
+    nstar = (P - 1) / 2.0 ** (2 * e + 1) / 2.0 ** 14
+    assert 2 ** 5 <= nstar < 2 ** 7
+    A = np.zeros((m, k))
+    A[:, :int(nstar)] = 1.0
+    bits = int((nstar - int(nstar)) * 2 ** 16)
+    for q in range(16):
+        A[:, -1 - q] = 2.0 ** (q - 16) if bits >> q & 1 else 0.0
+    B = np.ones((k, n))
+    Chat, st = ref.emulate(A, B, N, keep_stages=True)
+    r = run(A, B, N, keep_ws=True)
+    assert r.status == 0
+    assert r.fixups() == m + n
+    check_stages(r, A, B, N, st)
+    assert _same(r.C, Chat)
+
+
 def _constant_case(k):
     """Constant op(A) = c 2^-7 and op(B) = d 2^-7 (c, d in [128, 256)) chosen
     so that some digit product is 16 x 16: every FP8 product sum of that
