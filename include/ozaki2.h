@@ -176,14 +176,17 @@ int ozaki2_moduli(int num_moduli, int32_t *p, int32_t *kinds);
  *   off[4] uint8  [n_pad x k_pad]  Bbar (column j of op(B) as line j; accurate mode),
  *          k-blocked with n_pad lines
  *   off[5] uint8  [M x m_pad x k_pad]  digit slices of A' (slice order below), each
- *          k-blocked like Abar (INT8 residues as two's-complement bytes).  FP8
- *          lists with more than four output tiles (m_pad n_pad / 65536) hold
- *          the same digits as 6-bit E2M3 codes (sign, 5-bit magnitude) from the
- *          same offset, slice q at q (3/4) m_pad k_pad: line i, k h is code
- *          h % 32 (lowest bits first) of the 24 bytes of lane
- *          l = (i % 64) / 4 + 16 ((h % 128) / 32) in the 1536-byte fragment
+ *          k-blocked like Abar (INT8 residues as two's-complement bytes).  With
+ *          more than four output tiles (m_pad n_pad / 65536) they are kept in
+ *          fragments, from the same offset.  FP8 lists hold the digits as 6-bit
+ *          E2M3 codes (sign, 5-bit magnitude), slice q at q (3/4) m_pad k_pad:
+ *          line i, k h is code h % 32 (lowest bits first) of the 24 bytes of
+ *          lane l = (i % 64) / 4 + 16 ((h % 128) / 32) in the 1536-byte fragment
  *          i % 4 of line group i / 64 of 128-k stage h / 128 (stages outermost);
- *          a fragment holds the first 16 bytes of its 64 lanes, then their last 8
+ *          a fragment holds the first 16 bytes of its 64 lanes, then their last
+ *          8.  INT8 residues: byte h % 16 of the 16 bytes of lane
+ *          l = (i % 64) / 4 + 16 ((h % 64) / 16) in the 1024-byte fragment i % 4
+ *          of line group i / 64 of 64-k stage h / 64
  *   off[6] uint8  [M x n_pad x k_pad]  digit slices of B'
  *   off[7] int16  [N x n_pad x m_pad]  C'_l, entry (i, j) at l*n_pad*m_pad + j*m_pad + i;
  *          with k parts (ozaki2_set_split) one such copy per part, q*N*n_pad*m_pad
@@ -234,10 +237,10 @@ int ozaki2_workspace_parts(int64_t m, int64_t n, int64_t k, int num_moduli, int 
  * grouped launch over all problems, whose blocks are mapped to (problem,
  * tile) through prefix sums of per-problem tile counts.  The residue products
  * of all problems, moduli, 256 x 256 output tiles and k parts run as ONE
- * persistent launch (one workgroup per CU) that hands out a work list,
- * longest item first, through an atomic counter.  Its configuration (the
- * tile program and the split-K limit, see ozaki2_set_schedule) is the
- * default, the autotuner's choice (ozaki2_set_autotune) or a forced one.
+ * persistent launch (one workgroup per CU) over a work list, longest item
+ * first, dealt out in rounds.  Its configuration (the split-K limit, see
+ * ozaki2_set_schedule) is the default, the autotuner's choice
+ * (ozaki2_set_autotune) or a forced one.
  * Split-K applies to problems with at most 4 output tiles per modulus and a
  * padded k of at least 512: their k range is cut into up to 4 parts whose
  * products go to separate copies of the residue planes, summed by the CRT.
@@ -311,11 +314,10 @@ int ozaki2_get_schedule(void);
 /*
  * ozaki2_set_schedule - force the residue-product configuration of the
  * calling thread's subsequent batched calls, or -1 (default) to leave it to
- * the autotuner.  config / 3 is the tile program of the 256 x 256 output
- * tiles (0: eight waves of 128 x 64 outputs, two per SIMD; 1: four waves of
- * 128 x 128, one per SIMD; the FP8 lists have the first only, and 3 .. 5 then
- * act as 0 .. 2); config % 3 the split-K limit (at most 1, 2 or 4 k parts).  Every configuration gives bit-identical results.  Returns 0, or
- * -1 for a value outside -1..5 (the setting is then unchanged).
+ * the autotuner.  config % 3 is the split-K limit (at most 1, 2 or 4 k
+ * parts); there is one tile program, so 3 .. 5 act as 0 .. 2.  Every
+ * configuration gives bit-identical results.  Returns 0, or -1 for a value
+ * outside -1..5 (the setting is then unchanged).
  */
 int ozaki2_set_schedule(int config);
 

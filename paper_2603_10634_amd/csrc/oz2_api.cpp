@@ -292,19 +292,20 @@ bool valid_trans(char c) {
 
 bool is_trans(char c) { return !(c == 'N' || c == 'n'); }
 
-// Whether a single call's residue products run on E2M3 digits (k_residue6)
-// rather than E4M3 ones: FP8 lists with more than kE4M3Tiles output tiles in
-// the call, or in a full block of a blocked call (every block of a call has
-// the same format: op(A)'s digits serve a whole row of blocks).  Results are the same bits.  8192^3, N = 12: 8.55 against 12.7
-// ms, 4096^3 1.15 against 1.75.  Up to four tiles the digit slices stay E4M3
-// in the k-blocked layout that ozaki2_workspace_layout documents for
-// inspection (their launches leave most CUs idle in either format).  A batched
-// call of an FP8 list has E2M3 digits throughout: its problems share one
-// persistent launch.
-constexpr int64_t kE4M3Tiles = 4;
+// Whether a single call's digit slices are in the fragment order of k_residue6
+// (E2M3 digits; INT8 residues) rather than k-blocked (E4M3 digits; INT8
+// residues): with more than kBlockedTiles output tiles in the call, or in a full
+// block of a blocked call (every block of a call has the same format: op(A)'s
+// digits serve a whole row of blocks).  Results are the same bits.  Products of
+// 8192^3, N = 12: 8.55 against 12.7 ms, 4096^3 1.15 against 1.75, INT8 (N = 14)
+// 0.79 against 0.93.  Up to four tiles the slices stay in the k-blocked layout
+// that ozaki2_workspace_layout documents for inspection (their launches leave
+// most CUs idle in either format).  A batched call's are in fragment order
+// throughout: its problems share one persistent launch.
+constexpr int64_t kBlockedTiles = 4;
 
-int use_fp6(int list, int64_t mbp, int64_t nbp) {
-  return list != OZ2_MODULI_INT8 && (mbp / kGemmTIW) * (nbp / kGemmTJ) > kE4M3Tiles;
+int use_fp6(int64_t mbp, int64_t nbp) {
+  return (mbp / kGemmTIW) * (nbp / kGemmTJ) > kBlockedTiles;
 }
 
 // Problem descriptor of one call whose workspace starts at ws (layout L).
@@ -473,15 +474,11 @@ int enqueue_blocked(const Problem &P, int64_t mb, int64_t nb, hipStream_t st) {
 // ---- batched calls ----
 
 // Configurations of the batched residue products, chosen by the autotuner:
-// the tile program (config / 3: 0 = eight waves of 128 x 64 outputs per
-// 256 x 256 tile, two per SIMD; 1 = four waves of 128 x 128, one per SIMD)
-// and the split-K limit (config % 3: at most 1, 2 or 4 k parts for the
-// problems that parts_alloc allows to split).  Config 0 is the default.
-// The FP8 lists have the one tile program of k_residue6: their configurations
-// 3 .. 5 are 0 .. 2.
+// the split-K limit (config % 3: at most 1, 2 or 4 k parts for the problems
+// that parts_alloc allows to split).  There is one tile program (k_residue6),
+// so 3 .. 5 act as 0 .. 2.  Config 0 is the default.
 constexpr int kNumConfigs = 6;
-int distinct_configs(bool int8) { return int8 ? kNumConfigs : 3; }
-int config_waves(int c) { return c / 3 == 0 ? 8 : 4; }
+constexpr int kDistinctConfigs = 3;
 int config_max_parts(int c) { return c % 3 == 0 ? 1 : (c % 3 == 1 ? 2 : 4); }
 
 // Grouped launches of at most this many blocks carry a block -> problem
@@ -499,7 +496,7 @@ constexpr int kFamPersist = kNumFamilies;
 struct GLaunch {
   int fam, config;  // config: -1 for the launches every configuration shares
   size_t off_probs, off_order, off_start, off_seg;  // off_seg: 0 when there is no table
-  size_t off_items, off_counters;
+  size_t off_items;
   int64_t items;
   bool int8;
   Group G;
@@ -509,7 +506,6 @@ struct GLaunch {
 // Problems whose workspaces fit together, run as one set of grouped launches.
 struct SubBatch {
   std::vector<GLaunch> launches;
-  bool int8;
   int limbs;
   int N;  // number of moduli (every problem of a batch has the same)
 };
@@ -783,18 +779,14 @@ void build_subbatch(const std::vector<Problem> &probs, ImageWriter &W, SubBatch 
     L.G.total = start[np];
     sb->launches.push_back(L);
   };
-  sb->int8 = probs[0].g.list == OZ2_MODULI_INT8;
-  const Family res = sb->int8 ? kFamRes : kFamRes6;
   // every problem of a batch has the calling thread's mode
   if (probs[0].mode == OZ2_MODE_FAST) {
-    for (int f : {kFamFill, kFamLmax, kFamNorm, res}) add(f, at_probs, -1);
+    for (int f : {kFamFill, kFamLmax, kFamNorm, kFamRes6}) add(f, at_probs, -1);
   } else {
-    for (int f : {kFamFill, kFamLmax, kFamBar, kFamBgemm, kFamDecide, kFamFixup, res})
+    for (int f : {kFamFill, kFamLmax, kFamBar, kFamBgemm, kFamDecide, kFamFixup, kFamRes6})
       add(f, at_probs, -1);
   }
-  const uint32_t zero2[2] = {0u, 0u};
-  const size_t at_counters = W.put(zero2, sizeof(zero2));
-  for (int c = 0; c < distinct_configs(sb->int8); ++c) {
+  for (int c = 0; c < kDistinctConfigs; ++c) {
     std::vector<Problem> pc(probs);
     std::vector<ProductItem> items;
     for (int q = 0; q < np; ++q) {
@@ -832,9 +824,8 @@ void build_subbatch(const std::vector<Problem> &probs, ImageWriter &W, SubBatch 
       L.config = c;
       L.off_probs = at_pc;
       L.off_items = W.put(items.data(), sizeof(ProductItem) * items.size());
-      L.off_counters = at_counters;
       L.items = (int64_t)items.size();
-      L.int8 = sb->int8;
+      L.int8 = probs[0].g.list == OZ2_MODULI_INT8;
       sb->launches.push_back(L);
     }
     add(kFamCrt, at_pc, c);
@@ -870,12 +861,12 @@ int enqueue_subbatch(const SubBatch &sb, int config, int cus, hipStream_t st, Ma
     return OZ2_SUCCESS;
   };
   for (const GLaunch &L : sb.launches) {
-    if (L.config >= 0 && L.config != config % distinct_configs(sb.int8)) continue;
+    if (L.config >= 0 && L.config != config % kDistinctConfigs) continue;
     const int gq = family_group(L.fam);
     if (gq < g0 || gq > g1) continue;
     if (advance(gq) != OZ2_SUCCESS) return OZ2_ERR_HIP;
     if (L.fam == kFamPersist)
-      OZ2_TRY(launch_gemm_persistent(config_waves(config), L.int8, L.W, cus, st));
+      OZ2_TRY(launch_gemm_persistent(8, L.int8, L.W, cus, st));
     else if (L.fam == kFamBgemm)
       OZ2_TRY(launch_gemm_family(L.fam, nullptr, &L.G, st));
     else if (L.fam == kFamDecide || L.fam == kFamFixup)
@@ -933,7 +924,7 @@ int dgemm_fixed(char transA, char transB, int64_t m, int64_t n, int64_t k, doubl
   if (L.total > res.ws_bytes) return OZ2_ERR_SCRATCH;
   const Tables *dt = res.tables + (size_t)ts.list * kMaxN + (num_moduli - 1);
   const Problem P = make_problem(transA, transB, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc,
-                                 num_moduli, res.ws, L, dt, ht, use_fp6(ts.list, L.mbp, L.nbp));
+                                 num_moduli, res.ws, L, dt, ht, use_fp6(L.mbp, L.nbp));
   if (L.mbp < L.mp || L.nbp < L.np) return enqueue_blocked(P, L.mbp, L.nbp, st);
   Marks none{&ts, st, false};
   return enqueue_single(P, st, none);
@@ -1132,7 +1123,7 @@ int ozaki2_dgemm(char transA, char transB, int64_t m, int64_t n, int64_t k, doub
   int r = get_workspace(dev, L.total, &ws, &have);
   if (r != OZ2_SUCCESS) return r;
   const Problem P = make_problem(transA, transB, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc,
-                                 num_moduli, ws, L, dt, ht, use_fp6(ts.list, L.mbp, L.nbp));
+                                 num_moduli, ws, L, dt, ht, use_fp6(L.mbp, L.nbp));
   const bool blocked = L.mbp < L.mp || L.nbp < L.np;
   const int64_t mb = L.mbp, nb = L.nbp;
 
@@ -1328,7 +1319,7 @@ int ozaki2_dgemm_batched(int count, const char *transA, const char *transB, cons
       if (used + L.total > have) flush();
       cur.push_back(make_problem(transA[q], transB[q], m[q], n[q], k[q], alpha[q], A[q], lda[q],
                                  B[q], ldb[q], beta[q], C[q], ldc[q], num_moduli, ws + used, L,
-                                 dt, ht, ts.list != OZ2_MODULI_INT8));
+                                 dt, ht, 1));
       used += L.total;
       for (int64_t v : {m[q], n[q], k[q]}) p->shape_key.push_back(v);
     }
@@ -1351,7 +1342,6 @@ int ozaki2_dgemm_batched(int count, const char *transA, const char *transB, cons
             L.W.probs = (const Problem *)(base + L.off_probs);
             L.W.items = (const ProductItem *)(base + L.off_items);
             L.W.count = L.items;
-            L.W.counters = (uint32_t *)(base + L.off_counters);
             continue;
           }
           L.G.probs = (const Problem *)(base + L.off_probs);
@@ -1395,7 +1385,7 @@ int ozaki2_dgemm_batched(int count, const char *transA, const char *transB, cons
     // real pass)
     r = enqueue_subbatch(sb, 0, cus, st, none, nullptr, 0, 3);
     if (r != OZ2_SUCCESS) return r;
-    for (int c = 0; c < distinct_configs(sb.int8); ++c) {
+    for (int c = 0; c < kDistinctConfigs; ++c) {
       r = enqueue_subbatch(sb, c, cus, st, none, ts.ev, 4, 4);
       if (r != OZ2_SUCCESS) return r;
       float t = 0.0f;

@@ -597,14 +597,13 @@ __device__ __forceinline__ void int8_tile_w(const uint8_t *Asl, const uint8_t *B
                                             int16_t *__restrict__ planes,
                                             const Tables *__restrict__ tab, int64_t mp,
                                             int64_t np, int64_t kp, int64_t kbeg, int nk,
-                                            int accumulate, int l, int64_t i0, int64_t j0,
+                                            int l, int64_t i0, int64_t j0,
                                             uint8_t *lds, int tid) {
   const int sl0 = (int)uni(tab->slice0[l]);
   const int p = (int)uni(tab->p[l]);
   const float inv = __int_as_float((int)uni(__float_as_int(tab->inv_p[l])));
   resident(sl0, p, __float_as_int(inv), p);
   resident_ptr(planes, planes);
-  resident(accumulate, accumulate, accumulate, accumulate);
   const uint8_t *A0 = Asl + (int64_t)sl0 * mp * kp + i0 * 64;
   const uint8_t *B0 = Bsl + (int64_t)sl0 * np * kp + j0 * 64;
 
@@ -629,11 +628,10 @@ __device__ __forceinline__ void int8_tile_w(const uint8_t *Asl, const uint8_t *B
     for (int ti = 0; ti < TBW; ++ti) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        int r = smod_i32(acc[tj][ti][v], p, inv);
+        const int r = smod_i32(acc[tj][ti][v], p, inv);
         const int64_t i = i0 + wi * 32 * TBW + ti * 32 + (lane & 31);
         const int64_t j = j0 + wj * 128 + tj * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
         int16_t *dst = out + j * mp + i;
-        if (accumulate) r = smod_i32(r + (int)*dst, p, inv);
         *dst = (int16_t)r;
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -660,7 +658,7 @@ __global__ __launch_bounds__(64 * NW_RES, 1) void k_residue_gemm(Problem P) {
   int16_t *planes = uni(P.w.planes) + uni((int64_t)part * g.N) * mp * np;
   const int tid = threadIdx.x;
   if (INT8)
-    int8_tile_w<NW_RES>(uni(P.w.Asl), uni(P.w.Bsl), planes, uni(P.tab), mp, np, kp, k0, nk, 0, l,
+    int8_tile_w<NW_RES>(uni(P.w.Asl), uni(P.w.Bsl), planes, uni(P.tab), mp, np, kp, k0, nk, l,
                         uni(c.x * TIW), uni(c.y * TJ), lds, tid);
   else if (l < g.nsq)
     square_tile_w<NW_RES>(uni(P.w.Asl), uni(P.w.Bsl), planes, uni(P.tab), mp, np, kp, k0, nk, l,
@@ -668,49 +666,6 @@ __global__ __launch_bounds__(64 * NW_RES, 1) void k_residue_gemm(Problem P) {
   else
     karatsuba_tile_w<NW_RES>(uni(P.w.Asl), uni(P.w.Bsl), planes, uni(P.tab), mp, np, kp, k0, nk,
                              l, uni(c.x * TIW), uni(c.y * TJ), lds, tid);
-}
-
-// The INT8 residue products of a whole batch in one launch (the FP8 lists':
-// k_residue6): each workgroup takes the next item of the work list (tile x
-// modulus x k part of one problem, longest first) until the list is
-// exhausted; the k chunks of an item run in order inside the workgroup,
-// accumulating into its plane copy.  The last workgroup to finish clears the counters for the next launch, so the launch
-// needs no memset and replays from a graph.
-template <int NW>
-__global__ __launch_bounds__(64 * NW, 1) void k_residue_persistent(WorkList W) {
-  __shared__ __attribute__((aligned(1024))) uint8_t lds[LDS_RING];
-  __shared__ uint32_t item_s;
-  for (;;) {
-    if (threadIdx.x == 0) item_s = atomicAdd(&W.counters[0], 1u);
-    __syncthreads();
-    const int64_t it = (int64_t)__builtin_amdgcn_readfirstlane(item_s);
-    __syncthreads();
-    if (it >= W.count) break;
-    const ProductItem *I = uni(W.items) + it;
-    const Problem &P = uni(W.probs)[(int)uni((int64_t)I->prob)];
-    const int64_t mp = uni(P.g.mp), np = uni(P.g.np), kp = uni(P.g.kp);
-    const int l = (int)uni((int64_t)I->l);
-    const int64_t k0 = uni((int64_t)I->k0), k1 = uni((int64_t)I->k1);
-    const int64_t i0 = uni((int64_t)I->tx * TIW), j0 = uni((int64_t)I->ty * TJ);
-    int16_t *planes = uni(P.w.planes) + uni((int64_t)I->part * P.g.N) * mp * np;
-    for (int64_t kb = k0; kb < k1; kb += kChunkK) {
-      const int64_t len = k1 - kb < kChunkK ? k1 - kb : kChunkK;
-      // the thread index, opaque to the compiler once per chunk: the
-      // epilogue's addresses derived from it are then formed after the
-      // k-loop instead of being hoisted above it and kept live (spilled)
-      int tid = threadIdx.x;
-      asm volatile("" : "+v"(tid));
-      int8_tile_w<NW>(uni(P.w.Asl), uni(P.w.Bsl), planes, uni(P.tab), mp, np, kp, kb,
-                      (int)(len / BK), kb > k0 ? 1 : 0, l, i0, j0, lds, tid);
-    }
-  }
-  if (threadIdx.x == 0) {
-    __threadfence();
-    if (atomicAdd(&W.counters[1], 1u) == gridDim.x - 1) {
-      atomicExch(&W.counters[0], 0u);
-      atomicExch(&W.counters[1], 0u);
-    }
-  }
 }
 
 // Line maxima of one 256 x 256 tile (j0.., i0..) of the bound product held in
@@ -899,18 +854,8 @@ __global__ __launch_bounds__(64 * NW_BOUND) void k_bound_reduce(Problem P) {
 
 hipError_t launch_gemm_persistent(int nw, bool int8, const WorkList &W, int64_t grid,
                                   hipStream_t st) {
-  if (W.count <= 0) return hipSuccess;
-  if (!int8) return launch_gemm6_list(W, grid, st);
-  if (grid > W.count) grid = W.count;
-  if (grid <= 0 || grid > 0x7FFFFFFFll || W.count > 0xFFFFFFFFll) return hipErrorInvalidValue;
-  const dim3 gr((unsigned)grid);
-  if (nw == 8)
-    hipLaunchKernelGGL((k_residue_persistent<8>), gr, dim3(64 * 8), 0, st, W);
-  else if (nw == 4)
-    hipLaunchKernelGGL((k_residue_persistent<4>), gr, dim3(64 * 4), 0, st, W);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
+  if (nw != 8) return hipErrorInvalidValue;
+  return W.count <= 0 ? hipSuccess : launch_gemm6_list(int8, W, grid, st);
 }
 
 hipError_t launch_gemm_family(int fam, const Problem *P, const Group *G, hipStream_t st) {

@@ -1,5 +1,6 @@
-// Residue products on E2M3 digits (v_mfma_f32_16x16x128_f8f6f4, FP32
-// accumulation).
+// Residue products of calls of more than four output tiles and of batches: on
+// E2M3 digits (v_mfma_f32_16x16x128_f8f6f4, FP32 accumulation), or on INT8
+// residues (v_mfma_i32_16x16x64_i8, INT32 accumulation).
 //
 // Every digit of Sections III-B and III-C is an integer of magnitude at most
 // 16, and E2M3 (6 bits, steps of 1/8 up to 2, OCP MX) holds d / 8 exactly for
@@ -30,6 +31,13 @@
 // gives each lane four consecutive rows i of its column j in the accumulators,
 // so the int16 planes are stored 8 bytes per lane.
 //
+// INT8 residues (Section II, one product per modulus) keep the same order with
+// stages of 64 k, fragments of 1 KB and lane l = r / 4 + 16 (h / 16) holding 16
+// k.  A register-only loop sustains 4.17 POP/s with 16 x 16 x 64 steps and 3.47
+// with 32 x 32 x 32.  4096^3, N = 14: residues 248 -> 151 us and products 933 ->
+// 789 us (2.4 POP/s) against k-blocked slices and a workgroup per tile on 32 x
+// 32 x 32 steps.
+//
 // Workgroup: 256 (j) x 256 (i) outputs, 8 waves of 128 x 64 (128 accumulator
 // registers each, two waves per SIMD), one per CU, walking the (part,
 // modulus, tile) items in rounds of the grid.  The stages of an
@@ -40,6 +48,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "oz2_internal.h"
 
@@ -52,17 +61,30 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-constexpr int NW = 8;                       // waves: 2 (j) x 4 (i), each 128 x 64
-constexpr int TJ = 8, TI = 4;               // MFMA tiles of 16 x 16 per wave
-constexpr int FRAG = 1536;                  // bytes of a fragment: 16 lines x 128 k
-constexpr int SIDE = kGemmTJ / 16 * FRAG;   // one side of a stage: 256 lines, 24 KB
-constexpr int STAGE = 2 * SIDE;             // B side, then A side
-constexpr int S = 3;                        // ring slots
+constexpr int NW = 8;                       // waves: 2 (j) x 4 (i)
+constexpr int TJ = 8, TI = 4;               // MFMA tiles of 16 x 16 per wave: 128 x 64
 constexpr int64_t kCUs = 256;               // one workgroup per CU
-constexpr int RING = S * STAGE;             // 144 KB
-constexpr int LPW = STAGE / 1024 / NW;      // 1 KB loads per wave and stage
-static_assert(LPW == 6 && kGemmTJ == 256 && kGemmTIW == 256 && kPad % (2 * kStage6) == 0,
-              "tile shape");
+
+// The two formats of the slices: fragments of FRAG bytes, 16 lines x BK k (an
+// MFMA step, and a stage), S ring slots, PASSES products per modulus.
+template <bool I8_>
+struct Format {
+  static constexpr bool I8 = I8_;
+  static constexpr int FRAG = I8 ? 1024 : 1536;
+  static constexpr int BK = I8 ? kStage8 : kStage6;
+  static constexpr int S = I8 ? 4 : 3;
+  static constexpr int PASSES = I8 ? 1 : 3;
+  static constexpr int SIDE = kGemmTJ / 16 * FRAG;  // one side of a stage: 256 lines
+  static constexpr int STAGE = 2 * SIDE;            // B side, then A side
+  static constexpr int RING = S * STAGE;            // 144 KB (E2M3), 128 KB (INT8)
+  static constexpr int LPW = STAGE / 1024 / NW;     // 1 KB loads per wave and stage
+  typedef typename std::conditional<I8, v4i, v8i>::type Frag;
+  typedef typename std::conditional<I8, v4i, v4f>::type Acc;
+  static_assert(kGemmTJ == 32 * TJ && kGemmTIW == 64 * TI && LPW == (I8 ? 4 : 6) &&
+                kPad % (2 * BK) == 0, "tile shape");
+};
+typedef Format<false> E2M3;
+typedef Format<true> Int8;
 
 template <int N>
 __device__ __forceinline__ void wait_vm() {
@@ -74,18 +96,24 @@ __device__ __forceinline__ void wait_lgkm0() {
 }
 
 __device__ __forceinline__ int uni32(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ v4f mma6(v8i a, v8i b, v4f c) {
+__device__ __forceinline__ v4f mma(v8i a, v8i b, v4f c) {
   // cbsz = blgp = 2 selects E2M3 for both operands
   return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 2, 2, 0, 0, 0, 0);
 }
+__device__ __forceinline__ v4i mma(v4i a, v4i b, v4i c) {
+  return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
+}
 
-// A fragment: lane l's 32 digits (192 bits) as its first 16 bytes in one run
-// of 64 lanes and its last 8 in another.
-__device__ __forceinline__ v8i frag(const uint8_t *p, int lane) {
+// A fragment: of E2M3, lane l's 32 digits (192 bits) as its first 16 bytes in
+// one run of 64 lanes and its last 8 in another; of INT8, its 16 bytes.
+__device__ __forceinline__ void frag(v8i &f, const uint8_t *p, int lane) {
   const v4i lo = *(const v4i *)(p + 16 * lane);
   const v2i hi = *(const v2i *)(p + 1024 + 8 * lane);
-  return __builtin_shufflevector(lo, __builtin_shufflevector(hi, hi, 0, 1, -1, -1), 0, 1, 2, 3, 4,
-                                 5, -1, -1);
+  f = __builtin_shufflevector(lo, __builtin_shufflevector(hi, hi, 0, 1, -1, -1), 0, 1, 2, 3, 4, 5,
+                              -1, -1);
+}
+__device__ __forceinline__ void frag(v4i &f, const uint8_t *p, int lane) {
+  f = *(const v4i *)(p + 16 * lane);
 }
 
 __device__ __forceinline__ void dma16(const uint8_t *base, uint32_t voff, uint32_t lds_off) {
@@ -122,11 +150,12 @@ __device__ __forceinline__ void start_pass(Producer &p) {
 }
 
 // On to the next stage: of the pass, of the item's next pass or of the next item.
+template <int PASSES>
 __device__ __forceinline__ void advance(Producer &p) {
   p.pA += p.it.stA;
   p.pB += p.it.stB;
   if (__builtin_expect(--p.left == 0, 0)) {
-    if (++p.pass == 3) {
+    if (++p.pass == PASSES) {
       p.pass = 0;
       p.it = p.next;
     }
@@ -134,16 +163,18 @@ __device__ __forceinline__ void advance(Producer &p) {
   }
 }
 
+template <int LPW>
 struct Lanes {
   uint32_t vo[LPW / 2];  // byte offset of this lane in each of its wave's loads of a side
   uint32_t ls;           // place of the wave's first load in a slot
 };
 
-// Load u (0 .. 5: three of the B side, three of the A side) of the producer's
-// stage into the slot at LDS byte address `slot`.
-template <int U>
-__device__ __forceinline__ void load(const Producer &p, const Lanes &ln, uint32_t slot) {
-  dma16(U < 3 ? p.pB : p.pA, ln.vo[U % 3], slot + ln.ls + 1024u * NW * U);
+// Load u of the producer's stage (the first half of the B side, the second of
+// the A side) into the slot at LDS byte address `slot`.
+template <class F, int U>
+__device__ __forceinline__ void load(const Producer &p, const Lanes<F::LPW> &ln, uint32_t slot) {
+  constexpr int H = F::LPW / 2;
+  dma16(U < H ? p.pB : p.pA, ln.vo[U % H], slot + ln.ls + 1024u * NW * U);
   __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -153,64 +184,76 @@ struct Ring {
   uint32_t fill;     // slot offset of the stage being loaded
 };
 
+template <class F>
 __device__ __forceinline__ uint32_t next_slot(uint32_t s) {
-  return s + STAGE == RING ? 0u : s + STAGE;
+  return s + F::STAGE == F::RING ? 0u : s + F::STAGE;
 }
 
-// One stage j (128 k) of a wave's 128 x 64 outputs: rows tj of four MFMAs, the
-// B fragment of row tj + 3 read and one or two of the six loads of stage j + 2
-// (into the slot stage j - 1 left) issued between them; before the last two
-// rows the barrier B_j, at which the wave's own loads of stage j + 1 have
-// landed and its reads of stage j are done; under those rows the A fragments
-// and first three B fragments of stage j + 1 are read.  ZERO: the accumulators
-// start at zero.  WAIT: wait for the loads (else they are known to be there).
-template <bool ZERO, bool WAIT>
-__device__ __forceinline__ void stage(Producer &p, const Lanes &ln, Ring &r, const uint8_t *lds,
-                                      const v8i (&fa)[TI], v8i (&fan)[TI], v8i (&fb0)[3],
-                                      v4f (&acc)[TJ][TI], int lane, int wj, int wi) {
+// One stage j of a wave's 128 x 64 outputs: rows tj of four MFMAs, the B fragment of row tj + 3 read and the loads of stage j + S - 1 (into the
+// slot stage j - 1 left) issued between them; before the last two rows the barrier
+// B_j, at which the wave's own loads of stage j + 1 have landed and its reads
+// of stage j are done; under those rows the A fragments and first three B
+// fragments of stage j + 1 are read.  ZERO: the accumulators start at zero.
+// WAIT: wait for the loads (else they are known to be there).
+template <bool ZERO, bool WAIT, class F>
+__device__ __forceinline__ void stage(Producer &p, const Lanes<F::LPW> &ln, Ring &r,
+                                      const uint8_t *lds, const typename F::Frag (&fa)[TI],
+                                      typename F::Frag (&fan)[TI],
+                                      typename F::Frag (&fb0)[3],
+                                      typename F::Acc (&acc)[TJ][TI], int lane, int wj,
+                                      int wi) {
+  constexpr int FRAG = F::FRAG;
   const uint8_t *cur = lds + r.cur + wj * TJ * FRAG;
   const uint32_t fill = r.base + r.fill;
-  const v4f zero = {0.0f, 0.0f, 0.0f, 0.0f};
-  v8i fb[TJ];
+  const typename F::Acc zero = {0, 0, 0, 0};
+  typename F::Frag fb[TJ];
 #pragma unroll
   for (int t = 0; t < 3; ++t) fb[t] = fb0[t];
 #pragma unroll
   for (int tj = 0; tj < TJ - 2; ++tj)
 #pragma unroll
     for (int ti = 0; ti < TI; ++ti) {
-      acc[tj][ti] = mma6(fb[tj], fa[ti], ZERO ? zero : acc[tj][ti]);
+      acc[tj][ti] = mma(fb[tj], fa[ti], ZERO ? zero : acc[tj][ti]);
       __builtin_amdgcn_sched_barrier(0);
       if (ti == 0 && tj + 3 < TJ) {
-        fb[tj + 3] = frag(cur + (tj + 3) * FRAG, lane);
+        frag(fb[tj + 3], cur + (tj + 3) * FRAG, lane);
         __builtin_amdgcn_sched_barrier(0);
       }
-      if (tj == 0 && ti == 1) load<0>(p, ln, fill);
-      if (tj == 0 && ti == 3) load<3>(p, ln, fill);
-      if (tj == 1 && ti == 1) load<1>(p, ln, fill);
-      if (tj == 1 && ti == 3) load<4>(p, ln, fill);
-      if (tj == 2 && ti == 1) load<2>(p, ln, fill);
-      if (tj == 2 && ti == 3) load<5>(p, ln, fill);
+      const int q = tj * TI + ti;
+      if constexpr (F::LPW == 6) {
+        if (q == 1) load<F, 0>(p, ln, fill);
+        if (q == 3) load<F, 3>(p, ln, fill);
+        if (q == 5) load<F, 1>(p, ln, fill);
+        if (q == 7) load<F, 4>(p, ln, fill);
+        if (q == 9) load<F, 2>(p, ln, fill);
+        if (q == 11) load<F, 5>(p, ln, fill);
+      } else {
+        if (q == 1) load<F, 0>(p, ln, fill);
+        if (q == 4) load<F, 2>(p, ln, fill);
+        if (q == 7) load<F, 1>(p, ln, fill);
+        if (q == 10) load<F, 3>(p, ln, fill);
+      }
     }
-  advance(p);
-  r.fill = next_slot(r.fill);
+  advance<F::PASSES>(p);
+  r.fill = next_slot<F>(r.fill);
   wait_lgkm0();
-  if (WAIT) wait_vm<(S - 2) * LPW>();
+  if (WAIT) wait_vm<(F::S - 2) * F::LPW>();
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_sched_barrier(0);
   // stage j + 1 is readable by all waves and slot j is free
-  r.cur = next_slot(r.cur);
-  const uint8_t *nb = lds + r.cur + wj * TJ * FRAG, *na = lds + r.cur + SIDE + wi * TI * FRAG;
+  r.cur = next_slot<F>(r.cur);
+  const uint8_t *nb = lds + r.cur + wj * TJ * FRAG, *na = lds + r.cur + F::SIDE + wi * TI * FRAG;
 #pragma unroll
   for (int tj = TJ - 2; tj < TJ; ++tj)
 #pragma unroll
     for (int ti = 0; ti < TI; ++ti) {
-      acc[tj][ti] = mma6(fb[tj], fa[ti], ZERO ? zero : acc[tj][ti]);
+      acc[tj][ti] = mma(fb[tj], fa[ti], ZERO ? zero : acc[tj][ti]);
       __builtin_amdgcn_sched_barrier(0);
       const int q = (tj - (TJ - 2)) * TI + ti;  // next: a0 b0 a1 a2 a3 b1 b2
-      if (q == 0) fan[0] = frag(na, lane);
-      if (q == 1) fb0[0] = frag(nb, lane);
-      if (q >= 2 && q <= 4) fan[q - 1] = frag(na + (q - 1) * FRAG, lane);
-      if (q == 5 || q == 6) fb0[q - 4] = frag(nb + (q - 4) * FRAG, lane);
+      if (q == 0) frag(fan[0], na, lane);
+      if (q == 1) frag(fb0[0], nb, lane);
+      if (q >= 2 && q <= 4) frag(fan[q - 1], na + (q - 1) * FRAG, lane);
+      if (q == 5 || q == 6) frag(fb0[q - 4], nb + (q - 4) * FRAG, lane);
       __builtin_amdgcn_sched_barrier(0);
     }
 }
@@ -237,24 +280,28 @@ __device__ __forceinline__ void fold(v4f (&acc)[TJ][TI], float q64, float inv64,
 // Where an item's tile is: a modulus, output tile and k range of a problem.
 struct Place {
   CProblem *P;
-  int l, part, tx, ty;
-  int k0, nk;  // first k, stages per pass
+  int l, part, tx, ty;  // tile numbers in units of the shape
+  int k0, nk;           // first k, stages per pass
 };
 
+template <class F>
 __device__ __forceinline__ Item make_item(const Place &c, CTables *tab) {
   const int64_t mp = c.P->g.mp, np = c.P->g.np, kp = c.P->g.kp;
   const int sl0 = tab->slice0[c.l];
-  const int second = tab->kfold[c.l][3], third = 3 - second;
   Item I;
-  I.sA = mp * kp / 4 * 3;
-  I.sB = np * kp / 4 * 3;
-  I.stA = mp * 96;
-  I.stB = np * 96;
-  I.A = c.P->w.Asl + sl0 * I.sA + c.k0 / kStage6 * I.stA + c.tx * (int64_t)SIDE;
-  I.B = c.P->w.Bsl + sl0 * I.sB + c.k0 / kStage6 * I.stB + c.ty * (int64_t)SIDE;
+  I.stA = mp / 16 * F::FRAG;
+  I.stB = np / 16 * F::FRAG;
+  I.sA = kp / F::BK * I.stA;
+  I.sB = kp / F::BK * I.stB;
+  I.A = c.P->w.Asl + sl0 * I.sA + c.k0 / F::BK * I.stA + c.tx * (int64_t)F::SIDE;
+  I.B = c.P->w.Bsl + sl0 * I.sB + c.k0 / F::BK * I.stB + c.ty * (int64_t)F::SIDE;
   I.nk = c.nk;
-  I.ab = tab->kind[c.l] == 0 ? ((1 << 2) | (1 << 4) | (1 << 8) | (1 << 10))
-                             : ((second << 4) | (second << 6) | (third << 8) | (third << 10));
+  I.ab = 0;
+  if constexpr (!F::I8) {
+    const int second = tab->kfold[c.l][3], third = 3 - second;
+    I.ab = tab->kind[c.l] == 0 ? ((1 << 2) | (1 << 4) | (1 << 8) | (1 << 10))
+                               : ((second << 4) | (second << 6) | (third << 8) | (third << 10));
+  }
   return I;
 }
 
@@ -265,6 +312,7 @@ __device__ __forceinline__ Item make_item(const Place &c, CTables *tab) {
 // the 48 of a 4 x 4 grid dealt out tile by tile (1024 x 1024 x 65536).
 constexpr uint32_t kBand = 4;
 
+template <class F>
 __device__ __forceinline__ Place place_single(CProblem *P, int it) {
   const uint32_t tx_n = (uint32_t)(P->g.mp / kGemmTIW), ty_n = (uint32_t)(P->g.np / kGemmTJ);
   const uint32_t N = (uint32_t)P->g.N, parts = (uint32_t)P->parts;
@@ -280,10 +328,11 @@ __device__ __forceinline__ Place place_single(CProblem *P, int it) {
   c.tx = uni32((int)x);
   c.ty = uni32((int)(kBand * band + (r - x * h)));
   c.k0 = uni32((int)k0 * kPad);
-  c.nk = uni32((int)(k1 - k0) * (kPad / kStage6));
+  c.nk = uni32((int)(k1 - k0) * (kPad / F::BK));
   return c;
 }
 
+template <class F>
 __device__ __forceinline__ Place place_list(const WorkList &W, int it) {
   OZ2_CONST ProductItem *I = (OZ2_CONST ProductItem *)(uintptr_t)W.items + it;
   Place c;
@@ -293,7 +342,7 @@ __device__ __forceinline__ Place place_list(const WorkList &W, int it) {
   c.tx = I->tx;
   c.ty = I->ty;
   c.k0 = I->k0;
-  c.nk = (I->k1 - I->k0) / kStage6;
+  c.nk = (I->k1 - I->k0) / F::BK;
   return c;
 }
 
@@ -306,9 +355,9 @@ __device__ __forceinline__ Place place_list(const WorkList &W, int it) {
 // go to the workgroups in rounds, a list's every second one backwards: sorted
 // longest first it comes out within 3 % of the average (48 problems log-uniform
 // in [64, 2048]), with no counter to fetch from.
-template <bool LIST>
+template <bool LIST, class F>
 __global__ __launch_bounds__(64 * NW, 1) void k_residue6(Problem, WorkList W, int count) {
-  __shared__ __attribute__((aligned(1024))) uint8_t lds[RING];
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[F::RING];
   // the problem by value is the first kernel argument
   CProblem *P1 = (CProblem *)__builtin_amdgcn_kernarg_segment_ptr();
   const int tid = threadIdx.x, lane = tid & 63;
@@ -330,16 +379,16 @@ __global__ __launch_bounds__(64 * NW, 1) void k_residue6(Problem, WorkList W, in
   const int first = item;
   auto place = [&](int it) {
     const int i = it < count ? it : first;  // past the end: loads that nothing reads
-    return LIST ? place_list(W, i) : place_single(P1, i);
+    return LIST ? place_list<F>(W, i) : place_single<F>(P1, i);
   };
   auto loads_of = [&](int it) {
     const Place c = place(it);
-    return make_item(c, (CTables *)(uintptr_t)c.P->tab);
+    return make_item<F>(c, (CTables *)(uintptr_t)c.P->tab);
   };
-  Lanes ln;
+  Lanes<F::LPW> ln;
   ln.ls = 1024u * wave;
 #pragma unroll
-  for (int u = 0; u < 3; ++u) ln.vo[u] = 1024u * (wave + NW * u) + 16u * lane;
+  for (int u = 0; u < F::LPW / 2; ++u) ln.vo[u] = 1024u * (wave + NW * u) + 16u * lane;
 
   Ring r;
   r.base = lds_offset(lds);
@@ -352,28 +401,30 @@ __global__ __launch_bounds__(64 * NW, 1) void k_residue6(Problem, WorkList W, in
   start_pass(p);
   // stages 0 .. S - 2
 #pragma unroll 1
-  for (int t = 0; t < S - 1; ++t) {
+  for (int t = 0; t < F::S - 1; ++t) {
     const uint32_t slot = r.base + r.fill;
-    load<0>(p, ln, slot);
-    load<1>(p, ln, slot);
-    load<2>(p, ln, slot);
-    load<3>(p, ln, slot);
-    load<4>(p, ln, slot);
-    load<5>(p, ln, slot);
-    advance(p);
-    r.fill = next_slot(r.fill);
+    load<F, 0>(p, ln, slot);
+    load<F, 1>(p, ln, slot);
+    load<F, 2>(p, ln, slot);
+    if constexpr (F::LPW > 3) load<F, 3>(p, ln, slot);
+    if constexpr (F::LPW > 4) {
+      load<F, 4>(p, ln, slot);
+      load<F, 5>(p, ln, slot);
+    }
+    advance<F::PASSES>(p);
+    r.fill = next_slot<F>(r.fill);
   }
   wait_vm<0>();
   __builtin_amdgcn_s_barrier();
-  v8i fa0[TI], fa1[TI], fb[3];
+  typename F::Frag fa0[TI], fa1[TI], fb[3];
 #pragma unroll
   for (int t = 0; t < TI; ++t) {
-    fa0[t] = frag(lds + SIDE + (wi * TI + t) * FRAG, lane);
+    frag(fa0[t], lds + F::SIDE + (wi * TI + t) * F::FRAG, lane);
     __builtin_amdgcn_sched_barrier(0);
   }
 #pragma unroll
   for (int t = 0; t < 3; ++t) {
-    fb[t] = frag(lds + (wj * TJ + t) * FRAG, lane);
+    frag(fb[t], lds + (wj * TJ + t) * F::FRAG, lane);
     __builtin_amdgcn_sched_barrier(0);
   }
 
@@ -386,68 +437,109 @@ __global__ __launch_bounds__(64 * NW, 1) void k_residue6(Problem, WorkList W, in
     // a scalar load still pending would turn every LDS wait of the loops into
     // a full drain (both count on LGKM, out of order): wait for them here
     asm volatile("" ::"s"(p.next.ab), "s"(p.next.A), "s"(p.next.B), "s"(p.next.nk));
-    constexpr int kMaxStages = kChunkK / kStage6;
-    v4f acc[TJ][TI];
+    constexpr int kMaxStages = kChunkK / F::BK;
+    typename F::Acc acc[TJ][TI];
     // the loop over the stages [j, n) of one chunk
     auto loop = [&](int j, int n) {
 #pragma unroll 1
       for (; j < n; j += 2) {
-        stage<false, true>(p, ln, r, lds, fa0, fa1, fb, acc, lane, wj, wi);
-        stage<false, true>(p, ln, r, lds, fa1, fa0, fb, acc, lane, wj, wi);
+        stage<false, true, F>(p, ln, r, lds, fa0, fa1, fb, acc, lane, wj, wi);
+        stage<false, true, F>(p, ln, r, lds, fa1, fa0, fb, acc, lane, wj, wi);
       }
     };
-    // one pass (from stage j0 of it) and the fold that ends it: m (acc mods q)
-    // after the last chunk (m = 0: none), acc mods p after the others
-    auto pass = [&](int j0, float q, float iq, float m, float pf, float inv) {
-      int left = c.nk;
-      for (;;) {
-        const int n = LIST && left > kMaxStages ? kMaxStages : left;
-        loop(j0, n);
-        left -= n;
-        const bool last = !LIST || left == 0;
-        if (!last || m != 0.0f)
-          fold(acc, (last ? q : pf) * 0.015625f, (last ? iq : inv) * 64.0f, last ? m : 1.0f);
-        if (last) break;
-        j0 = 0;
-      }
-    };
-    const bool square = tab->kind[l] == 0;
+    // stages 0 .. S - 2 had landed before the previous item's stores
+    stage<true, false, F>(p, ln, r, lds, fa0, fa1, fb, acc, lane, wj, wi);
+    stage<false, F::S == 3, F>(p, ln, r, lds, fa1, fa0, fb, acc, lane, wj, wi);
     const float pf = (float)tab->p[l], inv = tab->inv_p[l];
-    // every load of stage 1 had landed before the previous item's stores
-    stage<true, false>(p, ln, r, lds, fa0, fa1, fb, acc, lane, wj, wi);
-    stage<false, true>(p, ln, r, lds, fa1, fa0, fb, acc, lane, wj, wi);
-    pass(2, pf, inv, square ? 0.0f : (float)tab->kfold[l][0], pf, inv);
-    const float q2 = square ? (float)tab->s[l] : pf, iq2 = square ? tab->inv_s[l] : inv;
-    pass(0, q2, iq2, square ? q2 : (float)tab->kfold[l][1], pf, inv);
-    pass(0, pf, inv, 0.0f, pf, inv);
-    // symmetric residue, four consecutive rows i per lane: a first reduction to
-    // |r| <= p / 2 + 2, the multiplier, and a second one whose quotient is
-    // nudged by 1 / (4 p), so that an exact half (even p) goes to -p / 2 and no
-    // other value (at least 1 / (2 p) from a half) moves
     const int64_t mp = c.P->g.mp, np = c.P->g.np;
-    const float m3 = 64.0f * (square ? 1.0f : (float)tab->kfold[l][2]);
-    const float inv64 = inv * 64.0f, q64 = pf * 0.015625f, bias = 0.25f * inv;
     int16_t *out = c.P->w.planes + ((int64_t)c.part * c.P->g.N + l) * mp * np +
                    ((int64_t)c.ty * kGemmTJ + wj * 128 + (lane >> 4) * 16) * mp +
                    (int64_t)c.tx * kGemmTIW + wi * 64 + 4 * (lane & 15);
+    // four consecutive rows i of a column
+    auto store = [&](int tj, int v, const int (&res)[TI]) {
+      int16_t *dst = out + ((tj >> 2) * 64 + 4 * v + (tj & 3)) * mp;
+      // the next item's first stages (their loads count with the stores)
+      if (tj == 0 && v == 0) wait_vm<0>();
+      *(uint2 *)dst = make_uint2(((uint32_t)res[0] & 0xFFFFu) | ((uint32_t)res[1] << 16),
+                                 ((uint32_t)res[2] & 0xFFFFu) | ((uint32_t)res[3] << 16));
+    };
+    if constexpr (F::I8) {
+      // one product; the symmetric residue of an INT32 sum in FP64, where the
+      // quotient is exact to 2^-28: one step, nudged like the last one below
+      const double pd = (double)tab->p[l], invd = tab->inv_pd[l], nudge = 0.25 * invd;
+      int left = c.nk, j0 = 2;
+      if (LIST)
+        for (; left > kMaxStages; left -= kMaxStages, j0 = 0) {
+          loop(j0, kMaxStages);
 #pragma unroll
-    for (int tj = 0; tj < TJ; ++tj) {
+          for (int tj = 0; tj < TJ; ++tj) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        int res[TI];
+            for (int ti = 0; ti < TI; ++ti)
 #pragma unroll
-        for (int ti = 0; ti < TI; ++ti) {
-          const float x = acc[tj][ti][v];
-          const float y = fmaf(-rintf(x * inv64), q64, x) * m3;
-          res[ti] = (int)fmaf(-rintf(fmaf(y, inv, bias)), pf, y);
+              for (int v = 0; v < 4; ++v) {
+                const double x = (double)acc[tj][ti][v];
+                acc[tj][ti][v] = (int)fma(-rint(x * invd), pd, x);
+              }
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
-        const uint2 w = make_uint2(((uint32_t)res[0] & 0xFFFFu) | ((uint32_t)res[1] << 16),
-                                   ((uint32_t)res[2] & 0xFFFFu) | ((uint32_t)res[3] << 16));
-        // the next item's first two stages (their loads count with the stores)
-        if (tj == 0 && v == 0) wait_vm<0>();
-        *(uint2 *)(out + ((tj >> 2) * 64 + 4 * v + (tj & 3)) * mp) = w;
+      loop(j0, left);
+#pragma unroll
+      for (int tj = 0; tj < TJ; ++tj) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          int res[TI];
+#pragma unroll
+          for (int ti = 0; ti < TI; ++ti) {
+            const double x = (double)acc[tj][ti][v];
+            res[ti] = (int)fma(-rint(fma(x, invd, nudge)), pd, x);
+          }
+          store(tj, v, res);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
-      __builtin_amdgcn_sched_barrier(0);
+    } else {
+      // one pass (from stage j0 of it) and the fold that ends it: m (acc mods q)
+      // after the last chunk (m = 0: none), acc mods p after the others
+      auto pass = [&](int j0, float q, float iq, float m, float pf, float inv) {
+        int left = c.nk;
+        for (;;) {
+          const int n = LIST && left > kMaxStages ? kMaxStages : left;
+          loop(j0, n);
+          left -= n;
+          const bool last = !LIST || left == 0;
+          if (!last || m != 0.0f)
+            fold(acc, (last ? q : pf) * 0.015625f, (last ? iq : inv) * 64.0f, last ? m : 1.0f);
+          if (last) break;
+          j0 = 0;
+        }
+      };
+      const bool square = tab->kind[l] == 0;
+      pass(2, pf, inv, square ? 0.0f : (float)tab->kfold[l][0], pf, inv);
+      const float q2 = square ? (float)tab->s[l] : pf, iq2 = square ? tab->inv_s[l] : inv;
+      pass(0, q2, iq2, square ? q2 : (float)tab->kfold[l][1], pf, inv);
+      pass(0, pf, inv, 0.0f, pf, inv);
+      // symmetric residue, four consecutive rows i per lane: a first reduction to
+      // |r| <= p / 2 + 2, the multiplier, and a second one whose quotient is
+      // nudged by 1 / (4 p), so that an exact half (even p) goes to -p / 2 and no
+      // other value (at least 1 / (2 p) from a half) moves
+      const float m3 = 64.0f * (square ? 1.0f : (float)tab->kfold[l][2]);
+      const float inv64 = inv * 64.0f, q64 = pf * 0.015625f, bias = 0.25f * inv;
+  #pragma unroll
+      for (int tj = 0; tj < TJ; ++tj) {
+  #pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          int res[TI];
+  #pragma unroll
+          for (int ti = 0; ti < TI; ++ti) {
+            const float x = acc[tj][ti][v];
+            const float y = fmaf(-rintf(x * inv64), q64, x) * m3;
+            res[ti] = (int)fmaf(-rintf(fmaf(y, inv, bias)), pf, y);
+          }
+          store(tj, v, res);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
   }
   wait_vm<0>();
@@ -465,17 +557,23 @@ hipError_t launch_gemm6(const Problem &P, hipStream_t st) {
   const int64_t count = family_blocks(kFamGemm6, P);
   if (count <= 0) return hipSuccess;
   if (count > 0x7FFFFFFFll - 2 * kCUs) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_residue6<false>), dim3((unsigned)grid_for(count, kCUs)), dim3(64 * NW), 0,
-                     st, P, WorkList{}, (int)count);
+  const dim3 gr((unsigned)grid_for(count, kCUs)), blk(64 * NW);
+  if (P.g.list == OZ2_MODULI_INT8)
+    hipLaunchKernelGGL((k_residue6<false, Int8>), gr, blk, 0, st, P, WorkList{}, (int)count);
+  else
+    hipLaunchKernelGGL((k_residue6<false, E2M3>), gr, blk, 0, st, P, WorkList{}, (int)count);
   return hipGetLastError();
 }
 
-hipError_t launch_gemm6_list(const WorkList &W, int64_t cus, hipStream_t st) {
+hipError_t launch_gemm6_list(bool int8, const WorkList &W, int64_t cus, hipStream_t st) {
   if (cus <= 0 || W.count > 0x7FFFFFFFll - 2 * cus) return hipErrorInvalidValue;
   Problem none;
   memset(&none, 0, sizeof(none));
-  hipLaunchKernelGGL((k_residue6<true>), dim3((unsigned)grid_for(W.count, cus)), dim3(64 * NW), 0,
-                     st, none, W, (int)W.count);
+  const dim3 gr((unsigned)grid_for(W.count, cus)), blk(64 * NW);
+  if (int8)
+    hipLaunchKernelGGL((k_residue6<true, Int8>), gr, blk, 0, st, none, W, (int)W.count);
+  else
+    hipLaunchKernelGGL((k_residue6<true, E2M3>), gr, blk, 0, st, none, W, (int)W.count);
   return hipGetLastError();
 }
 

@@ -80,8 +80,8 @@ struct Geometry {
   int nsq;                    // square moduli (the first nsq of the list)
   int nka;                    // Karatsuba moduli (the next nka); the rest are INT8
   int list;                   // OZ2_MODULI_HYBRID, _KARATSUBA or _INT8
-  int fp6;                    // the digit slices hold E2M3 digits in the fragment order of
-                              // oz2_gemm6.hip (else E4M3 digits or INT8 residues, k-blocked)
+  int fp6;                    // the digit slices are in the fragment order of oz2_gemm6.hip, FP8
+                              // lists' as E2M3 codes (else k-blocked, E4M3 codes)
 };
 
 // Workspace views of one call.
@@ -147,14 +147,11 @@ struct ProductItem {
   int32_t k0, k1;
 };
 
-// Work list of a persistent residue-product launch.  For the INT8 arm,
-// counters[0] hands out items, counters[1] counts finished workgroups; both are zero between
-// launches (the last workgroup to finish clears them).
+// Work list of a persistent residue-product launch.
 struct WorkList {
   const Problem *probs;
   const ProductItem *items;
   int64_t count;
-  uint32_t *counters;
 };
 
 // Layout of the FP8 bound operands and of every digit slice ("k-blocked"):
@@ -171,6 +168,7 @@ constexpr int kGemmTJ = 256;  // output columns j per tile
 constexpr int kGemmTIW = 256; // output rows i per tile of the single-product kernels
                               // (Karatsuba products, bound product)
 constexpr int kGemmBK = 64;   // k per pipeline stage
+constexpr int kStage8 = 64;   // the same of the INT8 products in fragment order
 constexpr int kStage6 = 128;  // k per pipeline stage of the E2M3 products (one MFMA step)
 constexpr int kQL = 16;       // quantization passes: 16 lines x 128 k per block
 constexpr int kQK = 128;
@@ -187,10 +185,10 @@ enum Family : int {
   kFamDecide,     // scale exponents from the FP8 bound
   kFamFixup,      // exact bound product for undecided lines
   kFamRes,        // residues and FP8 digits (or INT8 residues) of Problem::res_sides
-  kFamRes6,       // residues and E2M3 digits of Problem::res_sides
+  kFamRes6,       // the same in fragment order (E2M3 digits or INT8 residues)
   kFamGemm8,      // residue products on E4M3 digits, every FP8 modulus and k part
   kFamGemmI8,     // residue products, INT8 moduli
-  kFamGemm6,      // residue products on E2M3 digits, every FP8 modulus
+  kFamGemm6,      // residue products on digits in fragment order, every modulus
   kFamCrt,        // CRT, inverse scaling, alpha / beta
   kNumFamilies
 };
@@ -385,17 +383,16 @@ __device__ __forceinline__ Dims decode_block(const Dims &d, int64_t local) {
 hipError_t launch_quant_family(int fam, const Problem *P, const Group *G, hipStream_t st);
 hipError_t launch_scale_family(int fam, const Problem *P, const Group *G, hipStream_t st);
 hipError_t launch_gemm_family(int fam, const Problem *P, const Group *G, hipStream_t st);
-// The persistent residue-product launch: `grid` workgroups take the items of W
-// until none is left; int8 selects the INT8 arm's products (every item's
-// modulus is then an INT8 one, the tiles run nw = 8 or 4 waves), else every
-// item's modulus is a square or Karatsuba FP8 modulus with E2M3 digits.
+// The residue products of a batch on at most `grid` persistent workgroups of nw
+// = 8 waves: int8 selects the INT8 arm's products (every item's modulus is then
+// an INT8 one), else every item's modulus is a square or Karatsuba FP8 modulus
+// with E2M3 digits.
 hipError_t launch_gemm_persistent(int nw, bool int8, const WorkList &W, int64_t grid,
                                   hipStream_t st);
-// The residue products on E2M3 digits of a single problem (kFamGemm6 of
-// launch_gemm_family).
+// The residue products on digits in fragment order of a single problem
+// (kFamGemm6 of launch_gemm_family), and over a work list.
 hipError_t launch_gemm6(const Problem &P, hipStream_t st);
-// The same over a work list (every item's modulus an FP8 one).
-hipError_t launch_gemm6_list(const WorkList &W, int64_t grid, hipStream_t st);
+hipError_t launch_gemm6_list(bool int8, const WorkList &W, int64_t grid, hipStream_t st);
 // limbs: crt_shape of the tables.
 hipError_t launch_crt_family(const Problem *P, const Group *G, int limbs, int N, hipStream_t st);
 // Device memory of the entry point that allocates nothing: a workspace and

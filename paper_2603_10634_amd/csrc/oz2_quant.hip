@@ -525,25 +525,22 @@ __device__ __forceinline__ void residues_tile(const Operand &op, int64_t kp, int
     residue_moduli<false>(in, tab, range, base, slice_stride);
 }
 
-template <bool GROUPED>
-__global__ __launch_bounds__(256) void k_residues(Problem P1, Group G) {
+// (single problems only: a batch's slices are in fragment order)
+__global__ __launch_bounds__(256) void k_residues(Problem P) {
   __shared__ double tile[kQL * kRowLd];
-  int64_t local;
-  const Problem &P = *locate<GROUPED>(P1, G, blockIdx.x, local);
-  const Dims d = family_dims(kFamRes, P), c = decode_block(d, local);
+  const Dims d = family_dims(kFamRes, P), c = decode_block(d, blockIdx.x);
   const int64_t r0 = c.x * kQL, by = c.y;
   const int64_t first = P.res_sides & 1 ? P.g.mp : 0;
   const bool side = r0 >= first;
   residues_tile(operand(P, side), P.g.kp, side ? P.g.np : P.g.mp, side ? r0 - first : r0,
-                by * kQK, P.w, side ? P.w.lineB : 0, tables_of<GROUPED>(P1, G),
-                moduli_range(P.g, c.z, d.z), side ? P.w.Bsl : P.w.Asl, tile);
+                by * kQK, P.w, side ? P.w.lineB : 0, P.tab, moduli_range(P.g, c.z, d.z),
+                side ? P.w.Bsl : P.w.Asl, tile);
 }
 
-// ---- E2M3 digits ----
+// ---- slices in fragment order ----
 //
-// The digits of the products on E2M3 (k_residue6, oz2_gemm6.hip), in its
-// fragment order: the code of d / 8 is the sign and |d| as a 5-bit integer,
-// for |d| <= 16.
+// The slices of k_residue6 (oz2_gemm6.hip).  E2M3 digits: the code of d / 8 is
+// the sign and |d| as a 5-bit integer, for |d| <= 16.  INT8 residues: bytes.
 //
 // A thread owns one line and 32 consecutive k, i.e. one lane's 24 bytes of
 // every slice, a wave 64 lines, a workgroup 64 lines x 128 k (a whole group of
@@ -630,6 +627,30 @@ __device__ __forceinline__ void digits6(const float (&f)[kR6E], CTables *tab, in
   if (KIND == 1) store6(d3, dst + 2 * slice_stride, off16, off8);
 }
 
+// The residue of one INT8 modulus as the low bytes of its integers (an even p's
+// half may be +p / 2: for p = 256 the byte of -128), 32 bytes of the line in two
+// lanes' pieces of a 64-k stage.
+__device__ __forceinline__ void digits8(const float (&f)[kR6E], CTables *tab, int l, uint8_t *base,
+                                        int64_t slice_stride, uint32_t off) {
+  const float pf = (float)tab->p[l], invpf = tab->inv_p[l];
+  uint32_t w[kR6E / 4];
+#pragma unroll
+  for (int g = 0; g < kR6E / 4; ++g) {
+    uint32_t b[4];
+#pragma unroll
+    for (int z = 0; z < 4; ++z) {
+      const float u = fmaf(-rintf(f[4 * g + z] * invpf), pf, f[4 * g + z]);
+      b[z] = __float_as_uint(u + 0x1.8p23f);  // the integer in the low bits
+    }
+    const uint32_t lo = __builtin_amdgcn_perm(b[1], b[0], 0x0C0C0400u);
+    const uint32_t hi = __builtin_amdgcn_perm(b[3], b[2], 0x04000C0Cu);
+    w[g] = lo | hi;
+  }
+  uint8_t *dst = base + (int64_t)tab->slice0[l] * slice_stride + off;
+  *(uint4 *)dst = make_uint4(w[0], w[1], w[2], w[3]);
+  *(uint4 *)(dst + 256) = make_uint4(w[4], w[5], w[6], w[7]);
+}
+
 // x - R rint(x / R) for an integer x: with q the computed quotient (within
 // 2^-52 of x / R, relatively) it is a multiple of ulp(q) or 1 below
 // 2^-51 |x| + R / 2, i.e. of fewer than 53 bits (R < 2^21), so the fused
@@ -654,8 +675,13 @@ __device__ __forceinline__ void kind6(const double (&x)[kR6E], CTables *tab, int
       for (int s = 1; s < STEPS; ++s) y = mod_step(y, R, invR);
       f[q] = (float)y;
     }
-    digits6<KIND>(f, tab, l, base, slice_stride, off16, off8);
-    if (two) digits6<KIND>(f, tab, l + 1, base, slice_stride, off16, off8);
+    if constexpr (KIND == 2) {
+      digits8(f, tab, l, base, slice_stride, off16);
+      if (two) digits8(f, tab, l + 1, base, slice_stride, off16);
+    } else {
+      digits6<KIND>(f, tab, l, base, slice_stride, off16, off8);
+      if (two) digits6<KIND>(f, tab, l + 1, base, slice_stride, off16, off8);
+    }
   }
 }
 
@@ -665,6 +691,7 @@ __device__ __forceinline__ void moduli6(const double (&x)[kR6E], CTables *tab,
                                         uint32_t off8) {
   kind6<0, STEPS>(x, tab, m.l0, m.a, base, slice_stride, off16, off8);
   kind6<1, STEPS>(x, tab, m.a, m.b, base, slice_stride, off16, off8);
+  kind6<2, STEPS>(x, tab, m.b, m.l1, base, slice_stride, off16, off8);
 }
 
 template <bool GROUPED>
@@ -718,10 +745,15 @@ __global__ __launch_bounds__(256, 2) void k_residues6(Problem P1, Group G) {
   const int s = final_shift(P.w, base_line, r, tab->D, h0 == 0 && c.z == 0, &e);
 #pragma unroll
   for (int q = 0; q < kR6E; ++q) x[q] = trunc(ldexp(x[q], s));
-  const int64_t slice_stride = R * kp / 4 * 3;
-  const uint32_t off16 = (uint32_t)((lane & 3) * 1536 + 16 * ((lane >> 2) + 16 * wave));
-  const uint32_t off8 = (uint32_t)((lane & 3) * 1536 + 1024 + 8 * ((lane >> 2) + 16 * wave));
-  uint8_t *base = (side ? P.w.Bsl : P.w.Asl) + by * (R * 96) + bx * 6144;
+  // INT8: stages of 64 k, 4096 bytes per 64 lines, 16-byte pieces of 16 k; E2M3:
+  // stages of 128 k, 6144 bytes per 64 lines
+  const bool int8 = P.g.list == OZ2_MODULI_INT8;
+  const int64_t slice_stride = int8 ? R * kp : R * kp / 4 * 3;
+  const uint32_t kg = int8 ? 2 * (wave & 1) : wave, fragment = (lane & 3) * (int8 ? 1024u : 1536u);
+  const uint32_t off16 = fragment + 16 * ((lane >> 2) + 16 * kg);
+  const uint32_t off8 = fragment + 1024 + 8 * ((lane >> 2) + 16 * kg);
+  uint8_t *base = (side ? P.w.Bsl : P.w.Asl) +
+                  (int8 ? (h0 >> 6) * (R * 64) + bx * 4096 : by * (R * 96) + bx * 6144);
   const ModuliRange m = moduli_range(P.g, c.z, d.z);
   // |x| < 2^(e + 8): a step leaves |f| < R / 2 + 2^12 from below 2^63, two from
   // below 2^113; the scale exponent stays below 160, so four always do
@@ -759,7 +791,10 @@ hipError_t launch_quant_family(int fam, const Problem *P, const Group *G, hipStr
     case kFamLmax: OZ2_Q(k_line_max) break;
     case kFamBar: OZ2_Q(k_bound_operand) break;
     case kFamNorm: OZ2_Q(k_bound_norm) break;
-    case kFamRes: OZ2_Q(k_residues) break;
+    case kFamRes:
+      if (grouped) return hipErrorInvalidValue;
+      hipLaunchKernelGGL(k_residues, grid, blk, 0, st, p1);
+      break;
     case kFamRes6: OZ2_Q(k_residues6) break;
     default: return hipErrorInvalidValue;
   }

@@ -122,3 +122,17 @@ def test_folds_and_symmetric_residue(p, kind, s):
     t = np.rint((y.astype(np.float64) * np.float64(inv) + np.float64(bias)).astype(np.float32))
     z = y.astype(np.float64) - t.astype(np.float64) * p
     assert np.array_equal(z.astype(np.int64), _sym(x * last, p))
+
+
+def test_int8_fp64_residues():
+    # the products' epilogue: one FP64 step on an INT32 sum, the quotient nudged
+    # by 1 / (4 p) so that an even p's half goes to -p / 2
+    rng = np.random.default_rng(8)
+    top = 2 ** 29 + 2 ** 22
+    for p, _, _ in ref.moduli_table(33, "int8"):
+        inv = 1.0 / float(p)
+        x = np.concatenate([rng.integers(-top, top, 300), np.arange(-2 * p, 2 * p + 1),
+                            [-top, top], p * rng.integers(0, top // p, 50) + p // 2])
+        for v in x.tolist():
+            q = np.rint(_fma(float(v), inv, 0.25 * inv))
+            assert _fma(-q, float(p), float(v)) == _sym(v, p), (p, v)

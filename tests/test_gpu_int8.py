@@ -144,6 +144,65 @@ def test_int8_batched_list_switch():
         assert _same(Ch[q], ref.emulate(As[q], Bs[q], 14)), q
 
 
+def _fragments(r, which):
+    """N x lines x k residues decoded from the documented fragment order."""
+    mp, np_, kp, M = (r.pads[q] for q in ("mp", "np", "kp", "M"))
+    R = mp if which == "A" else np_
+    o = r.off[5 if which == "A" else 6]
+    h = np.arange(kp)
+    i = np.arange(R)[:, None]
+    at = (((h // 64) * (R // 64) + i // 64) * 4 + i % 4) * 1024 \
+        + 16 * ((i % 64) // 4 + 16 * ((h % 64) // 16)) + h % 16
+    return np.stack([r.ws[o + q * R * kp:o + (q + 1) * R * kp].view(np.int8)[at]
+                     for q in range(M)])
+
+
+@pytest.mark.parametrize("m,n,k,N,ta,tb,mode,phi", [
+    (513, 700, 1, 1, "N", "T", "fast", 1.0),
+    (1280, 64, 257, 5, "T", "N", "accurate", 1.0),
+    (700, 600, 130, 14, "N", "N", "accurate", 0.5),
+    (600, 520, 65, 33, "T", "T", "accurate", 6.0),   # the largest exponents
+])
+def test_int8_stages_in_fragments(m, n, k, N, ta, tb, mode, phi):
+    print(f"int8 fragments {m}x{n}x{k} N={N} {ta}{tb} {mode}", flush=True)
+    A, B = _inputs(m, n, k, phi, 7300 + m)
+    r = run(A, B, N, ta, tb, keep_ws=True, mode=mode, moduli=I8, pad=(1, 3, 2))
+    assert r.status == 0
+    Chat, st = ref.emulate(A, B, N, keep_stages=True, mode=mode, moduli_set=I8)
+    ps = [pm["p"] for pm in st["per_modulus"]]
+    P = r.planes(N, ps)
+    for which, lines in (("A", m), ("B", n)):
+        d = _fragments(r, which).astype(np.int64)
+        assert not d[:, lines:].any() and not d[:, :, k:].any(), "padding"
+        for l, pm in enumerate(st["per_modulus"]):
+            want = pm["uA"] if which == "A" else pm["uB"].T
+            assert not np.any((d[l, :lines, :k] - want.astype(np.int64)) % ps[l]), (which, l)
+    for l, plane in enumerate(st["planes"]):
+        assert np.array_equal(P[l, :n, :m].T, plane), f"plane {l}"
+    assert _same(r.C, Chat)
+
+
+@pytest.mark.parametrize("k", [32768, 65536 + 256])
+def test_int8_extreme_sums_in_fragments(k):
+    # sums of 2^29 modulo 256, in one part of a single problem (six tiles) and
+    # over the chunks of an item of a batch
+    a = _constant_case(k)
+    C1 = ref.emulate(np.full((1, k), a), np.full((k, 1), a), 14, moduli_set=I8)[0, 0]
+    print(f"int8 extreme residues in fragments a={a} k={k}", flush=True)
+    A, B = np.full((520, k), a), np.full((k, 260), a)
+    A[1::2] *= -1.0
+    want = np.where(np.arange(520)[:, None] % 2, -C1, C1) * np.ones((1, 260))
+    with split(1):
+        r = run(A, B, 14, moduli=I8)
+    assert r.status == 0 and _same(r.C, want)
+    assert oz.ozaki2_set_schedule(0) == 0    # one k part
+    try:
+        C = _batched([A, A[:3]], [B, B[:, :5]], 14, I8)
+    finally:
+        oz.ozaki2_set_schedule(-1)
+    assert _same(C[0], want) and _same(C[1], want[:3, :5])
+
+
 def test_int8_full_size_sampled():
     # m = n = k = 8192, phi = 0.5, 14 moduli (int8): shifts of sampled lines,
     # sampled outputs bit for bit, normalised error against double-double
