@@ -27,7 +27,7 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-ffp-contract
           "-Wall", "-Wno-unused-function", "-Wno-unused-variable"]
 
 SOURCES = ["oz2_tables.cpp", "oz2_api.cpp", "oz2_noalloc.cpp", "oz2_quant.hip",
-           "oz2_scale.hip", "oz2_gemm.hip", "oz2_gemm6.hip", "oz2_crt.hip"]
+           "oz2_scale.hip", "oz2_gemm.hip", "oz2_gemm6.hip", "oz2_small.hip", "oz2_crt.hip"]
 
 
 def _compile(src: str) -> str:

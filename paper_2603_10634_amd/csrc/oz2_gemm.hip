@@ -864,6 +864,8 @@ hipError_t launch_gemm_family(int fam, const Problem *P, const Group *G, hipStre
   const bool grouped = G != nullptr;
   if (grouped && fam != kFamBgemm) return hipErrorInvalidValue;
   if (fam == kFamGemm6) return launch_gemm6(*P, st);
+  if (!grouped)
+    if (const int w = small_width(fam, *P)) return launch_small(fam, *P, w, st);
   Problem p1;
   Group g1;
   memset(&p1, 0, sizeof(p1));

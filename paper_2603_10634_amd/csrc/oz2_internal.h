@@ -393,6 +393,10 @@ hipError_t launch_gemm_persistent(int nw, bool int8, const WorkList &W, int64_t 
 // (kFamGemm6 of launch_gemm_family), and over a work list.
 hipError_t launch_gemm6(const Problem &P, hipStream_t st);
 hipError_t launch_gemm6_list(bool int8, const WorkList &W, int64_t grid, hipStream_t st);
+// The products of a single problem's kFamBgemm, kFamGemm8 or kFamGemmI8 with few
+// output tiles, and the tile width they run with (0: they run in 256 x 256 tiles).
+int small_width(int fam, const Problem &P);
+hipError_t launch_small(int fam, const Problem &P, int w, hipStream_t st);
 // limbs: crt_shape of the tables.
 hipError_t launch_crt_family(const Problem *P, const Group *G, int limbs, int N, hipStream_t st);
 // Device memory of the entry point that allocates nothing: a workspace and
