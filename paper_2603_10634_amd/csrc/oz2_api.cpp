@@ -385,8 +385,12 @@ int enqueue_scaling(const Problem &P, hipStream_t st, Marks &mark) {
   const bool fast = P.mode == OZ2_MODE_FAST;
   mark();
   // step 1: mu', nu' and the FP8 bound operands (fast mode: their line norms)
-  for (int f : {kFamFill, kFamLmax, fast ? kFamNorm : kFamBar})
-    OZ2_TRY(launch_quant_family(f, &P, nullptr, st));
+  if (whole_lines(P.g.mp + P.g.np, P.g.k)) {
+    OZ2_TRY(launch_quant_family(kFamLines, &P, nullptr, st));
+  } else {
+    for (int f : {kFamFill, kFamLmax, fast ? kFamNorm : kFamBar})
+      OZ2_TRY(launch_quant_family(f, &P, nullptr, st));
+  }
   mark();
   // step 2: the FP8 bound product (its line maxima only; none in fast mode)
   if (!fast) {
@@ -780,12 +784,22 @@ void build_subbatch(const std::vector<Problem> &probs, ImageWriter &W, SubBatch 
     sb->launches.push_back(L);
   };
   // every problem of a batch has the calling thread's mode
-  if (probs[0].mode == OZ2_MODE_FAST) {
-    for (int f : {kFamFill, kFamLmax, kFamNorm, kFamRes6}) add(f, at_probs, -1);
-  } else {
-    for (int f : {kFamFill, kFamLmax, kFamBar, kFamBgemm, kFamDecide, kFamFixup, kFamRes6})
-      add(f, at_probs, -1);
+  const bool fast = probs[0].mode == OZ2_MODE_FAST;
+  int64_t max_k = 0, lines = 0;
+  for (const Problem &P : probs) {
+    max_k = std::max(max_k, P.g.k);
+    lines += P.g.mp + P.g.np;
   }
+  if (whole_lines(lines, max_k)) {
+    add(kFamLines, at_probs, -1);
+    sb->launches.back().G.max_k = max_k;
+    sb->launches.back().G.norm = fast;
+  } else {
+    for (int f : {kFamFill, kFamLmax, fast ? kFamNorm : kFamBar}) add(f, at_probs, -1);
+  }
+  if (!fast)
+    for (int f : {kFamBgemm, kFamDecide, kFamFixup}) add(f, at_probs, -1);
+  add(kFamRes6, at_probs, -1);
   for (int c = 0; c < kDistinctConfigs; ++c) {
     std::vector<Problem> pc(probs);
     std::vector<ProductItem> items;

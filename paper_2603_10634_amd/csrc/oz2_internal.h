@@ -177,6 +177,7 @@ constexpr int kQK = 128;
 // covers one problem or a whole group of problems (a batch).
 enum Family : int {
   kFamFill = 0,   // zero the per-line accumulators
+  kFamLines,      // line maxima and the bound operands (fast mode: norms), whole lines
   kFamLmax,       // line maxima of op(A), then of op(B)
   kFamBar,        // FP8 bound operands of both
   kFamNorm,       // fast mode: squared norms of the bound operands' lines
@@ -256,6 +257,8 @@ __host__ __device__ inline Dims family_dims(int fam, const Problem &P) {
       const LmaxShape a = lmax_shape(P.A), b = lmax_shape(P.B);
       return {a.gx * a.splits + b.gx * b.splits, 1, 1};
     }
+    case kFamLines:
+      return {(g.mp + g.np) / kQL, 1, 1};
     case kFamBar:
     case kFamNorm:
       return {(g.mp + g.np) / kQL, g.kp / kQK, 1};
@@ -288,6 +291,16 @@ __host__ __device__ inline Dims family_dims(int fam, const Problem &P) {
   }
 }
 
+// Whether kFamLines takes the place of kFamFill, kFamLmax and kFamBar (or
+// kFamNorm) for `lines` padded lines in all, of at most k.  It reads the inputs
+// once but a line's tiles in turn: 512 lines of k = 1024 11.9 against 16.7 us,
+// 2048 18.5 against 17.6; 2048 lines of k = 4096 36.9 against 38.6, 8192 66.0
+// against 66.2; 4096 lines of k = 8192 82 against 130.  Its tiles are held in
+// registers: 8192 k.
+inline bool whole_lines(int64_t lines, int64_t k) {
+  return k <= 1024 || (k <= 8192 && lines >= 2048);
+}
+
 // k range [*k0, *k1) of part `part` of `parts` of the residue products: the
 // kp / kPad blocks of 256 k dealt out as evenly as possible (no part is empty
 // when parts <= kp / kPad).
@@ -315,6 +328,8 @@ struct Group {
                         // through this kernel argument, they load with scalar loads
   int nseg;
   int64_t total;
+  int64_t max_k;        // largest k and whether in fast mode, of a kFamLines launch
+  bool norm;
 };
 
 // The device tables of the problem a block works on (see Group::tab).

@@ -281,6 +281,215 @@ __global__ __launch_bounds__(256) void k_bound_norm(Problem P1, Group G) {
                   P.w.flags + base, P.w.rfix + base, tile);
 }
 
+// ---- maxima and bound operands in one pass ----
+//
+// A workgroup of two groups of 256 threads holds 16 whole lines, a group every
+// second tile of 128 k, so that the inputs are read once and nothing has to be
+// cleared beforehand.  What the bound operand needs of a value until its line's
+// maximum is known are 16 bits: exponent and three mantissa bits, with one bit
+// for whether anything follows (rounding up asks no more).  The 8 values of a
+// thread and tile are 4 registers, T tiles per group.  A subnormal value keeps
+// fewer mantissa bits than that: scaled, it is below 2^-9 and rounds up to it
+// whatever its bits while the line's maximum is at least 2^kDeep; workgroups
+// with a smaller maximum read their lines again.
+//
+// Bound by memory, and by the latency of its T loads in turn where there are few
+// lines.  Both operands, against clearing, maxima and bound operand in three
+// launches: 8192^3 480 -> 333 us (3.6 TB/s), 4096^3 136 -> 88, 16384 x 16384 x
+// 1024 130 -> 72, 3000 x 2000 x 256 17.7 -> 9.4, 256^3 14.4 -> 7.2.  Four groups
+// (one workgroup per CU) reach 370 us at 8192^3.
+constexpr int kLinesG = 2;  // groups of 256 threads
+constexpr int kDeep = -1006;
+
+// Exponent, three mantissa bits and the bit for the rest (of a non-finite value
+// 0x7FF0 or more).
+__device__ __forceinline__ uint32_t line_code(double v) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const uint32_t hi = (uint32_t)(b >> 32);
+  return (hi >> 16 & 0x7FFFu) | (((hi << 16) | (uint32_t)b) != 0 ? 1u : 0u);
+}
+
+// e4m3_round_up of a value given by its code, 8 sh = 8 (sh7 - 1023) + 56: above
+// 2^-6 the code rounded up to three mantissa bits and rebased, below that
+// ceil((1 + m / 16) 2^fl 2^9) with s = -(fl + 5) bits dropped from 16 + m.
+__device__ __forceinline__ uint32_t round_up_code(uint32_t c, int rebase) {
+  const int normal = (int)((c + 1) >> 1) + rebase;
+  const int fl = (int)(c >> 4) + ((rebase - 56) >> 3);
+  int s = -5 - fl;
+  s = s < 0 ? 0 : s > 8 ? 8 : s;
+  const int small = (int)((16u + (c & 15u) + (1u << s) - 1u) >> s);
+  const int code = normal < 8 ? small : normal;
+  return c ? (uint32_t)code : 0u;
+}
+
+template <bool GROUPED, bool NORM, int T>
+__global__ __launch_bounds__(256 * kLinesG, T <= 16 ? 4 : 2) void k_lines(Problem P1, Group G) {
+  __shared__ double tiles[kLinesG][kQL * kRowLd];
+  __shared__ uint64_t red[kLinesG][kQL];
+  int64_t local;
+  const Problem &P = *locate<GROUPED>(P1, G, blockIdx.x, local);
+  const bool side = local * kQL >= P.g.mp;
+  const int64_t base = side ? P.g.mp : 0, r0 = local * kQL - base;
+  const Operand op = operand(P, side);
+  const int64_t kp = P.g.kp, lines_pad = side ? P.g.np : P.g.mp;
+  const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), t = threadIdx.x & 255;
+  const int rl = t >> 4, b = t & 15;
+  double *tile = tiles[grp];
+  auto first_k = [&](int u) { return (int64_t)kQK * (grp + kLinesG * u); };
+  // a thread's 8 values of a tile: of one line at every 16th k, or of every
+  // second line at one k; invalid ones read element 0 of the operand instead
+  const bool lcontig = op.sr == 1;
+  const int dr = lcontig ? 0 : 2, dh = lcontig ? 16 : 0;
+  const int64_t rt = r0 + (lcontig ? t & 15 : t >> 7);
+  const int ht = lcontig ? t >> 4 : t & 127;
+  const int64_t dq = lcontig ? 16 * op.sh : 2 * op.sr;
+  const int64_t at = rt * op.sr + ht * op.sh;
+  const int lines_left = (int)(op.lines - rt), k = (int)op.k;
+  auto valid = [&](int u, int q) {
+    return dr * q < lines_left && (int)first_k(u) + ht + dh * q < k;
+  };
+  double x[8];
+  auto load = [&](int u) {
+    const int64_t tile0 = at + first_k(u) * op.sh;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) x[q] = op.ptr[valid(u, q) ? tile0 + q * dq : 0];
+    __builtin_amdgcn_sched_barrier(0);  // (nothing that waits for them in between)
+  };
+  auto stage = [&](int u) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int idx = t + 256 * q;
+      tile[lcontig ? tile_at(idx & 15, idx >> 4) : tile_at(idx >> 7, idx & 127)] =
+          valid(u, q) ? x[q] : 0.0;
+    }
+  };
+
+  uint32_t code[T][4] = {}, top = 0;
+  bool bad = false;
+  load(0);
+#pragma unroll
+  for (int u = 0; u < T; ++u) {
+    if (T > 8 || kQK * kLinesG * u < kp) {  // (of a batch: T serves its longest k)
+      stage(u);
+      if (u + 1 < T) load(u + 1);
+      __syncthreads();
+  #pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        uint32_t c[2];
+  #pragma unroll
+        for (int z = 0; z < 2; ++z) {
+          c[z] = line_code(tile[tile_at(rl, b * 8 + w * 2 + z)]);
+          const bool finite = c[z] < 0x7FF0u;
+          bad |= !finite;
+          c[z] = finite ? c[z] : 0u;
+          top = c[z] > top ? c[z] : top;
+        }
+        code[u][w] = c[0] | (c[1] << 16);
+        // packed here and now: kept as its doubles a tile is 16 registers
+        asm volatile("" : "+v"(code[u][w]));
+      }
+      if (u + 1 < T) __syncthreads();
+    }
+  }
+  // the line's maximum: over its 16 lanes, then over the groups
+  top |= bad ? 0x8000u : 0u;
+  auto larger = [](uint32_t a, uint32_t o) {
+    const uint32_t x = a & 0x7FFFu, y = o & 0x7FFFu;
+    return (x > y ? x : y) | ((a | o) & 0x8000u);
+  };
+  for (int off = 1; off < 16; off <<= 1) top = larger(top, __shfl_xor(top, off, 64));
+  if (b == 0) red[grp][rl] = top;
+  __syncthreads();
+  top = 0;
+#pragma unroll
+  for (int q = 0; q < kLinesG; ++q) top = larger(top, (uint32_t)red[q][rl]);
+  bad = (top & 0x8000u) != 0;
+  top &= 0x7FFFu;
+  int E = top ? (int)(top >> 4) - 1023 : 0;
+  const bool again = __syncthreads_or(top != 0 && E < kDeep);
+  auto read = [&](int u) {
+    load(u);
+    __syncthreads();
+    stage(u);
+    __syncthreads();
+  };
+  auto value = [&](int q) {
+    const double v = tile[tile_at(rl, b * 8 + q)];
+    return __builtin_amdgcn_class(v, kFiniteNonzero) ? v : 0.0;
+  };
+  if (again) {  // the exponent of a subnormal maximum
+    double m = 0.0;
+#pragma unroll 1
+    for (int u = 0; u < T; ++u) {
+      read(u);
+      for (int q = 0; q < 8; ++q) m = fmax(m, fabs(value(q)));
+    }
+    for (int off = 1; off < 16; off <<= 1) m = fmax(m, __shfl_xor(m, off, 64));
+    if (b == 0) red[grp][rl] = (uint64_t)__double_as_longlong(m);
+    __syncthreads();
+    uint64_t am = 0;  // (of non-negative doubles the bits are in order)
+    for (int q = 0; q < kLinesG; ++q) am = red[q][rl] > am ? red[q][rl] : am;
+    E = am ? ufp_exponent(am) : 0;
+  }
+  const int64_t L = base + r0 + rl;
+  if (grp == 0 && b == 0) {
+    P.w.E[L] = E;
+    P.w.flags[L] = (bad ? kNonFinite : 0u) | (top ? 0u : kZeroLine) | (NORM ? kFixup : 0u);
+    P.w.rmax[L] = 0u;
+    if (!NORM) P.w.rfix[L] = 0ull;
+    if (local == 0 && t == 0) P.w.amb[0] = P.w.amb[1] = 0u;
+  }
+  uint8_t *bar = (side ? P.w.Bbar : P.w.Abar) + kblocked(r0 + rl, b * 8, lines_pad);
+  uint64_t sum = 0;
+  // a tile's bound operand (mu' = 2^(7 - E)) from the codes of its values
+  auto put = [&](int64_t h0, auto &&e4m3) {
+    if (h0 >= kp) return;
+    uint32_t packed[2] = {0, 0};
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const uint32_t e = e4m3(q);
+      if (NORM) {
+        const uint32_t q9 = e4m3_q9(e);
+        sum += (uint64_t)q9 * q9;
+      }
+      packed[q >> 2] |= e << (8 * (q & 3));
+    }
+    if (!NORM) *(uint2 *)(bar + h0 * lines_pad) = make_uint2(packed[0], packed[1]);
+  };
+  if (!again) {
+    const int rebase = 8 * (7 - E - 1023) + 56;
+#pragma unroll
+    for (int u = 0; u < T; ++u) {
+      put(first_k(u), [&](int q) {
+        return round_up_code(code[u][q >> 1] >> (16 * (q & 1)) & 0xFFFFu, rebase);
+      });
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else {
+#pragma unroll 1
+    for (int u = 0; u < T; ++u) {
+      read(u);
+      put(first_k(u), [&](int q) {
+        const double v = value(q);
+        return v != 0.0 ? e4m3_round_up(v, 7 - E) : 0u;
+      });
+    }
+  }
+  if (NORM) {
+    // 2^18 x the squared norm (see bound_norm_tile)
+    for (int off = 1; off < 16; off <<= 1) sum += __shfl_xor(sum, off, 64);
+    __syncthreads();
+    if (b == 0) red[grp][rl] = sum;
+    __syncthreads();
+    if (grp == 0 && b == 0) {
+      sum = 0;
+#pragma unroll
+      for (int q = 0; q < kLinesG; ++q) sum += red[q][rl];
+      P.w.rfix[L] = sum;
+    }
+  }
+}
+
 // Residues of a' (eq. def:A') for every modulus, split into digits, for one
 // tile (lines r0.., k h0..).
 //
@@ -786,6 +995,26 @@ hipError_t launch_quant_family(int fam, const Problem *P, const Group *G, hipStr
     hipLaunchKernelGGL((KER<true>), grid, blk, 0, st, p1, g1);              \
   else                                                                      \
     hipLaunchKernelGGL((KER<false>), grid, blk, 0, st, p1, g1);
+  if (fam == kFamLines) {
+    const bool norm = grouped ? G->norm : p1.mode == OZ2_MODE_FAST;
+    const int64_t k = grouped ? G->max_k : p1.g.k;
+#define OZ2_L(T)                                                              \
+  if (k <= kQK * kLinesG * T) {                                               \
+    if (grouped && norm)                                                      \
+      hipLaunchKernelGGL((k_lines<true, true, T>), grid, wide, 0, st, p1, g1);  \
+    else if (grouped)                                                         \
+      hipLaunchKernelGGL((k_lines<true, false, T>), grid, wide, 0, st, p1, g1); \
+    else if (norm)                                                            \
+      hipLaunchKernelGGL((k_lines<false, true, T>), grid, wide, 0, st, p1, g1); \
+    else                                                                      \
+      hipLaunchKernelGGL((k_lines<false, false, T>), grid, wide, 0, st, p1, g1); \
+    return hipGetLastError();                                                 \
+  }
+    const dim3 wide(256 * kLinesG);
+    OZ2_L(1) OZ2_L(2) OZ2_L(4) OZ2_L(8) OZ2_L(16) OZ2_L(32)
+#undef OZ2_L
+    return hipErrorInvalidValue;
+  }
   switch (fam) {
     case kFamFill: OZ2_Q(k_fill) break;
     case kFamLmax: OZ2_Q(k_line_max) break;
