@@ -258,12 +258,12 @@ __device__ __forceinline__ void stage(Producer &p, const Lanes<F::LPW> &ln, Ring
     }
 }
 
-// acc = m (acc mods q) up to a multiple of q: for an exact x (in units of
-// 1/64: q64 = q / 64, inv64 = 64 / q) with |64 x| < 2^24, x - rint(x / q) q is
-// exact in one fused multiply-add and at most q / 2 + 2 in magnitude, so the
-// result is below 258 256 < 2^17 and the next pass's sums (at most 2^23 more)
-// stay exact.
-__device__ __forceinline__ void fold(v4f (&acc)[TJ][TI], float q64, float inv64, float m) {
+// acc = acc mods q up to a multiple of q: for an exact x (in units of 1/64: q64
+// = q / 64, inv64 = 64 / q) with |64 x| < 2^24, x - rint(x / q) q is exact in one
+// fused multiply-add and at most q / 2 + 2 in magnitude; times a multiplier it
+// is below 258 256 < 2^17, and the next pass's sums (at most 2^23 more) stay
+// exact.
+__device__ __forceinline__ void reduce(v4f (&acc)[TJ][TI], float q64, float inv64) {
 #pragma unroll
   for (int tj = 0; tj < TJ; ++tj)
 #pragma unroll
@@ -271,8 +271,18 @@ __device__ __forceinline__ void fold(v4f (&acc)[TJ][TI], float q64, float inv64,
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const float x = acc[tj][ti][v];
-        acc[tj][ti][v] = fmaf(-rintf(x * inv64), q64, x) * m;
+        acc[tj][ti][v] = fmaf(-rintf(x * inv64), q64, x);
       }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+}
+__device__ __forceinline__ void scale(v4f (&acc)[TJ][TI], float m) {
+#pragma unroll
+  for (int tj = 0; tj < TJ; ++tj)
+#pragma unroll
+    for (int ti = 0; ti < TI; ++ti) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[tj][ti][v] *= m;
       __builtin_amdgcn_sched_barrier(0);
     }
 }
@@ -460,8 +470,9 @@ __global__ __launch_bounds__(64 * NW, 1) void k_residue6(Problem, WorkList W, in
       int16_t *dst = out + ((tj >> 2) * 64 + 4 * v + (tj & 3)) * mp;
       // the next item's first stages (their loads count with the stores)
       if (tj == 0 && v == 0) wait_vm<0>();
-      *(uint2 *)dst = make_uint2(((uint32_t)res[0] & 0xFFFFu) | ((uint32_t)res[1] << 16),
-                                 ((uint32_t)res[2] & 0xFFFFu) | ((uint32_t)res[3] << 16));
+      // the low halves of two values in one instruction
+      *(uint2 *)dst = make_uint2(__builtin_amdgcn_perm(res[1], res[0], 0x05040100u),
+                                 __builtin_amdgcn_perm(res[3], res[2], 0x05040100u));
     };
     if constexpr (F::I8) {
       // one product; the symmetric residue of an INT32 sum in FP64, where the
@@ -499,8 +510,8 @@ __global__ __launch_bounds__(64 * NW, 1) void k_residue6(Problem, WorkList W, in
         __builtin_amdgcn_sched_barrier(0);
       }
     } else {
-      // one pass (from stage j0 of it) and the fold that ends it: m (acc mods q)
-      // after the last chunk (m = 0: none), acc mods p after the others
+      // one pass (from stage j0 of it) and the fold that ends it: acc mods q
+      // unless q = 0 after the last chunk, acc mods p after the others, then m acc
       auto pass = [&](int j0, float q, float iq, float m, float pf, float inv) {
         int left = c.nk;
         for (;;) {
@@ -508,32 +519,40 @@ __global__ __launch_bounds__(64 * NW, 1) void k_residue6(Problem, WorkList W, in
           loop(j0, n);
           left -= n;
           const bool last = !LIST || left == 0;
-          if (!last || m != 0.0f)
-            fold(acc, (last ? q : pf) * 0.015625f, (last ? iq : inv) * 64.0f, last ? m : 1.0f);
+          const float qq = last ? q : pf;
+          if (qq != 0.0f) reduce(acc, qq * 0.015625f, (last ? iq : inv) * 64.0f);
           if (last) break;
           j0 = 0;
         }
+        if (m != 1.0f) scale(acc, m);
       };
+      // The vector work between an item's MFMAs (4 instructions per output for a
+      // fold, 5 for the result) is felt at short k, so what short sums don't need
+      // is left out (products of 3000 x 2000 x 256 64.5 -> 58.7 us, 16384 x 16384 x
+      // 1024 5.71 -> 5.58 ms):
+      //  - Karatsuba, k <= 3840: |a X + Y| <= 17 256 k < 2^24 without reducing X;
+      //  - no reduction before the multiplier c and the result's own when the
+      //    quotient's error stays below 1 / (4 p) (see the result below), about
+      //    |c acc| <= 2^21: squares to k = 8192, Karatsuba at k = 256.
       const bool square = tab->kind[l] == 0;
-      pass(2, pf, inv, square ? 0.0f : (float)tab->kfold[l][0], pf, inv);
+      const int k = c.nk * F::BK;
+      pass(2, square || k <= 3840 ? 0.0f : pf, inv, square ? 1.0f : (float)tab->kfold[l][0], pf,
+           inv);
       const float q2 = square ? (float)tab->s[l] : pf, iq2 = square ? tab->inv_s[l] : inv;
       pass(0, q2, iq2, square ? q2 : (float)tab->kfold[l][1], pf, inv);
-      pass(0, pf, inv, 0.0f, pf, inv);
-      // symmetric residue, four consecutive rows i per lane: a first reduction to
-      // |r| <= p / 2 + 2, the multiplier, and a second one whose quotient is
+      pass(0, k <= (square ? 8192 : 256) ? 0.0f : pf, inv, 1.0f, pf, inv);
+      // symmetric residue of c acc, four consecutive rows i per lane, its quotient
       // nudged by 1 / (4 p), so that an exact half (even p) goes to -p / 2 and no
       // other value (at least 1 / (2 p) from a half) moves
-      const float m3 = 64.0f * (square ? 1.0f : (float)tab->kfold[l][2]);
-      const float inv64 = inv * 64.0f, q64 = pf * 0.015625f, bias = 0.25f * inv;
-  #pragma unroll
+      const float mc = 64.0f * (square ? 1.0f : (float)tab->kfold[l][2]), bias = 0.25f * inv;
+#pragma unroll
       for (int tj = 0; tj < TJ; ++tj) {
-  #pragma unroll
+#pragma unroll
         for (int v = 0; v < 4; ++v) {
           int res[TI];
-  #pragma unroll
+#pragma unroll
           for (int ti = 0; ti < TI; ++ti) {
-            const float x = acc[tj][ti][v];
-            const float y = fmaf(-rintf(x * inv64), q64, x) * m3;
+            const float y = acc[tj][ti][v] * mc;
             res[ti] = (int)fmaf(-rintf(fmaf(y, inv, bias)), pf, y);
           }
           store(tj, v, res);

@@ -124,6 +124,38 @@ def test_folds_and_symmetric_residue(p, kind, s):
     assert np.array_equal(z.astype(np.int64), _sym(x * last, p))
 
 
+@pytest.mark.parametrize("p,kind,s", _moduli())
+def test_short_sums_in_one_step(p, kind, s):
+    # up to k = 8192 (squares) and 256 (Karatsuba) the result takes one step from
+    # the accumulator times its multiplier; up to 3840 Karatsuba's first fold
+    # only multiplies
+    if kind == "square":
+        last, limit = 1, (s // 2) ** 2 * 8192 + s * (s // 2 + 2)
+    else:
+        i = lambda v: pow(v % p, -1, p)
+        sym = lambda v: int(_sym(np.int64(v), p))
+        if np.gcd(p, 15) == 1:
+            a, b, last = sym(15), sym(-16 * i(15)), sym(-15)
+        else:
+            a, b, last = sym(-16), sym(-15 * i(16)), sym(16)
+        assert (abs(a) + 1) * 256 * 3840 < 2 ** 24
+        x = _values((abs(a) + 1) * 256 * 256, p)
+        assert np.abs(_reduce(x, p)).max() <= p // 2
+        limit = 256 * 256 + abs(b) * (p // 2)
+    x = _values(limit, p)
+    halves = (np.arange(max(0, limit // p - 3000), limit // p)[:, None] * p + np.arange(-2, 3)
+              + p // 2).ravel()
+    x = np.concatenate([x, halves, -halves])
+    x = x[np.abs(x) <= limit]
+    y = (x * last).astype(np.float32)
+    assert np.array_equal(y.astype(np.int64), x * last)
+    inv = np.float32(1) / np.float32(p)
+    bias = np.float32(0.25) * inv
+    t = np.rint((y.astype(np.float64) * np.float64(inv) + np.float64(bias)).astype(np.float32))
+    z = y.astype(np.float64) - t.astype(np.float64) * p
+    assert np.array_equal(z.astype(np.int64), _sym(x * last, p))
+
+
 def test_int8_fp64_residues():
     # the products' epilogue: one FP64 step on an INT32 sum, the quotient nudged
     # by 1 / (4 p) so that an even p's half goes to -p / 2
