@@ -354,6 +354,7 @@ Problem make_problem(char transA, char transB, int64_t m, int64_t n, int64_t k, 
   P.mode = g_ts.mode;
   P.parts = L.parts;
   P.res_sides = 3;
+  P.stream_c = 8 * m * n >= kStreamC;
   P.bparts = P.mode == OZ2_MODE_FAST ? 1 : L.bparts;
   P.g.fp6 = fp6;
   return P;
@@ -754,7 +755,10 @@ struct ImageWriter {
 // and per configuration the persistent residue products (one work list over
 // every problem, modulus, tile and k part, longest item first) and the CRT
 // (over descriptors that carry the configuration's k parts).
-void build_subbatch(const std::vector<Problem> &probs, ImageWriter &W, SubBatch *sb) {
+void build_subbatch(std::vector<Problem> probs, ImageWriter &W, SubBatch *sb) {
+  int64_t c_bytes = 0;
+  for (const Problem &P : probs) c_bytes += 8 * P.g.m * P.g.n;
+  for (Problem &P : probs) P.stream_c = c_bytes >= kStreamC;
   const int np = (int)probs.size();
   const size_t at_probs = W.put(probs.data(), sizeof(Problem) * np);
   std::vector<int32_t> nat(np);

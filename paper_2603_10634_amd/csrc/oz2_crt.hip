@@ -84,7 +84,7 @@ __device__ __forceinline__ void crt_pair(const Problem &P, const Tables *__restr
 #pragma unroll
   for (int l = 0; l < (NF > 0 ? NF : kMaxN); ++l)
     if (l < N) {
-      uu[l] = *(const uint32_t *)ql;
+      uu[l] = __builtin_nontemporal_load((const uint32_t *)ql);
       ql += pstride;
     }
   const uint2 fl = *(const uint2 *)(P.w.flags + i);
@@ -150,7 +150,15 @@ __device__ __forceinline__ void crt_pair(const Problem &P, const Tables *__restr
       r[0] = __dadd_rn(r[0], __dmul_rn(beta, c[0]));
       r[1] = __dadd_rn(r[1], __dmul_rn(beta, c[1]));
     }
-    *(d2 *)C = r;
+    if (P.stream_c) {
+      // (the empty statements keep the two stores from being merged into one
+      // ordinary one)
+      asm volatile("");
+      __builtin_nontemporal_store(r, (d2 *)C);
+      asm volatile("");
+    } else {
+      *(d2 *)C = r;
+    }
   } else {
     if (beta != 0.0) r[0] = __dadd_rn(r[0], __dmul_rn(beta, C[0]));
     C[0] = r[0];

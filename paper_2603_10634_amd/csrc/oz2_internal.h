@@ -133,6 +133,7 @@ struct Problem {
   int32_t parts;       // k parts of the residue products (split-K): the CRT sums this
                        // many copies of the residue planes, each N mp np entries apart
   int32_t res_sides;   // operands whose residues are computed: 1 op(A), 2 op(B), 3 both
+  int stream_c;   // whether C is stored past the caches (kStreamC bytes of C in the call)
   int32_t bparts;      // k parts of the bound product (1: one pass with line maxima)
 };
 
@@ -193,6 +194,14 @@ enum Family : int {
   kFamCrt,        // CRT, inverse scaling, alpha / beta
   kNumFamilies
 };
+
+// A call whose C is larger than this stores it past the caches: its inputs, digits
+// and planes have gone through them since anything else was read, and the dirty C
+// would leave when the next call's inputs come in (16384 x 16384 x 1024: CRT 1.70
+// -> 1.57 ms and the next line pass 118 -> 67 us; 48 products with 126 MB of C: 117
+// -> 106 us).  Smaller ones may be read from there (3000 x 2000 x 256 with beta = 1,
+// 48 MB: 41.7 against 42.5 us).
+constexpr int64_t kStreamC = 64 << 20;
 
 // k-split of the line-maxima pass: enough blocks for the chip, but at least
 // kLmaxK elements of a line per thread (64 threads' worth of 8 where k is
