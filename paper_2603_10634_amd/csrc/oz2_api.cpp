@@ -756,9 +756,15 @@ struct ImageWriter {
 // every problem, modulus, tile and k part, longest item first) and the CRT
 // (over descriptors that carry the configuration's k parts).
 void build_subbatch(std::vector<Problem> probs, ImageWriter &W, SubBatch *sb) {
-  int64_t c_bytes = 0;
-  for (const Problem &P : probs) c_bytes += 8 * P.g.m * P.g.n;
-  for (Problem &P : probs) P.stream_c = c_bytes >= kStreamC;
+  int64_t c_bytes = 0, tiles = 0;
+  for (const Problem &P : probs) {
+    c_bytes += 8 * P.g.m * P.g.n;
+    tiles += res6_tiles(P);
+  }
+  for (Problem &P : probs) {
+    P.stream_c = c_bytes >= kStreamC;
+    P.more_tiles = (int32_t)std::min<int64_t>(tiles - res6_tiles(P), 1 << 30);
+  }
   const int np = (int)probs.size();
   const size_t at_probs = W.put(probs.data(), sizeof(Problem) * np);
   std::vector<int32_t> nat(np);
