@@ -1,10 +1,12 @@
 // Quantization passes over the FP64 inputs (HBM-bound):
 //  - line maxima of op(A) rows / op(B) columns (for mu', nu', eq. def:mu'nu'),
 //  - the round-up FP8 bound operands Abar, Bbar (Section III-E), or in fast
-//    mode the squared norms of their lines (Cauchy-Schwarz bound),
+//    mode the squared norms of their lines (Cauchy-Schwarz bound); both steps in
+//    one pass for lines of up to 8192 k,
 //  - the residues of A', B' for every modulus, split into FP8 digits
 //    (eqs. def:A', def:B', CRTmatmul; digit splits of Sections III-B..III-D).
-// Outputs are k-blocked (kblocked in oz2_internal.h), zero padded.
+// Outputs are k-blocked (kblocked in oz2_internal.h) or, the slices of
+// k_residue6, in its fragment order; zero padded.
 #include <string.h>
 
 #include "oz2_device.h"
@@ -297,7 +299,8 @@ __global__ __launch_bounds__(256) void k_bound_norm(Problem P1, Group G) {
 // lines.  Both operands, against clearing, maxima and bound operand in three
 // launches: 8192^3 480 -> 333 us (3.6 TB/s), 4096^3 136 -> 88, 16384 x 16384 x
 // 1024 130 -> 72, 3000 x 2000 x 256 17.7 -> 9.4, 256^3 14.4 -> 7.2.  Four groups
-// (one workgroup per CU) reach 370 us at 8192^3.
+// (one workgroup per CU) reach 370 us at 8192^3.  512 products of 64 .. 4096 with
+// every line running the trips of the longest k: 4.5 ms, its own: 2.3.
 constexpr int kLinesG = 2;  // groups of 256 threads
 constexpr int kDeep = -1006;
 
@@ -369,7 +372,7 @@ __global__ __launch_bounds__(256 * kLinesG, T <= 16 ? 4 : 2) void k_lines(Proble
   load(0);
 #pragma unroll
   for (int u = 0; u < T; ++u) {
-    if (T > 8 || kQK * kLinesG * u < kp) {  // (of a batch: T serves its longest k)
+    if (kQK * kLinesG * u < kp) {  // (of a batch, T serves its longest k)
       stage(u);
       if (u + 1 < T) load(u + 1);
       __syncthreads();
