@@ -17,8 +17,9 @@
 // E4M3), with the MFMA busy 65 % of the cycles at 1.62 GHz.  Other orders of
 // the same work (a barrier per 64 or per 256 k, the barrier in the middle of
 // a stage, wave priorities, 32 x 32 x 64 steps at 71 % busy and 1.40 GHz)
-// came out within 2 % of one another or slower; the loads from L2 into LDS
-// alone account for a fifth of the time.
+// came out within 2 % of one another or slower.  Left out in turn: the loads into
+// LDS account for a fifth of the time, of it 6 % (10 % at k = 1024) for lines that
+// are not in L2; the planes' stores for 5 % at k = 4096 and 11 % at k = 1024.
 //
 // Layout (digit6): a slice of R lines is cut into stages of 128 k, a stage
 // into groups of 64 lines, a group into the fragments of its lines r = q (mod
@@ -258,6 +259,43 @@ __device__ __forceinline__ void stage(Producer &p, const Lanes<F::LPW> &ln, Ring
     }
 }
 
+// An item's stages of a wave whose outputs are all padding: its share of the loads
+// and one barrier per stage, as in stage(), then the next item's first fragments.
+// (Its matrix instructions were power and time of the others: 48 products of 64 ..
+// 2048, 47 % of their work padding, 443 -> 409 us.)
+template <class F>
+__device__ __forceinline__ void pad_item(Producer &p, const Lanes<F::LPW> &ln, Ring &r,
+                                         const uint8_t *lds, typename F::Frag (&fa)[TI],
+                                         typename F::Frag (&fb)[3], int stages, int lane, int wj,
+                                         int wi) {
+#pragma unroll 1
+  for (int j = 0; j < stages; ++j) {
+    const uint32_t slot = r.base + r.fill;
+    load<F, 0>(p, ln, slot);
+    load<F, 1>(p, ln, slot);
+    load<F, 2>(p, ln, slot);
+    load<F, 3>(p, ln, slot);
+    if constexpr (F::LPW > 4) {
+      load<F, 4>(p, ln, slot);
+      load<F, 5>(p, ln, slot);
+    }
+    advance<F::PASSES>(p);
+    r.fill = next_slot<F>(r.fill);
+    wait_lgkm0();
+    wait_vm<(F::S - 2) * F::LPW>();
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    r.cur = next_slot<F>(r.cur);
+  }
+  wait_vm<0>();  // the next item's first stages, as before the result's stores
+#pragma unroll
+  for (int t = 0; t < TI; ++t)
+    frag(fa[t], lds + r.cur + F::SIDE + (wi * TI + t) * F::FRAG, lane);
+#pragma unroll
+  for (int t = 0; t < 3; ++t) frag(fb[t], lds + r.cur + (wj * TJ + t) * F::FRAG, lane);
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // acc = acc mods q up to a multiple of q: for an exact x (in units of 1/64: q64
 // = q / 64, inv64 = 64 / q) with |64 x| < 2^24, x - rint(x / q) q is exact in one
 // fused multiply-add and at most q / 2 + 2 in magnitude; times a multiplier it
@@ -447,6 +485,10 @@ __global__ __launch_bounds__(64 * NW, 1) void k_residue6(Problem, WorkList W, in
     // a scalar load still pending would turn every LDS wait of the loops into
     // a full drain (both count on LGKM, out of order): wait for them here
     asm volatile("" ::"s"(p.next.ab), "s"(p.next.A), "s"(p.next.B), "s"(p.next.nk));
+    if (c.ty * kGemmTJ + wj * 128 >= c.P->g.n || c.tx * kGemmTIW + wi * 64 >= c.P->g.m) {
+      pad_item<F>(p, ln, r, lds, fa0, fb, F::PASSES * c.nk, lane, wj, wi);
+      continue;
+    }
     constexpr int kMaxStages = kChunkK / F::BK;
     typename F::Acc acc[TJ][TI];
     // the loop over the stages [j, n) of one chunk

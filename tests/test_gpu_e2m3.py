@@ -124,3 +124,36 @@ def test_split_and_blocked(parts):
     with split(parts):
         assert same_bits(run(A, B, 12).C, want)
         assert same_bits(run(A, B, 12, "T", "T", blocking=(768, 512)).C, want)
+
+
+@pytest.mark.parametrize("moduli", ["hybrid", "int8"])
+@pytest.mark.parametrize("m,n,k", [(1, 1300, 300), (1300, 1, 70), (64, 1409, 513), (65, 1408, 200),
+                                   (1345, 129, 256), (1344, 128, 700)])
+def test_waves_without_outputs(m, n, k, moduli):
+    # tiles of which a wave's 128 (columns) x 64 (rows) is padding, one row or
+    # column of it is not, or all of it is used, item after item
+    A, B = phi_matrix(m, k, 1.0, 9500 + m), phi_matrix(k, n, 1.0, 9600 + n)
+    print(f"padding waves {m}x{n}x{k} {moduli}", flush=True)
+    C, st = ref.emulate(A, B, 14, keep_stages=True, moduli_set=moduli)
+    r = run(A, B, 14, keep_ws=True, moduli=moduli)
+    assert r.status == 0
+    P = r.planes(14, [pm["p"] for pm in st["per_modulus"]])
+    for l, plane in enumerate(st["planes"]):
+        assert np.array_equal(P[l, :n, :m].T, plane), f"plane {l}"
+    assert same_bits(r.C, C)
+
+
+def test_waves_without_outputs_in_a_batch():
+    # items of several sizes in one launch, sorted by k only: full, ragged and
+    # nearly empty tiles follow one another in a workgroup
+    import torch
+    rng = np.random.default_rng(9700)
+    shapes = [(int(m), int(n), int(k)) for m, n, k in
+              zip(rng.choice([1, 63, 64, 65, 129, 256, 300, 513], 40),
+                  rng.choice([1, 127, 128, 129, 256, 400], 40), rng.choice([30, 257, 600], 40))]
+    As = [phi_matrix(m, k, 1.0, 9701 + q) for q, (m, n, k) in enumerate(shapes)]
+    Bs = [phi_matrix(k, n, 1.0, 9801 + q) for q, (m, n, k) in enumerate(shapes)]
+    Cs = oz.dgemm_batched([torch.from_numpy(a).cuda() for a in As],
+                          [torch.from_numpy(b).cuda() for b in Bs], 12)
+    for q, (a, b) in enumerate(zip(As, Bs)):
+        assert same_bits(Cs[q].cpu().numpy(), ref.emulate(a, b, 12)), shapes[q]
