@@ -10,8 +10,9 @@ resident in HBM before the timed region.  One step = one ozaki2_dgemm call
 Beside the emulated rate it reports: the native FP64 DGEMM (torch.matmul on
 float64, i.e. the vendor BLAS) on the same inputs, the normalised error of
 both against a double-double reference on sampled rows, the residue-product
-kernels against the FP8 MFMA roofline (timed with HIP events on the library's
-stream), and the CPU oracle on a bounded sample of the same workload.
+kernel against the MFMA roofline of the format its digits are in (timed with HIP
+events on the library's stream), and the CPU oracle on a bounded sample of the
+same workload.
 """
 from __future__ import annotations
 
@@ -25,8 +26,21 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 METRIC = "emulated FP64 TFLOP/s vs native FP64 DGEMM at ≤1e-15 err; FP8 MFMA util %"
-FP8_PEAK_TFLOPS = 5000.0       # MI355X dense FP8 MFMA
+# MI355X dense MFMA peaks, TFLOP/s (TOP/s), of the formats the residue products
+# read: the digits (integers of magnitude <= 16, exact in either) of the FP8 lists
+# are E2M3 in batches and with more than four 256 x 256 output tiles, E4M3 in
+# smaller calls; the INT8 list's residues are INT8.
+PEAK_TFLOPS = {"e2m3": 10000.0, "e4m3": 5000.0, "int8": 5000.0}
+DTYPE = {"e2m3": "fp6e2m3-mfma (exact integer digits)->f64", "e4m3": "fp8e4m3-mfma->f64",
+         "int8": "int8-mfma->f64"}
 HBM_PEAK_GBS = 8000.0
+
+
+def digit_format(moduli_list: str, m: int, n: int) -> str:
+    """Format of the residue products' operands for an m x n output."""
+    if moduli_list == "int8":
+        return "int8"
+    return "e2m3" if -(-m // 256) * -(-n // 256) > 4 else "e4m3"
 
 
 def _parse():
@@ -113,7 +127,7 @@ def _bench_batched(args):
     configuration; the timed steps replay the call's captured graph.  Beside
     it: the same problems as looped ozaki2_dgemm calls and as looped native
     FP64 DGEMMs (torch.matmul), and one eager timed pass for the kernel
-    breakdown (the persistent residue-product launch against the FP8 peak)."""
+    breakdown (the persistent residue-product launch against its MFMA peak)."""
     import numpy as np
     import torch
 
@@ -205,6 +219,8 @@ def _bench_batched(args):
     products = N if args.moduli_list == "int8" else 3 * N
     gemm_ms = float(k_mean[4])
     achieved = products * flops / (gemm_ms * 1e-3) / 1e12
+    fmt = "int8" if args.moduli_list == "int8" else "e2m3"
+    peak = PEAK_TFLOPS[fmt]
     out = {
         "metric": METRIC,
         "value": round(value, 3),
@@ -216,7 +232,7 @@ def _bench_batched(args):
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "fp8e4m3-mfma->f64",
+        "dtype": DTYPE[fmt],
         "data": "synthetic",
         "config": {"workload": f"batched: {cnt} emulated dgemms, m, n, k log-uniform in "
                                f"[64, 4096], col-major NN, phi={args.phi}, {N} "
@@ -231,10 +247,10 @@ def _bench_batched(args):
         "speedup_vs_looped_single": round(ms_looped / ms_batched, 3),
         "speedup_vs_native": (round(value / native["tflops"], 3) if native else None),
         "kernel_ms_mean_eager": [round(float(x), 4) for x in k_mean],
-        "roofline": {"bound": "mfma", "achieved": round(achieved, 1), "peak": FP8_PEAK_TFLOPS,
-                     "unit": "TFLOP/s", "frac": round(achieved / FP8_PEAK_TFLOPS, 4),
+        "roofline": {"bound": "mfma", "achieved": round(achieved, 1), "peak": peak,
+                     "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
                      "traffic": None,
-                     "kernel": f"k_residue_persistent (one launch: {products} FP8 products per "
+                     "kernel": f"k_residue6 (one launch: {products} {fmt} products per "
                                "problem, all problems; algorithmic flops on the unpadded "
                                "shapes)"},
         "cpu_baseline": None,
@@ -330,9 +346,11 @@ def main():
     k_med = np.median(kt, axis=0)
     step_med_ms = float(np.median(kt.sum(axis=1)))
 
-    # residue products (3 FP8 products per modulus) against the FP8 MFMA peak
+    # residue products (FP8 lists: three digit products per modulus; INT8 arm: one)
+    # against the MFMA peak of their operands' format
     gemm_ms = float(k_mean[4])
-    # FP8 lists: three products per modulus; INT8 arm: one (same peak rate)
+    fmt = digit_format(args.moduli_list, m, n)
+    peak = PEAK_TFLOPS[fmt]
     products = N if args.moduli_list == "int8" else 3 * N
     res_flops = products * flops
     achieved = res_flops / (gemm_ms * 1e-3) / 1e12
@@ -344,12 +362,11 @@ def main():
             rec = json.load(f)
         if rec.get("gemm_source_sha256") == gemm_source_sha():
             traffic = rec.get("bytes_per_call")
-    roofline = {"bound": "mfma", "achieved": round(achieved, 1), "peak": FP8_PEAK_TFLOPS,
-                "unit": "TFLOP/s", "frac": round(achieved / FP8_PEAK_TFLOPS, 4),
+    kernel = "k_residue6" if -(-m // 256) * -(-n // 256) > 4 else "k_residue_small / _gemm"
+    roofline = {"bound": "mfma", "achieved": round(achieved, 1), "peak": peak,
+                "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
                 "traffic": traffic,
-                "kernel": "k_residue_gemm (square + Karatsuba launches), "
-                          f"{products} {'INT8' if args.moduli_list == 'int8' else 'FP8'} "
-                          f"products of {m}x{n}x{k} per call"}
+                "kernel": f"{kernel}, {products} {fmt} products of {m}x{n}x{k} per call"}
 
     # accuracy against a double-double reference on sampled rows
     Cemu = tC.cpu().numpy().T                    # m x n
@@ -416,7 +433,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "fp8e4m3-mfma->f64",
+        "dtype": DTYPE[fmt],
         "data": "synthetic",
         "config": {"workload": f"emulated dgemm {m}x{n}x{k} col-major "
                                f"{args.transA}{args.transB}, phi={args.phi}"
@@ -430,7 +447,7 @@ def main():
         "native_fp64": native,
         "vendor_fp8_gemm": vendor,
         "speedup_vs_native": (round(value / native["tflops"], 3) if native else None),
-        "mfma_util_pct": round(100 * achieved / FP8_PEAK_TFLOPS, 2),
+        "mfma_util_pct": round(100 * achieved / peak, 2),
         "stage_ms_median": {kk: round(v, 4) for kk, v in stage.items()},
         "scale_fixup_lines": fixups,
         "workspace_bytes": wbytes,

@@ -16,11 +16,10 @@
 // read 4 bytes per lane, a wave 64 rows x 2 columns (outputs with few rows
 // leave few threads idle).
 //
-// Bound by HBM: 2 N + 8 bytes per output at the rate a plain copy reaches
-// (4.7 TB/s).  8192^2 outputs, N = 12: 0.455 ms; 16384^2: 1.80 ms.  With 32-bit
-// limbs, a borrow chain and integer rounding for every entry it was bound by
-// vector issue, 218 instructions per output against about 120: 0.58 and 2.20
-// ms.
+// Bound by HBM: 2 N + 8 bytes per output.  8192^2 outputs, N = 12: 0.41 ms (5.2
+// TB/s); 16384^2: 1.57 ms (0.455 and 1.80 through the caches).  With 32-bit limbs,
+// a borrow chain and integer rounding for every entry it was bound by vector
+// issue, 218 instructions per output against about 120: 0.58 and 2.20 ms.
 #include <string.h>
 
 #include "oz2_crt_math.h"

@@ -3,11 +3,13 @@
 //
 //  * bound product: Cbar' = Abar Bbar (Section III-E); only the row and column
 //    maxima of the FP32 result leave the kernel.
-//  * residue products: per modulus the three digit products of Sections III-B
-//    and III-C.  Digits are integers of magnitude <= 16, so over a chunk of
-//    k <= 2^15 every partial sum is an integer of magnitude <= 2^24 and the
-//    FP32 accumulation is exact (eq. error-free-FP8-matmult); the epilogue
-//    combines the products and reduces them modulo p into int16 planes.
+//  * residue products on k-blocked slices: single calls of at most four output
+//    tiles whose k is too long for oz2_small.hip (the others: oz2_gemm6.hip).
+//    Per modulus the three digit products of Sections III-B and III-C.  Digits
+//    are integers of magnitude <= 16, so over a chunk of k <= 2^15 every partial
+//    sum is an integer of magnitude <= 2^24 and the FP32 accumulation is exact
+//    (eq. error-free-FP8-matmult); the epilogue combines the products and
+//    reduces them modulo p into int16 planes.
 //  * INT8 arm (Section II): one product of the INT8 residues per modulus on
 //    v_mfma_i32_32x32x32_i8, INT32 accumulation, the same wide loop.
 //

@@ -13,8 +13,8 @@
       (FETCH_counter_collection.csv, WRITE_counter_collection.csv), each
       scaled so that the plain 1 GiB device copy that bench.py
       --copy-calibration runs reads exactly 1 GiB fetched and 1 GiB written.
-      OUT.json records the residue-product bytes per call (both launches)
-      with the SHA-256 of the GEMM source, so bench.py can tell whether the
+      OUT.json records the residue-product bytes per call (all launches)
+      with the SHA-256 of their source, so bench.py can tell whether the
       counters still describe the built kernel.
 
 The counters report KiB per dispatch; rows are averaged over the dispatches
@@ -30,7 +30,7 @@ import sys
 from collections import defaultdict
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-GEMM_SOURCE = os.path.join(HERE, "csrc", "oz2_gemm.hip")
+GEMM_SOURCE = os.path.join(HERE, "csrc", "oz2_gemm6.hip")
 COPY_BYTES = 1 << 30
 
 
@@ -126,10 +126,10 @@ def traffic(d: str, fetch: str, write: str, out_md: str, out_json: str, cmd: str
             if fb + wb < 1e6:
                 continue
             f.write(f"| `{k[0]}` | {k[1]} | {fb / 1e6:.1f} | {wb / 1e6:.1f} |\n")
-            if k[0].startswith("k_residue_gemm"):
+            if k[0].startswith(("k_residue6", "k_residue_gemm")):
                 gemm["fetch"] += fb
                 gemm["write"] += wb
-    rec = {"kernel": "residue products (square and Karatsuba launches of one call)",
+    rec = {"kernel": "residue products of one call",
            "fetch_bytes_per_call": gemm["fetch"], "write_bytes_per_call": gemm["write"],
            "bytes_per_call": gemm["fetch"] + gemm["write"], "fetch_scale": fscale,
            "write_scale": wscale, "gemm_source_sha256": gemm_source_sha(), "commands": cmd}
