@@ -299,8 +299,8 @@ __device__ __forceinline__ void pad_item(Producer &p, const Lanes<F::LPW> &ln, R
 // acc = acc mods q up to a multiple of q: for an exact x (in units of 1/64: q64
 // = q / 64, inv64 = 64 / q) with |64 x| < 2^24, x - rint(x / q) q is exact in one
 // fused multiply-add and at most q / 2 + 2 in magnitude; times a multiplier it
-// is below 258 256 < 2^17, and the next pass's sums (at most 2^23 more) stay
-// exact.
+// is below 258 256 < 2^17, and the next chunk's sums (at most 2^23 more) stay
+// exact.  (Only a square's first pass of one chunk goes on unreduced: 2^24.)
 __device__ __forceinline__ void reduce(v4f (&acc)[TJ][TI], float q64, float inv64) {
 #pragma unroll
   for (int tj = 0; tj < TJ; ++tj)
@@ -399,7 +399,8 @@ __device__ __forceinline__ Place place_list(const WorkList &W, int it) {
 // A2 B1, fold s (. mod s), + A2 B2; Karatsuba: X, fold a, + Y, fold b, + Z,
 // times c, see the tables) into one accumulator, then the symmetric residue
 // into the modulus's int16 plane.  A pass of a list item longer than kChunkK is
-// summed in chunks of that length, each but the last reduced modulo p.  Items
+// summed in chunks of that length, each but the last reduced modulo p, and the
+// last by the pass's fold.  Items
 // go to the workgroups in rounds, a list's every second one backwards: sorted
 // longest first it comes out within 3 % of the average (48 problems log-uniform
 // in [64, 2048]), with no counter to fetch from.
@@ -575,14 +576,16 @@ __global__ __launch_bounds__(64 * NW, 1) void k_residue6(Problem, WorkList W, in
       // fold, 5 for the result) is felt at short k, so what short sums don't need
       // is left out (products of 3000 x 2000 x 256 64.5 -> 58.7 us, 16384 x 16384 x
       // 1024 5.71 -> 5.58 ms):
+      //  - squares, one chunk: the first two passes sum to at most 2^24 (a longer
+      //    item's first pass ends at up to 2^23 + p / 2 + 2 and is reduced);
       //  - Karatsuba, k <= 3840: |a X + Y| <= 17 256 k < 2^24 without reducing X;
       //  - no reduction before the multiplier c and the result's own when the
       //    quotient's error stays below 1 / (4 p) (see the result below), about
       //    |c acc| <= 2^21: squares to k = 8192, Karatsuba at k = 256.
       const bool square = tab->kind[l] == 0;
       const int k = c.nk * F::BK;
-      pass(2, square || k <= 3840 ? 0.0f : pf, inv, square ? 1.0f : (float)tab->kfold[l][0], pf,
-           inv);
+      const bool plain = k <= (square ? kChunkK : 3840);
+      pass(2, plain ? 0.0f : pf, inv, square ? 1.0f : (float)tab->kfold[l][0], pf, inv);
       const float q2 = square ? (float)tab->s[l] : pf, iq2 = square ? tab->inv_s[l] : inv;
       pass(0, q2, iq2, square ? q2 : (float)tab->kfold[l][1], pf, inv);
       pass(0, k <= (square ? 8192 : 256) ? 0.0f : pf, inv, 1.0f, pf, inv);

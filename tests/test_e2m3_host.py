@@ -168,3 +168,42 @@ def test_int8_fp64_residues():
         for v in x.tolist():
             q = np.rint(_fma(float(v), inv, 0.25 * inv))
             assert _fma(-q, float(p), float(v)) == _sym(v, p), (p, v)
+
+
+@pytest.mark.parametrize("k", [300, 3840, 4096, 32768, 65536, 98304, 131072, 2 ** 18])
+@pytest.mark.parametrize("p,kind,s", _moduli())
+def test_sums_of_chunked_passes(p, kind, s, k):
+    # A list item's three passes: chunks of 2^15, each but the last reduced modulo
+    # p, the last one by the pass's own fold.  Digit products of +-256 throughout
+    # (and +-255, for odd sums) keep every FP32 sum at most 2^24 and the residue
+    # exact.
+    chunk = 2 ** 15
+    last = 1
+    if kind == "square":
+        folds = [(p if k > chunk else 0, 1), (s, s), (p if k > 8192 else 0, 1)]
+    else:
+        i = lambda v: pow(v % p, -1, p)
+        sym = lambda v: int(_sym(np.int64(v), p))
+        if np.gcd(p, 15) == 1:
+            a, b, last = sym(15), sym(-16 * i(15)), sym(-15)
+        else:
+            a, b, last = sym(-16), sym(-15 * i(16)), sym(16)
+        folds = [(p if k > 3840 else 0, a), (p, b), (p if k > 256 else 0, 1)]
+    for prods in [(256, 256, 256), (-256, -256, 256), (255, 256, -255), (256, -255, 256)]:
+        acc, exact, top = np.float32(0), 0, 0
+        for (q, m), d in zip(folds, prods):
+            left = k
+            while left:
+                n = min(left, chunk)
+                # whole chunk at once: the sums on the way lie between its ends
+                top = max(top, abs(int(acc)), abs(int(acc) + n * d))
+                acc = np.float32(np.float64(acc) + n * d)
+                left -= n
+                r = q if left == 0 else p
+                if r:
+                    acc = np.float32(_reduce(np.array([acc], np.float64), r)[0])
+            acc = np.float32(acc * np.float32(m))
+            # (s X only counts modulo p)
+            exact = (exact + k * d) * m % p
+        assert top <= 2 ** 24
+        assert (int(acc) * last - exact * last) % p == 0

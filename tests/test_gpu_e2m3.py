@@ -3,6 +3,7 @@ ABI: the stored digits, the residue planes and C against the oracle, at the
 edges of its tiles, stages and scale range."""
 import numpy as np
 import pytest
+import torch
 
 import paper_2603_10634_amd as oz
 from oracle import ozaki2_ref as ref
@@ -157,3 +158,38 @@ def test_waves_without_outputs_in_a_batch():
                           [torch.from_numpy(b).cuda() for b in Bs], 12)
     for q, (a, b) in enumerate(zip(As, Bs)):
         assert same_bits(Cs[q].cpu().numpy(), ref.emulate(a, b, 12)), shapes[q]
+
+
+@pytest.mark.parametrize("k,config", [(65536, 0), (131072, 0), (131072, 1)])
+def test_square_cross_sums_over_chunks(k, config):
+    # an item of a batch over several chunks of 2^15 (config 1: two k parts of two
+    # chunks), residues 544 = 16 x 33 + 16 modulo 1089 on both sides: A1 B2 and
+    # A2 B1 sum to 2^23 per chunk, with odd remainders of the chunks before
+    one = np.full((1, k), 1.0625)
+    sc = ref.scaling(one, one.T.copy(), 12)
+    v = _residue_value(int(sc["sA"][0]), 544, 1089)
+    w = _residue_value(int(sc["sB"][0]), 544, 1089)
+    C1, st = ref.emulate(np.full((1, k), v), np.full((k, 1), w), 12, keep_stages=True)
+    pm = next(q for q in st["per_modulus"] if q["p"] == 1089)
+    assert [int(d[0, 0]) for d in (*pm["dA"], *pm["dB"])] == [16] * 4
+    A, B = np.full((70, k), v), np.full((k, 90), w)
+    A[1::2] *= -1.0
+    want = np.where(np.arange(70)[:, None] % 2, -C1[0, 0], C1[0, 0]) * np.ones((1, 90))
+    print(f"square sums over chunks k={k} config={config} v={v!r} w={w!r}", flush=True)
+    assert oz.ozaki2_set_schedule(config) == 0
+    try:
+        Cs = oz.dgemm_batched([torch.from_numpy(x).cuda() for x in (A, A[:3])],
+                              [torch.from_numpy(x).cuda() for x in (B, B[:, :5].copy())], 12)
+    finally:
+        oz.ozaki2_set_schedule(-1)
+    assert same_bits(Cs[0].cpu().numpy(), want)
+    assert same_bits(Cs[1].cpu().numpy(), want[:3, :5])
+
+
+def _residue_value(shift, target, p, base=1.0625):
+    """A value just above `base` whose integer trunc(v 2^shift) is congruent to
+    `target` modulo p."""
+    g = max(shift - 52, 0)
+    t = int(base * 2.0 ** (shift - g))
+    t += (target * pow(2 ** g, -1, p) - t) % p
+    return float(np.ldexp(float(t), g - shift))
