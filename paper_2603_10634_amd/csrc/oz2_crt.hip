@@ -9,8 +9,8 @@
 // RN(alpha Chat) (+ RN(beta C_in)).
 //
 // Nearly every entry is decided by crt_rn (balanced 40-bit limbs, sums of
-// doubles with their exact errors); the others (ties, tiny C' against P,
-// subnormal results) by 32-bit limbs and integer rounding (crt_exact).
+// doubles with their exact errors); the others (ties where P >= 2^96, tiny C'
+// against P, subnormal results) by 32-bit limbs and integer rounding (crt_exact).
 //
 // A thread computes two consecutive rows of a column, so that the planes are
 // read 4 bytes per lane, a wave 64 rows x 2 columns (outputs with few rows
@@ -128,8 +128,9 @@ __device__ __forceinline__ void crt_pair(const Problem &P, const Tables *__restr
     }
   double out[2];
   const int t[2] = {si.x + sj, si.y + sj};
-  bool ok = crt_rn<L>(acc[0], cP, inv_P, crt_fast, t[0], out[0]);
-  ok = crt_rn<L>(acc[1], cP, inv_P, crt_fast, t[1], out[1]) && ok;
+  constexpr bool exact = LL <= 3;  // (P < 2^96 in LL 40-bit limbs)
+  bool ok = crt_rn<L, exact>(acc[0], cP, inv_P, crt_fast, t[0], out[0]);
+  ok = crt_rn<L, exact>(acc[1], cP, inv_P, crt_fast, t[1], out[1]) && ok;
   if (!ok)
 #pragma unroll 1
     for (int z = 0; z < 2; ++z) {

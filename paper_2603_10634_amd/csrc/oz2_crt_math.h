@@ -198,19 +198,26 @@ __host__ __device__ __forceinline__ double two_sum(double x, double y, double &e
 // RN(C' 2^-t) for S = sum_q acc[q] of multiples of 2^(wbits q) (the sums of
 // cw[l][q] u_l, exact), where C' = S mods P; false if this does not decide it
 // (the caller then takes the exact integers).
-//   Q = rint(S / P) from the two highest sums: within 2^-40 of S / P, so D =
-//     S - Q P, limb by limb exact (one fused multiply-add each), is C' or off
-//     by P, and in that case |D| > P (1/2 - 2^-40);
+//   Q = rint(S / P) from the two highest sums, at most one off (what the lower
+//     ones add to S / P is 2^-5 and less), so D = S - Q P, limb by limb exact (one
+//     fused multiply-add each), is C' or off by P, and then |D| >= P / 2 lies above
+//     crt_fast;
 //   D = th + (tl + the lower errors), by exact additions of the limbs from the
-//     lowest up; the errors' sum v is off by less than 2^-50 m, m the largest
-//     of them, so RN(D) lies between RN(th + v - 2^-45 m) and RN(th + v + 2^-45
-//     m) and is both when they agree (they differ at ties, near ties, and when
-//     D is tiny against its limbs);
+//     lowest up; the errors' sum v is off by at most 27 2^-53 m for eight limbs, m
+//     the largest of them, so RN(D) lies between RN(th + v - 2^-45 m) and RN(th + v
+//     + 2^-45 m) and is both when they agree (they differ at ties, near ties, and
+//     when D is tiny against its limbs);
+//   EXACT: v is the errors' sum itself, and RN(th + v) is RN(D) at ties too.  So it
+//     is with one error, and with two where P < 2^96 (three 40-bit limbs): both are
+//     integers below 2^45.  A P of 2^55 .. 2^75 leaves many results 54 .. 58 bits,
+//     of which up to a half are ties, and one undecided entry costs its wave the
+//     integers (2304^2 outputs: hybrid N = 6 72 us, N = 7 86, INT8 N = 8 90);
 //   the scaling is exact for a normal result.
-template <int L>
+template <int L, bool EXACT = (L < 3)>
 __host__ __device__ __forceinline__ bool crt_rn(const double (&acc)[L],
                                                 const double *__restrict__ cP, double inv_P,
                                                 double crt_fast, int t, double &out) {
+  static_assert(L <= 3 || !EXACT, "more errors than add exactly");
   const double Q = rint((acc[L - 1] + (L > 1 ? acc[L > 1 ? L - 2 : 0] : 0.0)) * inv_P);
   double r[L];
 #pragma unroll
@@ -221,9 +228,10 @@ __host__ __device__ __forceinline__ bool crt_rn(const double (&acc)[L],
     double e;
     th = two_sum(r[q], th, e);
     v = q == 1 ? e : v + e;
-    m = q == 1 ? fabs(e) : fmax(m, fabs(e));
+    if (!EXACT) m = q == 1 ? fabs(e) : fmax(m, fabs(e));
   }
-  const double lo = th + fma(-0x1p-45, m, v), hi = th + fma(0x1p-45, m, v);
+  const double lo = th + (EXACT ? v : fma(-0x1p-45, m, v));
+  const double hi = EXACT ? lo : th + fma(0x1p-45, m, v);
   out = ldexp(lo, -t);
 #if defined(__HIP_DEVICE_COMPILE__)
   const int ex = __builtin_amdgcn_frexp_exp(lo);
