@@ -354,7 +354,7 @@ Problem make_problem(char transA, char transB, int64_t m, int64_t n, int64_t k, 
   P.mode = g_ts.mode;
   P.parts = L.parts;
   P.res_sides = 3;
-  P.stream_c = 8 * m * n >= kStreamC;
+  P.stream_c = past_caches(8 * m * n, (((uintptr_t)C | (uint64_t)ldc * 8) & 127) == 0, false);
   P.bparts = P.mode == OZ2_MODE_FAST ? 1 : L.bparts;
   P.g.fp6 = fp6;
   return P;
@@ -762,7 +762,7 @@ void build_subbatch(std::vector<Problem> probs, ImageWriter &W, SubBatch *sb) {
     tiles += res6_tiles(P);
   }
   for (Problem &P : probs) {
-    P.stream_c = c_bytes >= kStreamC;
+    P.stream_c = past_caches(c_bytes, false, true);
     P.more_tiles = (int32_t)std::min<int64_t>(tiles - res6_tiles(P), 1 << 30);
   }
   const int np = (int)probs.size();

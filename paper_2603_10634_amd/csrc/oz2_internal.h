@@ -134,7 +134,7 @@ struct Problem {
                        // many copies of the residue planes, each N mp np entries apart
   int32_t res_sides;   // operands whose residues are computed: 1 op(A), 2 op(B), 3 both
   int32_t more_tiles;  // residue-pass tiles of the other problems of the launch
-  int32_t stream_c;    // whether C is stored past the caches (kStreamC bytes of C in the call)
+  int32_t stream_c;    // whether C is stored past the caches (past_caches)
   int32_t bparts;      // k parts of the bound product (1: one pass with line maxima)
 };
 
@@ -196,13 +196,24 @@ enum Family : int {
   kNumFamilies
 };
 
-// A call whose C is larger than this stores it past the caches: its inputs, digits
-// and planes have gone through them since anything else was read, and the dirty C
-// would leave when the next call's inputs come in (16384 x 16384 x 1024: CRT 1.70
-// -> 1.57 ms and the next line pass 118 -> 67 us; 48 products with 126 MB of C: 117
-// -> 106 us).  Smaller ones may be read from there (3000 x 2000 x 256 with beta = 1,
-// 48 MB: 41.7 against 42.5 us).
-constexpr int64_t kStreamC = 64 << 20;
+// Whether C (c_bytes of it in the call, or in a batch's sub-batch) is stored past
+// the caches.  A large one leaves them before anyone reads it, and dirty it leaves
+// when the next call's inputs come in: 16384 x 16384 x 1024, CRT 1.70 -> 1.57 ms and
+// the next line pass 118 -> 67 us.  One that the 256 MB cache holds is there for
+// whoever reads it next, and that read counts as much as the call.  Call and one
+// read of C, ordinary against past the caches:
+//  - columns of whole 128-byte lines: 3072 x 3072 x 1024 (72 MB) 374 against 371 us,
+//    3840 x 3840 x 1024 (112 MB) 530 / 523, 4096 x 4096 x 256 330 / 319; the call alone
+//    341 / 334, 494 / 486, 277 / 276;
+//  - others (a line's pieces go to memory one by one): 3300 x 3300 x 64 (83 MB) 223 /
+//    230, 3700 x 3700 x 64 264 / 272, 4500 x 4500 x 256 (154 MB) 407 / 417, 4900 x 4900
+//    x 256 (183 MB) 483 / 464, 5700 x 5700 x 256 634 / 615;
+//  - batches (their first products are long stored when the call ends): 6 of 2048 x
+//    2048 x 128 (192 MB) 611 / 621, 14 of 1500 x 1500 x 256 (240 MB) 851 / 872, 24 (412
+//    MB) 1497 / 1472, 10 of 2048 x 2048 x 128 (320 MB) 1038 / 1014.
+inline bool past_caches(int64_t c_bytes, bool whole_lines, bool batch) {
+  return c_bytes >= (batch ? 256ll << 20 : whole_lines ? 64ll << 20 : 176ll << 20);
+}
 
 // k-split of the line-maxima pass: enough blocks for the chip, but at least
 // kLmaxK elements of a line per thread (64 threads' worth of 8 where k is
