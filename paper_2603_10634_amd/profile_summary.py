@@ -14,7 +14,7 @@
       scaled so that the plain 1 GiB device copy that bench.py
       --copy-calibration runs reads exactly 1 GiB fetched and 1 GiB written.
       OUT.json records the residue-product bytes per call (all launches)
-      with the SHA-256 of their source, so bench.py can tell whether the
+      with the SHA-256 of their sources, so bench.py can tell whether the
       counters still describe the built kernel.
 
 The counters report KiB per dispatch; rows are averaged over the dispatches
@@ -30,13 +30,19 @@ import sys
 from collections import defaultdict
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-GEMM_SOURCE = os.path.join(HERE, "csrc", "oz2_gemm6.hip")
+# the kernels of the residue products and their sources
+PRODUCT_KERNELS = ("k_residue6", "k_residue_small", "k_residue_gemm")
+GEMM_SOURCES = [os.path.join(HERE, "csrc", f)
+                for f in ("oz2_gemm6.hip", "oz2_small.hip", "oz2_gemm.hip")]
 COPY_BYTES = 1 << 30
 
 
 def gemm_source_sha() -> str:
-    with open(GEMM_SOURCE, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    h = hashlib.sha256()
+    for path in GEMM_SOURCES:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def short(name: str) -> str:
@@ -126,7 +132,7 @@ def traffic(d: str, fetch: str, write: str, out_md: str, out_json: str, cmd: str
             if fb + wb < 1e6:
                 continue
             f.write(f"| `{k[0]}` | {k[1]} | {fb / 1e6:.1f} | {wb / 1e6:.1f} |\n")
-            if k[0].startswith(("k_residue6", "k_residue_gemm")):
+            if k[0].startswith(PRODUCT_KERNELS):
                 gemm["fetch"] += fb
                 gemm["write"] += wb
     rec = {"kernel": "residue products of one call",
