@@ -10,9 +10,10 @@
  *      FP8 bound product (accurate mode) or from Cauchy-Schwarz norms (fast
  *      mode, Section III-E);
  *   2. residues of A', B' modulo the hybrid moduli 1089, 1024, 961, 841, 625,
- *      529, 511, 509, ... (Section III-D), split into FP8 E4M3 digits;
- *   3. three exact FP8 products per modulus on e4m3 MFMA with FP32
- *      accumulation (Sections III-B, III-C), reduced modulo p;
+ *      529, 511, 509, ... (Section III-D), split into digits of magnitude at most
+ *      16, exact in FP8 E4M3 and in the 6-bit E2M3;
+ *   3. three exact digit products per modulus on E2M3 (small outputs: E4M3) MFMA
+ *      with FP32 accumulation (Sections III-B, III-C), reduced modulo p;
  *   4. Chinese-remainder reconstruction (eq. CRT_finalreduction) and inverse
  *      scaling back to FP64 (eq. inversescaling), rounded once to nearest.
  *
@@ -100,7 +101,7 @@ int ozaki2_dgemm(char transA, char transB, int64_t m, int64_t n, int64_t k,
 /*
  * ozaki2_workspace_bytes - device workspace one ozaki2_dgemm call of this
  * shape needs (every dimension padded to a multiple of 256, as in the paper's
- * Section IV-C): the FP8 bound operands, the FP8 digit slices of both
+ * Section IV-C): the FP8 bound operands, the digit slices of both
  * operands, one int16 residue plane per modulus and k part of the residue
  * products (see ozaki2_set_split) and per-line vectors, for the calling
  * thread's modulus list (ozaki2_set_moduli_list), m/n blocking
@@ -177,11 +178,12 @@ int ozaki2_moduli(int num_moduli, int32_t *p, int32_t *kinds);
  *          k-blocked with n_pad lines
  *   off[5] uint8  [M x m_pad x k_pad]  digit slices of A' (slice order below), each
  *          k-blocked like Abar (INT8 residues as two's-complement bytes).  With
- *          more than four output tiles (m_pad n_pad / 65536) they are kept in
- *          fragments, from the same offset.  FP8 lists hold the digits as 6-bit
- *          E2M3 codes (sign, 5-bit magnitude), slice q at q (3/4) m_pad k_pad:
- *          line i, k h is code h % 32 (lowest bits first) of the 24 bytes of
- *          lane l = (i % 64) / 4 + 16 ((h % 128) / 32) in the 1536-byte fragment
+ *          more than four output tiles (m_pad n_pad / 65536), and in batched
+ *          calls throughout, they are kept in fragments, from the same offset.
+ *          FP8 lists hold the digits as 6-bit E2M3 codes (sign, 5-bit
+ *          magnitude), slice q at q (3/4) m_pad k_pad: line i, k h is code h % 32
+ *          (lowest bits first) of the 24 bytes of lane
+ *          l = (i % 64) / 4 + 16 ((h % 128) / 32) in the 1536-byte fragment
  *          i % 4 of line group i / 64 of 128-k stage h / 128 (stages outermost);
  *          a fragment holds the first 16 bytes of its 64 lanes, then their last
  *          8.  INT8 residues: byte h % 16 of the 16 bytes of lane
@@ -324,13 +326,14 @@ int ozaki2_set_schedule(int config);
 /*
  * ozaki2_set_split - number of k parts of the residue products of the
  * calling thread's subsequent ozaki2_dgemm (and ozaki2_dgemm_noalloc) calls.
- * Each modulus kind's products are one launch of (256 x 256 output tiles) x
- * (moduli of the kind) x (k parts) workgroups, one per CU at a time; part q
- * covers the q-th of `parts` near-equal ranges of 256-blocks of k and writes
- * its own copy of the residue planes, which the CRT sums modulo p.  More
+ * The products are one launch over (256 x 256 output tiles) x (moduli) x
+ * (k parts) items, one per CU at a time (outputs of few tiles in smaller ones);
+ * part q covers the q-th of `parts` near-equal ranges of 256-blocks of k and
+ * writes its own copy of the residue planes, which the CRT sums modulo p.  More
  * parts keep the CUs busy when the output has few tiles.  0 (default): the
- * library's rule, which minimises the launches' waves of workgroups per unit
- * of k over 1..8 parts of at least 2048 k each (1 part for large outputs).
+ * library's rule, which minimises the rounds of items per unit of k, counted for
+ * each kind of modulus, over 1..8 parts of at least 2048 k each (1 part for large
+ * outputs).
  * 1..8: that many parts (at most one per 256-block of k).  Every setting
  * gives bit-identical results; the workspace grows by 2 N mp np bytes per
  * part beyond the first.  Returns 0, or -1 for a value outside 0..8 (the
@@ -368,7 +371,7 @@ int ozaki2_get_mode(void);
  *        511, 509, 503, ... (Karatsuba split, s = 16).
  *   OZ2_MODULI_KARATSUBA  Section III-B: 513, 512, 511, 509, 505, ...
  *        (greedy pairwise coprime from 513), all with the Karatsuba split.
- *        Three FP8 products per modulus like the hybrid list, but a smaller
+ *        Three digit products per modulus like the hybrid list, but a smaller
  *        P for the same N (P/2 > 2^115 needs N = 13 instead of 12), so about
  *        one more modulus for the same accuracy: an ablation of the hybrid
  *        list's saving.
@@ -376,7 +379,7 @@ int ozaki2_get_mode(void);
  *        paper's baseline): 256, 255, 253, 251, 247, ... (greedy pairwise
  *        coprime from 256); each residue, in [-128, 127], is one INT8
  *        operand and each modulus costs ONE INT8 product (INT32
- *        accumulation, v_mfma_i32_32x32x32_i8).  P/2 > 2^109 needs N = 14.
+ *        accumulation on the INT8 MFMA).  P/2 > 2^109 needs N = 14.
  *        The scale exponents come from the same FP8 bound (or, in fast mode,
  *        the same norms) as the FP8 lists.
  * ozaki2_moduli reports kind 2 for INT8 moduli; the workspace holds one

@@ -89,18 +89,22 @@ int parts_alloc(int64_t m, int64_t n, int64_t k) {
   return tiles <= kSplitTiles && round_up(k, kPad) >= 2 * kPad ? kMaxParts : 1;
 }
 
-// Split-K in single calls: each modulus kind's residue products are one
-// launch of T tiles x n moduli workgroups (T tiles of 256 x 256 outputs in a
-// block), one per CU at a time.  When T n is small against the CU count the
-// launch leaves CUs idle for its whole k loop, so k is split into parts that
-// run as workgroups of their own, each into its own copy of the planes (the
+// Split-K in single calls: the residue products are T tiles (of 256 x 256
+// outputs in a block) x N moduli items, one per CU at a time.  When T N is small
+// against the CU count, CUs are idle for the whole k loop, so k is split into
+// parts that are items of their own, each into its own copy of the planes (the
 // CRT sums the copies).  Every part is at most kChunkK long (one exact FP32
 // accumulation), so there are at least ceil(kp / kChunkK) parts; above that
-// the number minimises the launches' waves of workgroups per unit of k,
-// sum over kinds of ceil(T n_kind parts / kCUs) / parts (ties to fewer
-// parts), with at least kMinPartK of k in every added part and at most
-// kMaxSplit parts (kMaxSplit kChunkK = OZ2_MAX_K).  A fixed CU count keeps
-// the workspace size a function of the shape alone.
+// the number minimises sum over kinds of ceil(T n_kind parts / kCUs) / parts
+// (ties to fewer parts), with at least kMinPartK of k in every added part and at
+// most kMaxSplit parts (kMaxSplit kChunkK = OZ2_MAX_K).  A fixed CU count keeps
+// the workspace size a function of the shape alone, and that size is what callers
+// and the entry point without allocation plan with: hence a rule that rounds up
+// per kind (square, Karatsuba, INT8), although all kinds are one launch.  It is
+// within 6 % of the best count's call: N = 12, products and CRT, 1024 x 1024 x
+// 65536 8 parts 1127 + 61 us, 4 parts 1117 + 34 (the call 2.6 ms); 512 x 512 x 32768
+// 389 + 39, 4 parts 355 + 18; 768 x 1024 x 40000 7 parts 584 + 50, 5 parts 575 + 37;
+// 512 x 256 x 65536 8 parts 394 + 30, 4 parts 530 + 18.
 constexpr int kMaxSplit = 8;
 constexpr int64_t kMinPartK = 2048;
 constexpr int64_t kCUs = 256;
@@ -298,10 +302,13 @@ bool is_trans(char c) { return !(c == 'N' || c == 'n'); }
 // block of a blocked call (every block of a call has the same format: op(A)'s
 // digits serve a whole row of blocks).  Results are the same bits.  Products of
 // 8192^3, N = 12: 8.55 against 12.7 ms, 4096^3 1.15 against 1.75, INT8 (N = 14)
-// 0.79 against 0.93.  Up to four tiles the slices stay in the k-blocked layout
-// that ozaki2_workspace_layout documents for inspection (their launches leave
-// most CUs idle in either format).  A batched call's are in fragment order
-// throughout: its problems share one persistent launch.
+// 0.79 against 0.93.  Up to four tiles the slices stay in the k-blocked layout that
+// ozaki2_workspace_layout documents for inspection, and that oz2_small.hip reads
+// where the small tiles pay (256^3: products 24 -> 9.8 us).  With few tiles and a
+// long k that costs time: whole calls of 512 x 512 x 32768 956 us against 704 in
+// fragment order, 256 x 1024 x 16384 609 / 476, 512 x 512 x 4096 168 / 141.  A batched
+// call's slices are in fragment order throughout: its problems share one persistent
+// launch.
 constexpr int64_t kBlockedTiles = 4;
 
 int use_fp6(int64_t mbp, int64_t nbp) {
@@ -1393,10 +1400,9 @@ int ozaki2_dgemm_batched(int count, const char *transA, const char *transB, cons
   // autotuner: on the first call of a new batch shape (no choice for its
   // exact shapes in this process, none for its shape bucket in the cache
   // file), run the first sub-batch's residue products under every
-  // configuration (tile program x split-K limit; the products are
-  // recomputed from the digit slices each time, into plane copies the CRT of
-  // the chosen configuration reads, so the result is the same) and keep the
-  // fastest
+  // configuration (split-K limit; the products are recomputed from the digit
+  // slices each time, into plane copies the CRT of the chosen configuration
+  // reads, so the result is the same) and keep the fastest
   if (plan->schedule < 0 && ts.autotune && ts.forced < 0 && !plan->subs.empty()) {
     r = ensure_events(dev);
     if (r != OZ2_SUCCESS) return r;

@@ -425,7 +425,7 @@ hipError_t launch_quant_family(int fam, const Problem *P, const Group *G, hipStr
 hipError_t launch_scale_family(int fam, const Problem *P, const Group *G, hipStream_t st);
 hipError_t launch_gemm_family(int fam, const Problem *P, const Group *G, hipStream_t st);
 // The residue products of a batch on at most `grid` persistent workgroups of nw
-// = 8 waves: int8 selects the INT8 arm's products (every item's modulus is then
+// waves (8: the one tile program): int8 selects the INT8 arm's products (every item's modulus is then
 // an INT8 one), else every item's modulus is a square or Karatsuba FP8 modulus
 // with E2M3 digits.
 hipError_t launch_gemm_persistent(int nw, bool int8, const WorkList &W, int64_t grid,

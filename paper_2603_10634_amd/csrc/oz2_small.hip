@@ -26,7 +26,6 @@ typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-
 __device__ __forceinline__ v16f mma(v8i a, v8i b, v16f c) {
   return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
 }
@@ -49,7 +48,8 @@ __device__ __forceinline__ float reduce(float x, float p, float inv) {
   return fmaf(-rintf(x * inv), p, x);
 }
 
-// The symmetric residue of an integer |x| < 2^28 as an int16: one FP64 step
+// The symmetric residue of an integer |x| < 2^30 (INT8 sums reach 2^29) as an int16:
+// one FP64 step
 // whose quotient is nudged by 1 / (4 p), so that an exact half (even p) goes to
 // -p / 2 and no other value (at least 1 / (2 p) from a half) moves.
 __device__ __forceinline__ int16_t residue(double x, double p, double inv) {
