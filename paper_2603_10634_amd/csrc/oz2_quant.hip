@@ -546,7 +546,7 @@ __device__ __forceinline__ void fp64_step(const ResidueIn &in, double R, double 
 
 template <int KIND, bool EVEN, bool HUGE>
 __device__ __forceinline__ void modulus_pass(const float (&f)[kRE], const ResidueIn &in,
-                                             const Tables *__restrict__ tab, int l, uint8_t *dst,
+                                             CTables *tab, int l, uint8_t *dst,
                                              int64_t slice_stride) {
   const int p = tab->p[l];
   const float pf = (float)p;
@@ -623,7 +623,7 @@ __device__ __forceinline__ void modulus_pass(const float (&f)[kRE], const Residu
 
 template <int KIND, bool HUGE>
 __device__ __forceinline__ void one_modulus(const float (&f)[kRE], const ResidueIn &in,
-                                            const Tables *__restrict__ tab, int l, uint8_t *base,
+                                            CTables *tab, int l, uint8_t *base,
                                             int64_t slice_stride) {
   uint8_t *dst = base + (int64_t)tab->slice0[l] * slice_stride;
   // p is uniform: the parity test is a branch, not a select
@@ -636,7 +636,7 @@ __device__ __forceinline__ void one_modulus(const float (&f)[kRE], const Residue
 // The moduli l0 .. l1 - 1 of one kind, two per FP64 step (one per step on
 // the rare path with t > 10, which holds more registers).
 template <int KIND, bool HUGE>
-__device__ __forceinline__ void kind_moduli(const ResidueIn &in, const Tables *__restrict__ tab,
+__device__ __forceinline__ void kind_moduli(const ResidueIn &in, CTables *tab,
                                             int l0, int l1, uint8_t *base, int64_t slice_stride) {
   int l = l0;
   for (; !HUGE && l + 1 < l1; l += 2) {
@@ -659,8 +659,10 @@ struct ModuliRange {
 
 __device__ __forceinline__ ModuliRange moduli_range(const Geometry &g, int64_t z, int64_t groups) {
   ModuliRange r;
-  r.l0 = (int)(z * g.N / groups);
-  r.l1 = (int)((z + 1) * g.N / groups);
+  // (a division, of 64 bits above all, is felt in a block of a few microseconds)
+  const uint32_t N = (uint32_t)g.N, n = (uint32_t)groups, q = (uint32_t)z;
+  r.l0 = n == 1 ? 0 : (int)(q * N / n);
+  r.l1 = n == 1 ? g.N : (int)((q + 1) * N / n);
   r.a = max(r.l0, min(r.l1, g.nsq));
   r.b = max(r.l0, min(r.l1, g.nsq + g.nka));
   return r;
@@ -668,7 +670,7 @@ __device__ __forceinline__ ModuliRange moduli_range(const Geometry &g, int64_t z
 
 // Those moduli of one thread's inputs, kind by kind.
 template <bool HUGE>
-__device__ __forceinline__ void residue_moduli(const ResidueIn &in, const Tables *__restrict__ tab,
+__device__ __forceinline__ void residue_moduli(const ResidueIn &in, CTables *tab,
                                                const ModuliRange &r, uint8_t *base,
                                                int64_t slice_stride) {
   kind_moduli<0, HUGE>(in, tab, r.l0, r.a, base, slice_stride);
@@ -702,16 +704,22 @@ __device__ __forceinline__ int final_shift(const Work &w, int64_t base, int64_t 
 __device__ __forceinline__ void residues_tile(const Operand &op, int64_t kp, int64_t lines_pad,
                                               int64_t r0, int64_t h0, const Work &w,
                                               int64_t base_line,
-                                              const Tables *__restrict__ tab,
+                                              CTables *tab,
                                               const ModuliRange &range,
                                               uint8_t *__restrict__ slices, double *tile) {
-  stage_tile(op, r0, h0, tile);
-  __syncthreads();
   // thread t: line t / 16, the kRE = 8 consecutive k (t % 16) * 8 .. + 7
   const int rl = threadIdx.x >> 4, b = threadIdx.x & 15;
   const int64_t r = r0 + rl;
-  int e;
-  const int s = final_shift(w, base_line, r, tab->D, h0 == 0 && b == 0, &e);  // log2(mu_r)
+  // asked for before the tile: after it, one after the other, they are two more
+  // latencies of a block that is mostly latency
+  const uint32_t flags = w.flags[base_line + r];
+  int s = w.shift[base_line + r];  // log2(mu_r)
+  stage_tile(op, r0, h0, tile);
+  __syncthreads();
+  if (flags & kFixup) {
+    int e;
+    s = final_shift(w, base_line, r, tab->D, h0 == 0 && b == 0, &e);
+  }
 
   ResidueIn in;
   bool huge = false;
@@ -737,16 +745,26 @@ __device__ __forceinline__ void residues_tile(const Operand &op, int64_t kp, int
     residue_moduli<false>(in, tab, range, base, slice_stride);
 }
 
-// (single problems only: a batch's slices are in fragment order)
+// (single problems only: a batch's slices are in fragment order)  The tables are read
+// through the constant address space: the stores of final_shift would otherwise make
+// every modulus' constants vector loads, waited for together with the stores before
+// them.  op(A)'s tiles first, then op(B)'s, each line by line at one k: in turn they
+// are two regions of memory at a time.  512 x 512 x 120000, N = 12: 906 us; with
+// vector loads of the tables 1308, with both sides in turn 941; INT8, N = 14: 600, 900
+// and 655.
 __global__ __launch_bounds__(256) void k_residues(Problem P) {
   __shared__ double tile[kQL * kRowLd];
-  const Dims d = family_dims(kFamRes, P), c = decode_block(d, blockIdx.x);
-  const int64_t r0 = c.x * kQL, by = c.y;
-  const int64_t first = P.res_sides & 1 ? P.g.mp : 0;
-  const bool side = r0 >= first;
-  residues_tile(operand(P, side), P.g.kp, side ? P.g.np : P.g.mp, side ? r0 - first : r0,
-                by * kQK, P.w, side ? P.w.lineB : 0, P.tab, moduli_range(P.g, c.z, d.z),
-                side ? P.w.Bsl : P.w.Asl, tile);
+  const Dims d = family_dims(kFamRes, P);
+  const uint32_t y = (uint32_t)d.y, per = (uint32_t)d.x * y;
+  const uint32_t z = d.z == 1 ? 0u : blockIdx.x / per;
+  const uint32_t xa = (uint32_t)(P.res_sides & 1 ? P.g.mp / kQL : 0);
+  uint32_t q = blockIdx.x - z * per;
+  const bool side = q >= xa * y;
+  if (side) q -= xa * y;
+  const uint32_t x = side ? (uint32_t)d.x - xa : xa, by = q / x;
+  residues_tile(operand(P, side), P.g.kp, side ? P.g.np : P.g.mp, (int64_t)(q - by * x) * kQL,
+                (int64_t)by * kQK, P.w, side ? P.w.lineB : 0, (CTables *)(uintptr_t)P.tab,
+                moduli_range(P.g, z, d.z), side ? P.w.Bsl : P.w.Asl, tile);
 }
 
 // ---- slices in fragment order ----
