@@ -641,18 +641,18 @@ __device__ __forceinline__ void int8_tile_w(const uint8_t *Asl, const uint8_t *B
 }
 
 // Residue products of one problem, 256 x 256 tiles, over the INT8 moduli
-// (INT8) or the FP8 moduli of either kind on E4M3 digits: modulus z mod N and
-// k part z / N of P.parts, whose copy of the planes the workgroup writes; the
+// (INT8) or the FP8 moduli of either kind on E4M3 digits: modulus l0 + z mod nl
+// and k part z / nl of P.parts, whose copy of the planes the workgroup writes; the
 // host makes every part at most kChunkK long.
 template <bool INT8>
-__global__ __launch_bounds__(64 * NW_RES, 1) void k_residue_gemm(Problem P) {
+__global__ __launch_bounds__(64 * NW_RES, 1) void k_residue_gemm(Problem P, int l0, int nl) {
   __shared__ __attribute__((aligned(1024))) uint8_t lds[LDS_RING];
   const Geometry &g = P.g;
   const Dims d = family_dims(kFamGemm8, P);
   const Dims c = decode_block(d, blockIdx.x);
   const int64_t mp = uni(g.mp), np = uni(g.np), kp = uni(g.kp);
-  const int part = (int)uni(c.z / g.N);
-  const int l = (int)uni(c.z % g.N);
+  const int part = (int)uni(c.z / nl);
+  const int l = (int)uni(l0 + c.z % nl);
   int64_t k0, k1;
   part_range(kp, (int)uni((int64_t)P.parts), part, &k0, &k1);
   const int nk = (int)uni((k1 - k0) / BK);
@@ -854,6 +854,29 @@ __global__ __launch_bounds__(64 * NW_BOUND) void k_bound_reduce(Problem P) {
 
 }  // namespace
 
+// k_residue_gemm over every modulus, in one launch or, where that takes no more
+// rounds of one workgroup per CU, the squares first and then the Karatsuba moduli:
+// a full round is bound by the chip's power, one of 192 workgroups by its CUs, so
+// 192 + 192 beat 256 + 128.  N = 12, k = 120000, 8 parts: 512 x 512 1468 us in one
+// launch, 1233 in two; 250 x 700 (288 workgroups) 1265 and 1019; N = 33, 4 parts, 512
+// x 512 (96 + 432) 4731 and 4164.
+static hipError_t launch_residue_gemm(const Problem &P, hipStream_t st) {
+  constexpr int64_t cus = 256;
+  const int64_t per = P.g.mp / kGemmTIW * (P.g.np / kGemmTJ) * P.parts;  // per modulus
+  auto rounds = [&](int64_t moduli) { return (per * moduli + cus - 1) / cus; };
+  const int N = P.g.N, nsq = P.g.nsq;
+  const bool two = nsq > 0 && nsq < N && rounds(nsq) + rounds(N - nsq) <= rounds(N);
+  const dim3 blk(64 * NW_RES);
+  for (int l0 = 0; l0 < N;) {
+    const int nl = !two ? N : l0 == 0 ? nsq : N - nsq;
+    hipLaunchKernelGGL((k_residue_gemm<false>), dim3((unsigned)(per * nl)), blk, 0, st, P, l0, nl);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    l0 += nl;
+  }
+  return hipSuccess;
+}
+
 hipError_t launch_gemm_persistent(int nw, bool int8, const WorkList &W, int64_t grid,
                                   hipStream_t st) {
   if (nw != 8) return hipErrorInvalidValue;
@@ -892,10 +915,9 @@ hipError_t launch_gemm_family(int fam, const Problem *P, const Group *G, hipStre
       hipLaunchKernelGGL(k_bound_reduce, gr, blk, 0, st, p1);
       break;
     case kFamGemm8:
-      hipLaunchKernelGGL((k_residue_gemm<false>), gr, blk, 0, st, p1);
-      break;
+      return launch_residue_gemm(p1, st);
     case kFamGemmI8:
-      hipLaunchKernelGGL((k_residue_gemm<true>), gr, blk, 0, st, p1);
+      hipLaunchKernelGGL((k_residue_gemm<true>), gr, blk, 0, st, p1, 0, p1.g.N);
       break;
     default:
       return hipErrorInvalidValue;

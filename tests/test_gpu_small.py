@@ -46,3 +46,22 @@ def test_bound_of_many_tiles(m, n, k):
     e, f = r.lines(2)
     assert np.array_equal(e, st["e"]) and np.array_equal(f, st["f"])
     assert same_bits(r.C, C)
+
+
+@pytest.mark.parametrize("moduli,N,parts", [
+    ("hybrid", 12, 5),      # 240 workgroups
+    ("hybrid", 12, 6),      # 144 + 144
+    ("hybrid", 24, 5),      # 480 (120 + 360 would be three rounds)
+    ("karatsuba", 13, 6),
+])
+def test_rounds_of_tiles(moduli, N, parts):
+    # four 256 x 256 tiles whose k parts fill one round of the CUs, or more than
+    # one (the squares and the Karatsuba moduli are then launched one after the
+    # other where that takes no more rounds)
+    A, B = phi_matrix(400, 1700, 1.0, 9900), phi_matrix(1700, 300, 1.0, 9901)
+    print(f"rounds of tiles {moduli} N={N} parts={parts}", flush=True)
+    with split(parts):
+        r = run(A, B, N, "T", "N", keep_ws=True, moduli=moduli)
+        assert r.status == 0 and r.parts == parts
+        check_stages(r, A, B, N, moduli=moduli)
+        assert same_bits(r.C, ref.emulate(A, B, N, moduli_set=moduli))
