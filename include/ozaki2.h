@@ -327,7 +327,8 @@ int ozaki2_set_schedule(int config);
  * ozaki2_set_split - number of k parts of the residue products of the
  * calling thread's subsequent ozaki2_dgemm (and ozaki2_dgemm_noalloc) calls.
  * The products are one launch over (256 x 256 output tiles) x (moduli) x
- * (k parts) items, one per CU at a time (outputs of few tiles in smaller ones);
+ * (k parts) items, one per CU at a time (outputs of few tiles in smaller ones, or
+ * kind by kind);
  * part q covers the q-th of `parts` near-equal ranges of 256-blocks of k and
  * writes its own copy of the residue planes, which the CRT sums modulo p.  More
  * parts keep the CUs busy when the output has few tiles.  0 (default): the

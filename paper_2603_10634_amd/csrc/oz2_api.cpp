@@ -100,11 +100,11 @@ int parts_alloc(int64_t m, int64_t n, int64_t k) {
 // most kMaxSplit parts (kMaxSplit kChunkK = OZ2_MAX_K).  A fixed CU count keeps
 // the workspace size a function of the shape alone, and that size is what callers
 // and the entry point without allocation plan with: hence a rule that rounds up
-// per kind (square, Karatsuba, INT8), although all kinds are one launch.  It is
-// within 6 % of the best count's call: N = 12, products and CRT, 1024 x 1024 x
-// 65536 8 parts 1127 + 61 us, 4 parts 1117 + 34 (the call 2.6 ms); 512 x 512 x 32768
-// 389 + 39, 4 parts 355 + 18; 768 x 1024 x 40000 7 parts 584 + 50, 5 parts 575 + 37;
-// 512 x 256 x 65536 8 parts 394 + 30, 4 parts 530 + 18.
+// per kind (square, Karatsuba, INT8), although beyond four tiles all kinds are one
+// launch.  It is within 4 % of the best count's call: products and CRT, 1024 x 1024
+// x 65536 (N = 12) 8 parts 1150 + 60 us, 4 parts 1136 + 34 (the call 2.6 ms); 1280 x
+// 1024 x 16384 (N = 14) 8 parts 492 + 113, 5 parts 484 + 72 (the call 1.4 ms); 512 x
+// 512 x 32768 8 parts 355 + 38, 4 parts 346 + 18 (0.9 ms).
 constexpr int kMaxSplit = 8;
 constexpr int64_t kMinPartK = 2048;
 constexpr int64_t kCUs = 256;
@@ -305,8 +305,8 @@ bool is_trans(char c) { return !(c == 'N' || c == 'n'); }
 // 0.79 against 0.93.  Up to four tiles the slices stay in the k-blocked layout that
 // ozaki2_workspace_layout documents for inspection, and that oz2_small.hip reads
 // where the small tiles pay (256^3: products 24 -> 9.8 us).  With few tiles and a
-// long k that costs time: whole calls of 512 x 512 x 32768 956 us against 704 in
-// fragment order, 256 x 1024 x 16384 609 / 476, 512 x 512 x 4096 168 / 141.  A batched
+// long k that costs time: whole calls of 512 x 512 x 32768 852 us against 704 in
+// fragment order, 256 x 1024 x 16384 545 / 476, 512 x 512 x 4096 168 / 141.  A batched
 // call's slices are in fragment order throughout: its problems share one persistent
 // launch.
 constexpr int64_t kBlockedTiles = 4;
