@@ -13,7 +13,7 @@ from test_crt_host import CSRC, LISTS, ROOT, SANITIZE, _bits, _rn, _smod
 
 
 @pytest.fixture(scope="module")
-def checker(tmp_path_factory):
+def host_crt(tmp_path_factory):
     out = str(tmp_path_factory.mktemp("crt_small") / "crt_small_host_check")
     cmd = ["g++", "-O1", "-g", *SANITIZE, "-ffp-contract=off", "-std=c++17",
            "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + CSRC,
@@ -24,7 +24,7 @@ def checker(tmp_path_factory):
 
 
 @pytest.mark.parametrize("moduli", ["hybrid", "karatsuba", "int8"])
-def test_every_value_is_decided(checker, moduli):
+def test_every_value_is_decided(host_crt, moduli):
     rng = random.Random(8300 + LISTS[moduli])
     for N in range(1, 34):
         mods = [p for p, _, _ in ref.moduli_table(N, moduli)]
@@ -42,7 +42,7 @@ def test_every_value_is_decided(checker, moduli):
         ts = [rng.randrange(-900, 900) for _ in cases]
         text = "\n".join(" ".join(str(v) for v in [t] + [_smod(c, p) for p in mods])
                          for c, t in zip(cases, ts))
-        res = subprocess.run([checker, str(N), str(LISTS[moduli])], input=text + "\n",
+        res = subprocess.run([host_crt, str(N), str(LISTS[moduli])], input=text + "\n",
                              capture_output=True, text=True, check=True)
         got = [x.split() for x in res.stdout.splitlines()]
         assert len(got) == len(cases)
